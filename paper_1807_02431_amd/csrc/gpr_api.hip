@@ -38,6 +38,11 @@ struct gpr_system {
     int bt_persist = 0;
     int groups = 1;            // workgroups per replica on the persistent path
     Split split{};             // their atom ranges
+    Split splits[4]{};         // the atom ranges with 1, 2, 4 and 8 workgroups per replica
+    bool split_ok[4]{};        // whether a workgroup of that split fits on a compute unit
+    // whose choice the launch shape is: 0 the library's, for the replicas of each launch
+    // (run_shape), 1 the autotuner's, for launches of all replicas, 2 the caller's, for every launch
+    int bt_from = 0, groups_from = 0;
     std::vector<double> work;  // per-atom work estimate that places the ranges
     // force-field parameters as the caller gave them (gpr_set_params rewrites the device copies)
     std::vector<double> mass_h, eps_h, sig_h, q_h, tor_k_h, tor_phi0_h;
@@ -45,9 +50,8 @@ struct gpr_system {
     std::vector<int2> p14_h;
     double scale14 = 0.0;
     int max_coresident = 0;    // persistent-kernel workgroups that fit on the device at once
-    int cap_bt = -1;           // persist_capacity: the launch shape last asked for and its capacity
-    size_t cap_lds = 0;
-    int cap_blocks = 0;
+    struct Cap { int bt; size_t lds; int blocks; };
+    std::vector<Cap> caps;     // persist_capacity: the launch shapes asked for and their capacities
     int n = 0, R = 0, np = 0, kind = 0, nobs = 0;
     int t_gr = 1, tcd = 1, tcp = 1;
     double tol = 0, dt = 0, kT = 0;
@@ -82,10 +86,11 @@ struct gpr_system {
     double *obs_out = nullptr;
     int *donor = nullptr, *surv = nullptr;
     long long *fec = nullptr;
-    size_t lds_persist = 0, lds_nb = 0, lds_stage = 0;
+    size_t lds_nb = 0, lds_stage = 0;
     int maxlds = 0;            // LDS bytes one workgroup may use on this device
     int maxlds_persist = 0;    // of which k_persist may allocate dynamically
     int persist_ok = 0;
+    bool small_ok = false;     // the system may run k_persist_small (with one workgroup per replica)
     // event timing of the dominant stepping kernel
     bool prof = false;
     std::vector<hipEvent_t> ev_a, ev_b;
@@ -259,6 +264,49 @@ static size_t persist_lds(int n, int np, const Split &sp)
            (size_t)2 * lmax;
 }
 
+// LDS of k_persist_small (the order of small_lds_layout) and its units of work per step
+static size_t small_lds(const gpr_system *S)
+{
+    const Topo &T = S->d.tp;
+    const size_t n = S->n, np = S->np, nterm = (size_t)T.nt + T.na + T.n14 + T.nb + T.nr;
+    return 16 * np + 16 * nterm + 48 * n + 64 + 24 * MAX_OBS + 8 * np + 8 * 64 * ((n + 15) / 16) + 8 * nterm + 32 * n;
+}
+static int small_units(const gpr_system *S)
+{
+    const Topo &T = S->d.tp;
+    auto blocks = [](int c) { return (c + 63) / 64; };
+    return blocks(T.nt) + blocks(T.na) + blocks(T.n14) + blocks(T.nb) + blocks(T.nr) + blocks(S->n) +
+           (S->kind == GPR_KIND_TOY2D ? 0 : (S->n + 15) / 16);
+}
+// Launch shape of a persistent launch of one system's first nrep replicas.  Unless the caller (or
+// the autotuner) chose it:
+//   threads of k_persist_small: a wave per unit of a step's work, fewer where the replicas outnumber
+//   the compute units, so that they run side by side (16 waves fit on one at its register count;
+//   1,024 replicas of 22 atoms: 3.6 us per step with 4 waves each, 4.3 with 2, 4.9 with 7).
+struct RunShape {
+    int bt;
+    const Split *sp;
+    bool small;                // k_persist_small, else k_persist
+    size_t lds;
+};
+static RunShape run_shape(const gpr_system *S, int nrep)
+{
+    auto chosen = [&](int from) { return from == 2 || (from == 1 && nrep == S->R); };
+    const int cus = std::max(1, S->max_coresident);
+    RunShape sh{S->bt_persist, &S->split, false, 0};
+    if (S->small_ok && S->groups == 1) {
+        sh.small = true;
+        if (!chosen(S->bt_from)) {
+            const int waves = std::min(16, std::max(small_units(S), S->nobs));
+            sh.bt = 64 * std::max(1, std::min(waves, 16 / ((nrep + cus - 1) / cus)));
+        }
+        sh.lds = small_lds(S);
+        return sh;
+    }
+    sh.lds = persist_lds(S->n, S->np, *sh.sp);
+    return sh;
+}
+
 // ------------------------------------------------------------------ force-field parameters
 // Device copies of the per-atom parameters (sigma/2, 2 sqrt(eps), q sqrt(f), 1/m), the torsion
 // parameters (k, cos phi0, sin phi0, n) and the 1-4 pair parameters (sigma_ij, 4 eps_ij s14,
@@ -330,19 +378,17 @@ static gpr_status launch_forces(gpr_system *S, int r_off, int nrep, long long s,
 // advances replicas [0, nrep) by nsteps from local step counter t0; sample: accumulate the
 // observables of workers every t_gr; state_end: state ids at the end
 // Workgroups of the persistent kernel that the device holds at once for (bt, lds): the
-// occupancy query, kept per system for the last launch shape asked for.
+// occupancy query, kept per system and launch shape.
 static gpr_status persist_capacity(gpr_system *S, int bt, size_t lds, int &cap)
 {
-    if (S->cap_bt != bt || S->cap_lds != lds) {
-        int dev = 0, cus = 0, per_cu = 0;
-        HIPCHK(S, hipGetDevice(&dev));
-        HIPCHK(S, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        HIPCHK(S, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_persist, bt, lds));
-        S->cap_bt = bt;
-        S->cap_lds = lds;
-        S->cap_blocks = per_cu * cus;
-    }
-    cap = S->cap_blocks;
+    for (const auto &c : S->caps)
+        if (c.bt == bt && c.lds == lds) { cap = c.blocks; return GPR_OK; }
+    int dev = 0, cus = 0, per_cu = 0;
+    HIPCHK(S, hipGetDevice(&dev));
+    HIPCHK(S, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    HIPCHK(S, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_persist, bt, lds));
+    S->caps.push_back({bt, lds, per_cu * cus});
+    cap = per_cu * cus;
     return GPR_OK;
 }
 
@@ -355,13 +401,13 @@ static gpr_status persist_capacity(gpr_system *S, int bt, size_t lds, int &cap)
 // the barrier's bounded spin, the call reports GPR_EDEVICE, never hangs.)  No cooperative
 // launch: it adds tens of microseconds to each launch and is refused while another process
 // holds the device's cooperative resources.
-static gpr_status persist_item(gpr_system *S, int nrep, int bt, size_t lds, int cap_blocks, PersistItem &it,
-                               int &nblocks)
+static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt, size_t lds, int cap_blocks,
+                               PersistItem &it, int &nblocks)
 {
-    const int G = S->groups;
+    const int G = sp.G;
     it = PersistItem{};
     it.dev = S->d_dev;
-    it.sp = S->split;
+    it.sp = sp;
     it.nrep = nrep;
     it.boff = 0;
     if (G == 1 && cap_blocks < 0) {
@@ -418,17 +464,19 @@ static gpr_status check_layout(gpr_system *S, const PersistBatch &pb, int nblock
     return GPR_OK;
 }
 
-// One item whose sets each take one replica (roff + set) runs k_persist; anything else
+// One item whose sets each take one replica (roff + set) runs k_persist, or k_persist_small when
+// its shape `one` says so; anything else
 // (several systems, or sets that take replicas in turn) runs k_persist_batch.
 static gpr_status launch_persist(gpr_system *S, PersistBatch &pb, int nblocks, int bt, size_t lds,
-                                 hipStream_t stream, bool one_round = false)
+                                 hipStream_t stream, const RunShape *one = nullptr)
 {
-    const bool single = pb.nitems == 1 && (one_round || pb.it[0].nsets >= pb.it[0].nrep);
+    const bool single = pb.nitems == 1 && (one || pb.it[0].nsets >= pb.it[0].nrep);
     {
         const gpr_status rc = check_layout(S, pb, nblocks, bt, single);
         if (rc) return rc;
     }
-    const void *fn = single ? (const void *)k_persist : (const void *)k_persist_batch;
+    const void *fn = !single ? (const void *)k_persist_batch
+                             : one && one->small ? (const void *)k_persist_small : (const void *)k_persist;
     void *args_single[] = {(void *)&pb.it[0]};
     void *args_batch[] = {(void *)&pb};
     void **args = single ? args_single : args_batch;
@@ -530,8 +578,8 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
         PersistBatch pb{};
         pb.nitems = 1;
         int nblocks = 0;
-        const size_t lds = persist_lds(S->n, S->np, S->split);
-        gpr_status rc = persist_item(S, nrep, S->bt_persist, lds, -1, pb.it[0], nblocks);
+        const RunShape sh = run_shape(S, nrep);
+        gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, pb.it[0], nblocks);
         if (rc) return rc;
         // more replicas than sets that fit at once: rounds of launches, each set taking one
         // replica per launch (replicas are independent between checks)
@@ -549,7 +597,7 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
             for (int k = 0; k < rounds; ++k) {
                 it.roff = k * it.nsets;
                 HIPCHK(S, prof_begin(S));
-                rc = launch_persist(S, pb, nblocks, S->bt_persist, lds, S->stream, true);
+                rc = launch_persist(S, pb, nblocks, sh.bt, sh.lds, S->stream, &sh);
                 if (rc) return rc;
                 HIPCHK(S, prof_end(S));
             }
@@ -981,6 +1029,17 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     }
     S->bt_persist = std::min(1024, std::max(64, (n * P + 63) / 64 * 64));
     {
+        hipFuncAttributes fa{};
+        HIPCHK(S, hipFuncGetAttributes(&fa, (const void *)k_persist_small));
+        const int room = maxlds - (int)fa.sharedSizeBytes;
+        HIPCHK(S, hipFuncSetAttribute((const void *)k_persist_small, hipFuncAttributeMaxDynamicSharedMemorySize, room));
+        // Every pair is evaluated, so the limit is where lists come out cheaper (measured, us per
+        // step of 64 replicas, small / general kernel at its best shape): with a cutoff 3.4 / 6.4 at
+        // 80 atoms, 5.0 / 7.1 at 128, 7.2 / 7.7 at 160, 11.2 / 9.0 at 200; without one 2.0 / 4.7 at
+        // 22, 3.0 / 5.1 at 60, 5.3 / 7.3 at 128, 13.9 / 15.7 at 256 (one group per replica).
+        S->small_ok = n <= (d.cutoff_on ? 160 : SMALL_MAX) && small_lds(S) <= (size_t)room;
+    }
+    {
         // persistent split: the fewest workgroups per replica (1, 2, 4 or 8) whose LDS fits, then
         // more while each keeps >= 256 atoms; with more than one, every workgroup of the grid
         // must be resident at once (the grid is sized to what the device holds)
@@ -990,7 +1049,8 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         // usable: the LDS fits and a workgroup can run; all_at_once: every replica's workgroups are
         // resident together (with fewer, sets of workgroups take the replicas in turn)
         auto usable = [&](int G, bool &ok, bool &all_at_once) -> hipError_t {
-            const size_t lds = persist_lds(n, np, make_split(S->work, n, np, G));
+            const int k = G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3;
+            const size_t lds = persist_lds(n, np, S->splits[k]);
             ok = all_at_once = false;
             if ((int)lds > S->maxlds_persist) return hipSuccess;
             int per_cu = 0;
@@ -1000,6 +1060,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
             all_at_once = ok && (G == 1 || (long)R * G <= (long)per_cu * cus);
             return e;
         };
+        for (int k = 0; k < 4; ++k) S->splits[k] = make_split(S->work, n, np, 1 << k);
         int G = 1;
         bool ok = false, all = false;
         for (; G <= 8; G *= 2) {
@@ -1019,7 +1080,10 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         }
         S->groups = G;
         S->split = make_split(S->work, n, np, G);
-        S->lds_persist = persist_lds(n, np, S->split);
+        for (int k = 0; k < 4; ++k) {
+            bool all2 = false;
+            HIPCHK(S, usable(1 << k, S->split_ok[k], all2));
+        }
     }
 
     // initial velocities, copies into every replica, forces, Omega and the observable shift
@@ -1144,7 +1208,9 @@ extern "C" gpr_status gpr_set_launch(gpr_system *S, int32_t block_threads, int32
     }
     drop_cycle_graphs(S);                                   // captured with the old shape
     S->bt_persist = bt;
+    if (block_threads != 0) S->bt_from = 2;
     if (groups_per_replica != 0) {
+        S->groups_from = 2;
         S->groups = groups_per_replica;
         S->split = make_split(S->work, S->n, S->np, groups_per_replica);
     }
@@ -1201,6 +1267,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
     HIPCHK(S, copy_all(true));
     const long long s_saved = S->s;
     const int path_saved = S->path, bt_saved = S->bt_persist, g_saved = S->groups;
+    const int btf_saved = S->bt_from, gf_saved = S->groups_from;
     const Split sp_saved = S->split;
     int dev = 0, cus = 0;
     HIPCHK(S, hipGetDevice(&dev));
@@ -1212,6 +1279,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
     int best_bt = bt_saved, best_g = g_saved;
     gpr_status rc = GPR_OK;
     S->path = GPR_PATH_PERSISTENT;
+    S->bt_from = S->groups_from = 1;                       // the shapes tried, then the one kept
     for (int G = 1; G <= 8 && rc == GPR_OK; G *= 2) {
         const Split sp = make_split(S->work, S->n, S->np, G);
         const size_t lds = persist_lds(S->n, S->np, sp);
@@ -1248,6 +1316,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
     HIPCHK(S, copy_all(false));
     if (rc) {
         S->bt_persist = bt_saved; S->groups = g_saved; S->split = sp_saved;
+        S->bt_from = btf_saved; S->groups_from = gf_saved;
         return rc;
     }
     S->bt_persist = best_bt;
@@ -1766,11 +1835,11 @@ static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
     PersistBatch pb{};
     pb.nitems = 1;
     int nblocks = 0;
-    const size_t lds = persist_lds(S->n, S->np, S->split);
-    gpr_status rc = persist_item(S, nrep, S->bt_persist, lds, -1, pb.it[0], nblocks);
+    const RunShape sh = run_shape(S, nrep);
+    gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, pb.it[0], nblocks);
     if (rc) return rc;
     const int rounds = (nrep + pb.it[0].nsets - 1) / pb.it[0].nsets;
-    rc = check_layout(S, pb, nblocks, S->bt_persist, true);
+    rc = check_layout(S, pb, nblocks, sh.bt, true);
     if (rc) return rc;
     const dim3 cgrid = dep ? dim3((3 * S->np + 255) / 256, nrep) : dim3(1, 1);
     hipStream_t cs = nullptr;
@@ -1784,7 +1853,8 @@ static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
         for (int k = 0; k < rounds && e == hipSuccess; ++k) {
             it.roff = k * it.nsets;
             void *args[] = {(void *)&it};
-            e = hipLaunchKernel((const void *)k_persist, dim3(nblocks), dim3(S->bt_persist), args, lds, cs);
+            e = hipLaunchKernel(sh.small ? (const void *)k_persist_small : (const void *)k_persist, dim3(nblocks), dim3(sh.bt),
+                                args, sh.lds, cs);
         }
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(k_check, cgrid, dim3(256), sizeof(int) * nrep, cs, S->d_dev, dep ? CHK_DEPHASE : CHK_PARALLEL,
@@ -2085,7 +2155,8 @@ static gpr_status batch_layout(gpr_system *const *systems, int32_t nsys, const s
     std::vector<int> nb(nsys, 0);
     for (int k = 0; k < nsys; ++k) {
         if (nrep[k] <= 0) continue;
-        gpr_status rc = persist_item(systems[k], nrep[k], sh.bt, sh.lds, sets[k] * systems[k]->groups, items[k], nb[k]);
+        gpr_status rc = persist_item(systems[k], systems[k]->split, nrep[k], sh.bt, sh.lds, sets[k] * systems[k]->groups,
+                                     items[k], nb[k]);
         if (rc) return rc;
     }
     slot.assign(nsys, -1);

@@ -208,7 +208,12 @@ __device__ __forceinline__ long long fix_f(float f)
     return __double_as_longlong(y) - 0x4338000000000000LL;
 }
 __device__ __forceinline__ long long fix_d(double d) { return __double2ll_rn(d * FIX); }
-__device__ __forceinline__ float unfix_f(long long a) { return (float)((double)a * FIX_INV); }
+// (float)((double)a 2^-32), the sum of the two halves rounded once to FP64 by one FMA instead of a
+// conversion of the whole word, which scales and adds them in separate instructions
+__device__ __forceinline__ float unfix_f(long long a)
+{
+    return (float)__builtin_fma((double)(uint32_t)a, FIX_INV, (double)(int)(a >> 32));
+}
 __device__ __forceinline__ double unfix_d(long long a) { return (double)a * FIX_INV; }
 
 __device__ __forceinline__ void lds_add(long long *p, long long v)

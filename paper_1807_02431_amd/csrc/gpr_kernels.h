@@ -72,6 +72,9 @@ struct PersistItem {
     const CycRec *cyc;  // non-null: cycle `cycle` of a captured run (s0 and t0 from the record)
     int cycle;
 };
+// k_persist_small: one workgroup per replica of a system of at most SMALL_MAX atoms (the partner
+// masks have 64 bits per lane and an atom four lanes, so 256 at most)
+constexpr int SMALL_MAX = 256;
 constexpr int MAX_BATCH = 8;
 struct PersistBatch {
     int nitems;
@@ -101,6 +104,7 @@ __host__ __device__ inline bool persist_place(const PersistItem &it, int local, 
 }
 
 __global__ void k_persist(PersistItem it);
+__global__ void k_persist_small(PersistItem it);
 __global__ void k_persist_batch(PersistBatch pb);
 __global__ void k_grad_nb(const Dev *__restrict__ Sp, const double *w);
 __global__ void k_grad_terms(const Dev *__restrict__ Sp, const double *w);

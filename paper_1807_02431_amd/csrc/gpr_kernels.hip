@@ -551,8 +551,9 @@ __device__ __forceinline__ IntConsts int_consts(const Dev &S)
     return k;
 }
 
-__device__ __forceinline__ void integrate_baoa_k(const IntConsts &K, int a, int r, long long s, float3 &x, float3 &v,
-                                                 float3 F, float im, float sd)
+// the step with its Gaussians g given (drawn for (atom, step, replica) beforehand or by the caller)
+__device__ __forceinline__ void integrate_baoa_g(const IntConsts &K, float3 &x, float3 &v, float3 F, float im, float sd,
+                                                 float3 g)
 {
     const float h = K.h, c1 = K.c1;
     v.x = kick(v.x, F.x, h, im);
@@ -561,13 +562,23 @@ __device__ __forceinline__ void integrate_baoa_k(const IntConsts &K, int a, int 
     x.x = x.x + h * v.x;
     x.y = x.y + h * v.y;
     x.z = x.z + h * v.z;
-    const float3 g = gauss3(philox_ctr((uint32_t)a, s, (uint32_t)r, STREAM_NOISE, K.key0, K.key1));
     v.x = c1 * v.x + sd * g.x;
     v.y = c1 * v.y + sd * g.y;
     if (!K.toy) v.z = c1 * v.z + sd * g.z;
     x.x = x.x + h * v.x;
     x.y = x.y + h * v.y;
     x.z = x.z + h * v.z;
+}
+
+__device__ __forceinline__ float3 step_noise(const IntConsts &K, int a, int r, long long s)
+{
+    return gauss3(philox_ctr((uint32_t)a, s, (uint32_t)r, STREAM_NOISE, K.key0, K.key1));
+}
+
+__device__ __forceinline__ void integrate_baoa_k(const IntConsts &K, int a, int r, long long s, float3 &x, float3 &v,
+                                                 float3 F, float im, float sd)
+{
+    integrate_baoa_g(K, x, v, F, im, sd, step_noise(K, a, r, s));
 }
 
 __device__ __forceinline__ void integrate_baoa(const Dev &S, int a, int r, long long s, float3 &x, float3 &v,
@@ -1606,6 +1617,17 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
 #endif
 }
 
+// The first step and local step of cycle it.cycle of a captured run; false after the check that
+// ended the call
+__device__ __forceinline__ bool cycle_start(const PersistItem &it, long long &s0, int &t0)
+{
+    if (it.cyc->halt_cycle < it.cycle) return false;
+    const long long first = (long long)it.cycle * it.nsteps;
+    s0 = it.cyc->s_start + first;
+    t0 = (int)((it.cyc->t_start + first) % it.dev->t_gr);
+    return true;
+}
+
 // One system, one replica per set: replicas roff, roff + 1, ... (a system with more replicas
 // than sets that fit at once takes several launches, each with the body inlined).
 __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
@@ -1614,15 +1636,411 @@ __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
     if (!persist_place(it, (int)blockIdx.x, set, g) || set + it.roff >= it.nrep) return;
     long long s0 = it.s0;
     int t0 = it.t0;
-    if (it.cyc) {
-        // cycle of a captured run: nothing after the check that ended the call
-        if (it.cyc->halt_cycle < it.cycle) return;
-        const long long first = (long long)it.cycle * it.nsteps;
-        s0 = it.cyc->s_start + first;
-        t0 = (int)((it.cyc->t_start + first) % it.dev->t_gr);
-    }
+    if (it.cyc && !cycle_start(it, s0, t0)) return;
     persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], set + it.roff, g, s0, it.nsteps,
                     t0, it.sample, it.state_end);
+}
+
+// ------------------------------------------------------------------ small systems
+// A step of a small replica (one workgroup) is a chain of latencies, not work: on the general body
+// it waits for list words and terms read from memory, runs the Philox rounds before every drift
+// and passes six barriers.  Here everything a step reads is in LDS for the whole launch, the step
+// has two barriers, and between them each wave takes units of independent work:
+//   a block of 64 bonded terms of one kind; a pair task (16 atoms on 64 lanes, all partners in the
+//   sub-list order of the pair lists: lane 4 (i - i0) + q runs over j = q, q + 4, ... with the
+//   partners outside the list, the cutoff or the system adding an exact zero); the Gaussians of
+//   the next step for 64 atoms.
+// The arithmetic, its order and the fixed-point sums are the general body's, so are the bits.
+// Pairs are not listed (up to SMALL_MAX atoms running over all of them costs less than reading a
+// list), so the launch leaves a system with a cutoff marked for a list rebuild.
+struct SmallLds {
+    long long *fa;              // [2][3][n] force accumulators: one read, the other being summed
+    long long *red;             // [8] scratch of the state test
+    double *acc, *shift;        // [MAX_OBS][2], [MAX_OBS]
+    float4 *xs;                 // [np]
+    float2 *pp;                 // [np]
+    unsigned long long *am;     // [64 ceil(n / 16)] bit k: partner 4 k + q of the lane's atom counts
+    float4 *tp;                 // [nterm] parameters of the bonded terms
+    uint2 *ti;                  // [nterm] their atoms, 16 bits each
+    float *vs, *im, *sd, *gn;   // [3][n], [n], [n], [3][n]: velocities, 1/m, noise amplitudes, Gaussians
+};
+
+__device__ __forceinline__ SmallLds small_lds_layout(unsigned char *raw, int n, int np, int nterm)
+{
+    SmallLds L;
+    L.xs = (float4 *)raw;
+    L.tp = L.xs + np;
+    L.fa = (long long *)(L.tp + nterm);
+    L.red = L.fa + 6 * n;
+    L.acc = (double *)(L.red + 8);
+    L.shift = L.acc + 2 * MAX_OBS;
+    L.pp = (float2 *)(L.shift + MAX_OBS);
+    L.am = (unsigned long long *)(L.pp + np);
+    L.ti = (uint2 *)(L.am + 64 * ((n + 15) >> 4));
+    L.vs = (float *)(L.ti + nterm);
+    L.im = L.vs + 3 * n;
+    L.sd = L.im + n;
+    L.gn = L.sd + n;
+    return L;
+}
+
+// Observable j of the replica by one wave (the value is valid in lane 0); the sums over atoms are
+// the integer sums of observables_wg, in another order
+__device__ double small_observable(const Dev &S, const ObsDesc &o, const SmallLds &L, double U, int lane)
+{
+    const int n = S.n;
+    auto vel2 = [&](int a) {
+        const double vx = L.vs[a], vy = L.vs[n + a], vz = L.vs[2 * n + a];
+        return vx * vx + vy * vy + vz * vz;
+    };
+    auto com = [&](int off, int cnt, double m, double &cx, double &cy, double &cz) {
+        long long s0 = 0, s1 = 0, s2 = 0;
+        for (int k = lane; k < cnt; k += 64) {
+            const int a = S.groups[off + k];
+            const double ma = (double)S.mass[a];
+            s0 += fix_d(ma * (double)L.xs[a].x);
+            s1 += fix_d(ma * (double)L.xs[a].y);
+            s2 += fix_d(ma * (double)L.xs[a].z);
+        }
+        cx = unfix_d(wave_sum_ll(s0)) / m;
+        cy = unfix_d(wave_sum_ll(s1)) / m;
+        cz = unfix_d(wave_sum_ll(s2)) / m;
+    };
+    switch (o.kind) {
+    case OB_COORD: {
+        const float4 p = L.xs[o.atoms[0]];
+        return o.atoms[1] == 0 ? (double)p.x : (o.atoms[1] == 1 ? (double)p.y : (double)p.z);
+    }
+    case OB_POT: return U;
+    case OB_KIN: {
+        long long s = 0;
+        for (int a = lane; a < n; a += 64) s += fix_d(0.5 * (double)S.mass[a] * vel2(a));
+        return unfix_d(wave_sum_ll(s));
+    }
+    case OB_DIH: return dihedral_d(xs_d(L.xs, o.atoms[0]), xs_d(L.xs, o.atoms[1]), xs_d(L.xs, o.atoms[2]), xs_d(L.xs, o.atoms[3]));
+    case OB_COMD: {
+        double ax, ay, az, bx, by, bz;
+        com(o.ga_off, o.ga_n, o.ma, ax, ay, az);
+        com(o.gb_off, o.gb_n, o.mb, bx, by, bz);
+        return sqrt((ax - bx) * (ax - bx) + (ay - by) * (ay - by) + (az - bz) * (az - bz));
+    }
+    case OB_RMSV: {
+        long long s = 0;
+        for (int k = lane; k < o.ga_n; k += 64) s += fix_d(vel2(S.groups[o.ga_off + k]));
+        return sqrt(unfix_d(wave_sum_ll(s)) / (double)o.ga_n);
+    }
+    default: return 0.0;
+    }
+}
+
+// The pairs of one lane with its nk partners xj[4 k], k = 0, 1, ... (staged far away past n), those
+// not in the mask adding an exact zero
+template <bool ENERGY>
+__device__ __forceinline__ void small_pairs(const float4 pi, const float2 ppi, const float4 *xj, const float2 *pj,
+                                            unsigned long long m, int nk, float rc2, float krf2, float krf, float crf,
+                                            float &fx, float &fy, float &fz, float &e)
+{
+    auto pair = [&](int k, int bit) {
+        const float lim = __uint_as_float(__float_as_uint(rc2) & (0u - (((unsigned)m >> bit) & 1u)));
+        pair_term(pi, ppi, xj[4 * k], pj[4 * k], lim, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+    };
+    int k = 0;
+    for (; k + 4 <= nk; k += 4, m >>= 4) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) pair(k + w, w);
+    }
+    if (nk & 2) { pair(k, 0); pair(k + 1, 1); k += 2; m >>= 2; }
+    if (nk & 1) pair(k, 0);
+}
+
+__device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0, int nsteps, int t0, int sample,
+                                              int state_end)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int sbuf;
+    __shared__ long long eacc[2];
+    const int tid = threadIdx.x, BT = blockDim.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = BT >> 6;
+    const int n = S.n, np = S.np;
+    const bool toy = S.kind == KIND_TOY;
+    const Topo &T = S.tp;
+    const int nt = T.nt, na = T.na, n14 = T.n14, nb = T.nb, nr = T.nr;
+    const SmallLds L = small_lds_layout(lds_raw, n, np, nt + na + n14 + nb + nr);
+#ifdef GPR_PHASE_PROBE
+    __shared__ unsigned long long ph_acc[NPHASE + 1];
+    if (tid < NPHASE) ph_acc[tid] = 0;
+    if (tid == 0) ph_acc[NPHASE] = ph_acc[PH_START] = __builtin_amdgcn_s_memrealtime();
+#endif
+    const size_t b = (size_t)r * 3 * np;
+    const IntConsts ik = int_consts(S);
+    const float rc2 = S.rc2, krf = S.krf, krf2 = 2.0f * S.krf, crf = S.crf;
+    const int t_gr = S.t_gr, need_energy = S.need_energy;
+    int *const errp = S.err;
+    const int npt = toy ? 0 : (n + 15) >> 4;
+
+    // stage the replica and its terms
+    stage_replica(S, r, L.xs, L.pp, tid, BT);
+    for (int a = tid; a < n; a += BT) {
+        const float3 g = step_noise(ik, a, r, s0);
+        for (int d = 0; d < 3; ++d) {
+            L.vs[d * n + a] = gconst(S.v)[b + d * np + a];
+            L.fa[d * n + a] = gconst(S.F)[b + d * np + a];
+            L.fa[(3 + d) * n + a] = 0;
+        }
+        L.im[a] = gld(gconst(S.prm) + a).w;
+        L.sd[a] = gconst(S.sd)[a];
+        L.gn[a] = g.x; L.gn[n + a] = g.y; L.gn[2 * n + a] = g.z;
+    }
+    auto pack = [](int i, int j, int k, int l) { return make_uint2((unsigned)i | ((unsigned)j << 16), (unsigned)k | ((unsigned)l << 16)); };
+    for (int t = tid; t < nt; t += BT) {
+        const int4 q = gld(gconst(T.t_ijkl) + t);
+        L.ti[t] = pack(q.x, q.y, q.z, q.w);
+        L.tp[t] = gld(gconst(T.t_p) + t);
+    }
+    for (int t = tid; t < na; t += BT) {
+        const int4 q = gld(gconst(T.a_ijk) + t);
+        const float2 p = gld(gconst(T.a_p) + t);
+        L.ti[nt + t] = pack(q.x, q.y, q.z, 0);
+        L.tp[nt + t] = make_float4(p.x, p.y, 0.f, 0.f);
+    }
+    for (int t = tid; t < n14; t += BT) {
+        const int2 q = gld(gconst(T.p_ij) + t);
+        L.ti[nt + na + t] = pack(q.x, q.y, 0, 0);
+        L.tp[nt + na + t] = gld(gconst(T.p_p) + t);
+    }
+    for (int t = tid; t < nb; t += BT) {
+        const int2 q = gld(gconst(T.b_ij) + t);
+        const float2 p = gld(gconst(T.b_p) + t);
+        L.ti[nt + na + n14 + t] = pack(q.x, q.y, 0, 0);
+        L.tp[nt + na + n14 + t] = make_float4(p.x, p.y, 0.f, 0.f);
+    }
+    for (int t = tid; t < nr; t += BT) {
+        L.ti[nt + na + n14 + nb + t] = pack(gconst(T.r_i)[t], 0, 0, 0);
+        L.tp[nt + na + n14 + nb + t] = gld(gconst(T.r_p) + t);
+    }
+    // partners of lane (i, q): every j = 4 k + q < n but itself, the excluded and the 1-4 ones
+    for (int c = tid; c < 64 * npt; c += BT) {
+        const int i = c >> 2, q = c & 3;
+        unsigned long long m = 0ull;
+        if (i < n) {
+            const unsigned long long ex = gconst(S.excl)[i] | (1ull << 32);
+            for (int k = 0; 4 * k + q < n; ++k) {
+                const int off = 4 * k + q - i + 32;
+                const bool drop = (unsigned)off < 64u && ((ex >> off) & 1ull);
+                m |= (unsigned long long)!drop << k;
+            }
+            if (S.has_far)
+                for (int f = gconst(S.far_start)[i]; f < gconst(S.far_start)[i + 1]; ++f) {
+                    const int j = gconst(S.far_j)[f];
+                    if ((j & 3) == q) m &= ~(1ull << (j >> 2));
+                }
+        }
+        L.am[c] = m;
+    }
+    if (tid < 2 * MAX_OBS) L.acc[tid] = S.acc[(size_t)r * 2 * MAX_OBS + tid];
+    if (tid < MAX_OBS) L.shift[tid] = S.shift[tid];
+    if (tid < 2) eacc[tid] = 0;
+    __syncthreads();
+    PHASE_MARK(PH_PROLOGUE);
+
+    // units of a step, the longest first: torsions, pair tasks, angles, noise, 1-4, bonds, restraints
+    const int u0 = (nt + 63) >> 6, u1 = u0 + npt, u2 = u1 + ((na + 63) >> 6), u3 = u2 + ((n + 63) >> 6), u4 = u3 + ((n14 + 63) >> 6), u5 = u4 + ((nb + 63) >> 6), u6 = u5 + ((nr + 63) >> 6);
+    bool pend = false;                                      // the previous step's closing B is due
+    int cur = 0;                                            // accumulators holding the last forces
+    for (int step = 0; step < nsteps; ++step) {
+        const bool samp = sample && r >= 1 && ((t0 + step + 1) % t_gr == 0);
+        const bool energy = samp && need_energy;
+        // B A O A; the accumulators read here are cleared while the others are being summed
+        long long *const f0 = L.fa + 3 * n * cur;
+        bool bad = false;
+        for (int a = tid; a < n; a += BT) {
+            float3 x = make_float3(L.xs[a].x, L.xs[a].y, L.xs[a].z);
+            float3 v = make_float3(L.vs[a], L.vs[n + a], L.vs[2 * n + a]);
+            const float3 F = make_float3(unfix_f(f0[a]), unfix_f(f0[n + a]), unfix_f(f0[2 * n + a]));
+            const float im = L.im[a];
+            if (pend) {
+                v.x = kick(v.x, F.x, ik.h, im);
+                v.y = kick(v.y, F.y, ik.h, im);
+                v.z = kick(v.z, F.z, ik.h, im);
+                bad |= bad_force(F.x) || bad_force(F.y) || bad_force(F.z);
+            }
+            integrate_baoa_g(ik, x, v, F, im, L.sd[a], make_float3(L.gn[a], L.gn[n + a], L.gn[2 * n + a]));
+            L.xs[a].x = x.x; L.xs[a].y = x.y; L.xs[a].z = x.z;
+            L.vs[a] = v.x; L.vs[n + a] = v.y; L.vs[2 * n + a] = v.z;
+            bad |= !(finite3(x) && finite3(v));
+        }
+        if (bad) atomicOr(&errp[ERR_UNSTABLE], 1);
+        cur ^= 1;
+        long long *const fa = L.fa + 3 * n * cur;
+        __syncthreads();
+        PHASE_MARK(PH_INTEGRATE);
+        auto add = [&](int a, float3 f) {
+            lds_add(&fa[a], fix_f(f.x));
+            lds_add(&fa[n + a], fix_f(f.y));
+            lds_add(&fa[2 * n + a], fix_f(f.z));
+        };
+        const PosLDS pos{L.xs};
+        long long e = 0;
+        for (int u = wv; u < u6; u += nwv) {
+            if (u >= u0 && u < u1) {
+                const int i = 16 * (u - u0) + (lane >> 2), q = lane & 3;
+                const float4 pi = L.xs[i];
+                const float2 ppi = L.pp[i];
+                const unsigned long long m = L.am[64 * (u - u0) + lane];
+                float fx = 0.f, fy = 0.f, fz = 0.f, ep = 0.f;
+                if (energy) small_pairs<true>(pi, ppi, L.xs + q, L.pp + q, m, (n + 3) >> 2, rc2, krf2, krf, crf, fx, fy, fz, ep);
+                else small_pairs<false>(pi, ppi, L.xs + q, L.pp + q, m, (n + 3) >> 2, rc2, krf2, krf, crf, fx, fy, fz, ep);
+                fx = quad_sum(fx);
+                fy = quad_sum(fy);
+                fz = quad_sum(fz);
+                if (energy) ep = quad_sum(ep);
+                // one lane of the atom per component
+                if (i < n && q < 3) lds_add(&fa[q * n + i], fix_f(q == 0 ? fx : (q == 1 ? fy : fz)));
+                if (energy && i < n && q == 3) e += fix_f(ep);
+            } else if (u < u0) {
+                const int t = 64 * u + lane;
+                if (t < nt) {
+                    const uint2 w = L.ti[t];
+                    const int i = w.x & 0xFFFF, j = w.x >> 16, k = w.y & 0xFFFF, l = w.y >> 16;
+                    float3 fi, fj, fk, fl;
+                    const float ut = term_torsion(pos(i), pos(j), pos(k), pos(l), L.tp[t], fi, fj, fk, fl);
+                    add(i, fi);
+                    add(j, fj);
+                    add(k, fk);
+                    add(l, fl);
+                    e += fix_f(ut);
+                }
+            } else if (u < u2) {
+                const int t = 64 * (u - u1) + lane;
+                if (t < na) {
+                    const uint2 w = L.ti[nt + t];
+                    const float4 p = L.tp[nt + t];
+                    const int i = w.x & 0xFFFF, j = w.x >> 16, k = w.y & 0xFFFF;
+                    float3 fi, fk;
+                    const float ut = term_angle(pos(i), pos(j), pos(k), make_float2(p.x, p.y), fi, fk);
+                    add(i, fi);
+                    add(k, fk);
+                    add(j, make_float3(-fi.x - fk.x, -fi.y - fk.y, -fi.z - fk.z));
+                    e += fix_f(ut);
+                }
+            } else if (u < u3) {
+                // the next step's Gaussians, and the clearing of the forces just used
+                const int a = 64 * (u - u2) + lane;
+                if (a < n) {
+                    f0[a] = f0[n + a] = f0[2 * n + a] = 0;
+                    const float3 g = step_noise(ik, a, r, s0 + step + 1);
+                    L.gn[a] = g.x; L.gn[n + a] = g.y; L.gn[2 * n + a] = g.z;
+                    if (a == 0) eacc[cur ^ 1] = 0;
+                    if (toy) {
+                        float3 f = make_float3(0.f, 0.f, 0.f);
+                        e += fix_f(toy_force(L.xs[0].x, L.xs[0].y, f.x, f.y));
+                        fa[0] = fix_f(f.x);
+                        fa[n] = fix_f(f.y);
+                    }
+                }
+            } else if (u < u4) {
+                const int t = 64 * (u - u3) + lane;
+                if (t < n14) {
+                    const uint2 w = L.ti[nt + na + t];
+                    float3 fi;
+                    const float ut = term_pair14(pos(w.x & 0xFFFF), pos(w.x >> 16), L.tp[nt + na + t], fi);
+                    add(w.x & 0xFFFF, fi);
+                    add(w.x >> 16, neg3(fi));
+                    e += fix_f(ut);
+                }
+            } else if (u < u5) {
+                const int t = 64 * (u - u4) + lane;
+                if (t < nb) {
+                    const uint2 w = L.ti[nt + na + n14 + t];
+                    const float4 p = L.tp[nt + na + n14 + t];
+                    float3 fi;
+                    const float ut = term_bond(pos(w.x & 0xFFFF), pos(w.x >> 16), make_float2(p.x, p.y), fi);
+                    add(w.x & 0xFFFF, fi);
+                    add(w.x >> 16, neg3(fi));
+                    e += fix_f(ut);
+                }
+            } else {
+                const int t = 64 * (u - u5) + lane;
+                if (t < nr) {
+                    const int i = L.ti[nt + na + n14 + nb + t].x;
+                    const float4 p = L.tp[nt + na + n14 + nb + t];
+                    const float3 x = pos(i);
+                    const float dx = x.x - p.x, dy = x.y - p.y, dz = x.z - p.z;
+                    add(i, make_float3(-p.w * dx, -p.w * dy, -p.w * dz));
+                    e += fix_f(0.5f * p.w * (dx * dx + dy * dy + dz * dz));
+                }
+            }
+        }
+        if (energy) {
+            e = wave_sum_ll(e);
+            if (lane == 0 && e != 0) lds_add(&eacc[cur], e);
+        }
+        __syncthreads();
+        PHASE_MARK(PH_FORCES);
+        // the closing B: here when the step's velocities are read, else by the next integrator
+        pend = !(samp || step + 1 == nsteps);
+        if (!pend) {
+            for (int a = tid; a < n; a += BT) {
+                const float im = L.im[a];
+                const float Fx = unfix_f(fa[a]), Fy = unfix_f(fa[n + a]), Fz = unfix_f(fa[2 * n + a]);
+                L.vs[a] = kick(L.vs[a], Fx, ik.h, im);
+                L.vs[n + a] = kick(L.vs[n + a], Fy, ik.h, im);
+                L.vs[2 * n + a] = kick(L.vs[2 * n + a], Fz, ik.h, im);
+                if (bad_force(Fx) || bad_force(Fy) || bad_force(Fz)) atomicOr(&errp[ERR_UNSTABLE], 1);
+            }
+        }
+        if (samp) {
+            // one wave per observable, its sums kept in LDS
+            __syncthreads();
+            for (int j = wv; j < S.nobs; j += nwv) {
+                const double val = small_observable(S, S.obs[j], L, unfix_d(eacc[cur]), lane);
+                if (lane == 0) {
+                    const double xj = val - L.shift[j];
+                    L.acc[2 * j] += xj;
+                    const double x2 = xj * xj;
+                    L.acc[2 * j + 1] += x2;
+                }
+            }
+            __syncthreads();
+        }
+        PHASE_MARK(PH_TAIL);
+        PHASE_COUNT(PH_NSTEP);
+    }
+    __syncthreads();
+    const long long *const fl = L.fa + 3 * n * cur;
+    for (int a = tid; a < n; a += BT) {
+        gmut(S.x)[b + a] = L.xs[a].x; gmut(S.x)[b + np + a] = L.xs[a].y; gmut(S.x)[b + 2 * np + a] = L.xs[a].z;
+        for (int d = 0; d < 3; ++d) {
+            gmut(S.v)[b + d * np + a] = L.vs[d * n + a];
+            gmut(S.F)[b + d * np + a] = fl[d * n + a];
+        }
+    }
+    if (sample && r >= 1 && tid < 2 * S.nobs) S.acc[(size_t)r * 2 * MAX_OBS + tid] = L.acc[tid];
+    if (S.cutoff_on && tid == 0 && nsteps > 0) S.need_build[r] = 1;
+    if (state_end) {
+        const int id = state_wg(S, L.xs, L.red, &sbuf, tid, BT);
+        if (tid == 0) S.state[r] = id;
+    }
+#ifdef GPR_PHASE_PROBE
+    PHASE_MARK(PH_EPILOGUE);
+    if (tid == 0 && r < PHASE_MAX_R) {
+        unsigned long long *acc = gpr_phase_acc + (size_t)r * PHASE_MAX_G * NPHASE;
+        for (int k = 0; k < PH_START; ++k) acc[k] += ph_acc[k];
+        acc[PH_START] = ph_acc[PH_START];
+        acc[PH_END] = __builtin_amdgcn_s_memrealtime();
+    }
+#endif
+}
+
+// One workgroup per replica (sp.G = 1): replica roff + blockIdx.x
+__global__ void __launch_bounds__(1024) k_persist_small(PersistItem it)
+{
+    const int r = (int)blockIdx.x + it.roff;
+    if (r >= it.nrep) return;
+    long long s0 = it.s0;
+    int t0 = it.t0;
+    if (it.cyc && !cycle_start(it, s0, t0)) return;
+    persist_small(*it.dev, r, s0, it.nsteps, t0, it.sample, it.state_end);
 }
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
