@@ -280,6 +280,10 @@ static int small_units(const gpr_system *S)
 }
 // Launch shape of a persistent launch of one system's first nrep replicas.  Unless the caller (or
 // the autotuner) chose it:
+//   workgroups per replica: those of a launch of all replicas, doubled while all workgroups of the
+//   launch still get a compute unit of their own and a group keeps 64 atoms (measured, us per step:
+//   one replica of 2,432 atoms 20.7 with 4 groups, 14.9 with 8; 8 replicas of 1,200 atoms 15.3 and
+//   12.1; 24 replicas of 300 atoms 10.6, 9.3, 8.3 and 8.6 with 1, 2, 4 and 8, where 8 leave 38 atoms);
 //   threads of k_persist_small: a wave per unit of a step's work, fewer where the replicas outnumber
 //   the compute units, so that they run side by side (16 waves fit on one at its register count;
 //   1,024 replicas of 22 atoms: 3.6 us per step with 4 waves each, 4.3 with 2, 4.9 with 7).
@@ -303,6 +307,11 @@ static RunShape run_shape(const gpr_system *S, int nrep)
         sh.lds = small_lds(S);
         return sh;
     }
+    if (!chosen(S->groups_from))
+        for (int k = 1; k < 4; ++k) {
+            const int G = 1 << k;
+            if (G > sh.sp->G && S->split_ok[k] && S->n >= 64 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
+        }
     sh.lds = persist_lds(S->n, S->np, *sh.sp);
     return sh;
 }
