@@ -23,6 +23,7 @@ using namespace gpr;
 namespace {
 
 constexpr double COULOMB_F = 138.935458;
+constexpr double margin_heavy = 1.35;
 enum { PH_IDLE = 0, PH_DECORR = 1, PH_DEPHASE = 2, PH_CONVERGED = 3, PH_PARALLEL = 4, PH_DEPHASE_FIXED = 5 };
 
 thread_local std::string g_thread_err;
@@ -44,6 +45,16 @@ struct gpr_system {
     // (run_shape), 1 the autotuner's, for launches of all replicas, 2 the caller's, for every launch
     int bt_from = 0, groups_from = 0;
     std::vector<double> work;  // per-atom work estimate that places the ranges
+    // bonded terms in the sorted order (kinds as in the bonded units), and the units laid out so far
+    std::vector<int4> term_idx[5];
+    std::vector<float4> term_prm[5];
+    struct Units {
+        std::vector<int> src;  // per record: 5 * (sorted term) + kind, or -1
+        std::vector<int> first;// first unit of each range, and the end
+        uint2 *bi = nullptr;
+        float4 *bp = nullptr;
+    };
+    Units units_plain, units_split[4];
     // force-field parameters as the caller gave them (gpr_set_params rewrites the device copies)
     std::vector<double> mass_h, eps_h, sig_h, q_h, tor_k_h, tor_phi0_h;
     std::vector<int> tor_n_h, tor_order, p14_order;   // sorted term -> caller's index
@@ -149,26 +160,16 @@ bool idx_ok(const int32_t *a, long cnt, int n)
     return true;
 }
 
-// sorts terms of width w by their smallest atom; returns order, start offsets, span
-void sort_terms(const int32_t *atoms, int cnt, int w, int n, std::vector<int> &order, std::vector<int> &start, int &span)
+// the order of terms of width w by their smallest atom
+void sort_terms(const int32_t *atoms, int cnt, int w, std::vector<int> &order)
 {
     order.resize(cnt);
     std::vector<int> mn(cnt);
-    span = 0;
     for (int t = 0; t < cnt; ++t) {
-        int lo = atoms[t * w], hi = atoms[t * w];
-        for (int k = 1; k < w; ++k) { lo = std::min(lo, (int)atoms[t * w + k]); hi = std::max(hi, (int)atoms[t * w + k]); }
-        mn[t] = lo;
-        span = std::max(span, hi - lo);
+        mn[t] = *std::min_element(atoms + t * w, atoms + (t + 1) * w);
         order[t] = t;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return mn[a] < mn[b]; });
-    start.assign(n + 1, cnt);
-    int t = 0;
-    for (int a = 0; a <= n; ++a) {
-        while (t < cnt && mn[order[t]] < a) ++t;
-        start[a] = t;
-    }
 }
 
 long long count_samples(long long t_old, long long t_new, int t_gr) { return t_new / t_gr - t_old / t_gr; }
@@ -255,6 +256,8 @@ static Split make_split(const std::vector<double> &work, int n, int np, int G)
     return sp;
 }
 
+static int split_index(int G) { return G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3; }
+
 static size_t persist_lds(int n, int np, const Split &sp)
 {
     const int lmax = sp.lmax;
@@ -316,6 +319,90 @@ static RunShape run_shape(const gpr_system *S, int nrep)
     return sh;
 }
 
+// ------------------------------------------------------------------ bonded units
+// The terms touching each of the atom ranges [bnd[k], bnd[k + 1]) in units of 64 terms of one kind
+// (the records of gpr_device.h): first the terms inside the range, the longest kinds first, then
+// those that reach outside it; a term's energy counts in the range that holds its smallest atom.
+static void write_units(const gpr_system *S, const std::vector<int> &bnd, gpr_system::Units &U, std::vector<uint2> &bi)
+{
+    const int nr = (int)bnd.size() - 1;
+    auto range_of = [&](int a) { return (int)(std::upper_bound(bnd.begin() + 1, bnd.end(), a) - bnd.begin()) - 1; };
+    // terms of (range, kind, inside or edge)
+    std::vector<std::vector<int>> in((size_t)nr * 10);
+    for (int k = 0; k < 5; ++k)
+        for (int t = 0; t < (int)S->term_idx[k].size(); ++t) {
+            const int4 q = S->term_idx[k][t];
+            const int at[4] = {q.x, q.y, q.z, q.w};
+            int rg[4], m = 0;
+            for (int a : at) {
+                if (a < 0) continue;
+                const int r = range_of(a);
+                if (std::find(rg, rg + m, r) == rg + m) rg[m++] = r;
+            }
+            for (int j = 0; j < m; ++j) in[(size_t)rg[j] * 10 + k + (m > 1 ? BONDED_EDGE : 0)].push_back(t);
+        }
+    U.first.assign(1, 0);
+    for (int r = 0; r < nr; ++r) {
+        for (int kk : {2, 7, 1, 6, 4, 9, 0, 5, 3, 8}) {
+            const std::vector<int> &l = in[(size_t)r * 10 + kk];
+            const int k = kk % 5;
+            const size_t cnt = (l.size() + 63) / 64 * 64;
+            for (size_t c = 0; c < cnt; ++c) {
+                const unsigned kind0 = (unsigned)(kk & 3) << 14, kind1 = (unsigned)(kk >> 2) << 14;
+                unsigned f[4] = {kind0, kind1, 0u, 0u};
+                if (c < l.size()) {
+                    const int4 q = S->term_idx[k][l[c]];
+                    const int at[4] = {q.x, q.y, q.z, q.w};
+                    int mn = q.x;
+                    for (int j = 0; j < 4; ++j) {
+                        if (at[j] < 0) continue;
+                        mn = std::min(mn, at[j]);
+                        f[j] |= (unsigned)at[j] | (at[j] >= bnd[r] && at[j] < bnd[r + 1] ? (unsigned)BONDED_ATOMS : 0u);
+                    }
+                    f[2] |= (mn >= bnd[r] && mn < bnd[r + 1] ? 0x4000u : 0u) | 0x8000u;
+                }
+                bi.push_back(make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16)));
+                U.src.push_back(c < l.size() ? 5 * l[c] + k : -1);
+            }
+        }
+        U.first.push_back((int)(U.src.size() / 64));
+    }
+}
+
+// the records' parameters, from the terms' current ones (nothing for units not laid out)
+static hipError_t write_unit_params(gpr_system *S, const gpr_system::Units &U)
+{
+    if (!U.bp || U.src.empty()) return hipSuccess;
+    std::vector<float4> p(U.src.size(), make_float4(0.f, 0.f, 0.f, 0.f));
+    for (size_t c = 0; c < p.size(); ++c)
+        if (U.src[c] >= 0) p[c] = S->term_prm[U.src[c] % 5][U.src[c] / 5];
+    const hipError_t e = hipMemcpyAsync(U.bp, p.data(), sizeof(float4) * p.size(), hipMemcpyHostToDevice, S->stream);
+    return e == hipSuccess ? hipStreamSynchronize(S->stream) : e;
+}
+
+static hipError_t make_units(gpr_system *S, const std::vector<int> &bnd, gpr_system::Units &U)
+{
+    if (U.bi) return hipSuccess;
+    std::vector<uint2> bi;
+    write_units(S, bnd, U, bi);
+    hipError_t e = dalloc(S, &U.bp, bi.size());
+    if (e == hipSuccess) e = upload(S, &U.bi, bi);
+    if (e == hipSuccess) e = write_unit_params(S, U);
+    return e;
+}
+
+// the split with its bonded units, laid out when a launch first needs them (never under capture:
+// captured launches take them before the capture begins)
+static gpr_status split_units(gpr_system *S, Split &sp)
+{
+    gpr_system::Units &U = S->units_split[split_index(sp.G)];
+    HIPCHK(S, make_units(S, std::vector<int>(sp.bnd, sp.bnd + sp.G + 1), U));
+    for (int g = 0; g <= sp.G; ++g) sp.bu[g] = U.first[g];
+    sp.bi = U.bi;
+    sp.bp = U.bp;
+    return GPR_OK;
+}
+
 // ------------------------------------------------------------------ force-field parameters
 // Device copies of the per-atom parameters (sigma/2, 2 sqrt(eps), q sqrt(f), 1/m), the torsion
 // parameters (k, cos phi0, sin phi0, n) and the 1-4 pair parameters (sigma_ij, 4 eps_ij s14,
@@ -345,6 +432,7 @@ static hipError_t write_params(gpr_system *S)
                                (float)S->tor_n_h[t]);
         }
         e = hipMemcpyAsync((void *)T.t_p, p.data(), sizeof(float4) * T.nt, hipMemcpyHostToDevice, S->stream);
+        S->term_prm[2] = p;
     }
     if (e == hipSuccess && mol && T.n14) {
         std::vector<float4> p(T.n14);
@@ -356,7 +444,11 @@ static hipError_t write_params(gpr_system *S)
                                (float)(COULOMB_F * S->q_h[ij.x] * S->q_h[ij.y] * S->scale14), 0.f);
         }
         e = hipMemcpyAsync((void *)T.p_p, p.data(), sizeof(float4) * T.n14, hipMemcpyHostToDevice, S->stream);
+        S->term_prm[4] = p;
     }
+    if (e == hipSuccess) e = write_unit_params(S, S->units_plain);
+    for (auto &u : S->units_split)
+        if (e == hipSuccess) e = write_unit_params(S, u);
     if (e == hipSuccess) e = hipStreamSynchronize(S->stream);
     return e;
 }
@@ -417,6 +509,10 @@ static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt,
     it = PersistItem{};
     it.dev = S->d_dev;
     it.sp = sp;
+    {
+        const gpr_status rc = split_units(S, it.sp);
+        if (rc) return rc;
+    }
     it.nrep = nrep;
     it.boff = 0;
     if (G == 1 && cap_blocks < 0) {
@@ -777,6 +873,10 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         far_j.insert(far_j.end(), far[i].begin(), far[i].end());
     }
     d.has_far = far_j.empty() ? 0 : 1;
+    d.excl_span = 0;
+    for (int i = 0; i < n; ++i)
+        for (int b = 0; b < 64; ++b)
+            if ((excl[i] >> b) & 1ull) d.excl_span = std::max(d.excl_span, std::abs(b - 32));
     HIPCHK(S, upload(S, (unsigned long long **)&d.excl, excl));
     HIPCHK(S, upload(S, (int **)&d.far_start, far_start));
     HIPCHK(S, upload(S, (int **)&d.far_j, far_j));
@@ -800,10 +900,11 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
 
     // bonded topology, each type sorted by smallest atom
     Topo &T = d.tp;
-    std::vector<int> order, start;
+    std::vector<int> order;
+    auto wide = [](const float2 &v) { return make_float4(v.x, v.y, 0.f, 0.f); };
     if (D->kind == GPR_KIND_MOLECULAR) {
         {
-            sort_terms(D->bond_atoms, D->n_bonds, 2, n, order, start, T.b_span);
+            sort_terms(D->bond_atoms, D->n_bonds, 2, order);
             std::vector<int2> ij(D->n_bonds); std::vector<float2> p(D->n_bonds);
             for (int k = 0; k < D->n_bonds; ++k) {
                 const int t = order[k];
@@ -811,11 +912,11 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                 p[k] = make_float2((float)D->bond_r0[t], (float)D->bond_k[t]);
             }
             T.nb = D->n_bonds;
+            for (int k = 0; k < T.nb; ++k) { S->term_idx[0].push_back(make_int4(ij[k].x, ij[k].y, -1, -1)); S->term_prm[0].push_back(wide(p[k])); }
             HIPCHK(S, upload(S, (int2 **)&T.b_ij, ij)); HIPCHK(S, upload(S, (float2 **)&T.b_p, p));
-            HIPCHK(S, upload(S, (int **)&T.b_start, start));
         }
         {
-            sort_terms(D->angle_atoms, D->n_angles, 3, n, order, start, T.a_span);
+            sort_terms(D->angle_atoms, D->n_angles, 3, order);
             std::vector<int4> ijk(D->n_angles); std::vector<float2> p(D->n_angles);
             for (int k = 0; k < D->n_angles; ++k) {
                 const int t = order[k];
@@ -823,11 +924,11 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                 p[k] = make_float2((float)D->angle_theta0[t], (float)D->angle_k[t]);
             }
             T.na = D->n_angles;
+            for (int k = 0; k < T.na; ++k) { S->term_idx[1].push_back(make_int4(ijk[k].x, ijk[k].y, ijk[k].z, -1)); S->term_prm[1].push_back(wide(p[k])); }
             HIPCHK(S, upload(S, (int4 **)&T.a_ijk, ijk)); HIPCHK(S, upload(S, (float2 **)&T.a_p, p));
-            HIPCHK(S, upload(S, (int **)&T.a_start, start));
         }
         {
-            sort_terms(D->torsion_atoms, D->n_torsions, 4, n, order, start, T.t_span);
+            sort_terms(D->torsion_atoms, D->n_torsions, 4, order);
             std::vector<int4> q(D->n_torsions); std::vector<float4> p(D->n_torsions);
             for (int k = 0; k < D->n_torsions; ++k) {
                 const int t = order[k];
@@ -837,13 +938,13 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)std::sin(D->torsion_phi0[t]), (float)D->torsion_n[t]);
             }
             T.nt = D->n_torsions;
+            S->term_idx[2] = q;
+            S->term_prm[2] = p;
             S->tor_order = order;
             HIPCHK(S, upload(S, (int4 **)&T.t_ijkl, q)); HIPCHK(S, upload(S, (float4 **)&T.t_p, p));
-            HIPCHK(S, upload(S, (int **)&T.t_start, start));
         }
         {
-            int span0 = 0;
-            sort_terms(D->restraint_atom, D->n_restraints, 1, n, order, start, span0);
+            sort_terms(D->restraint_atom, D->n_restraints, 1, order);
             std::vector<int> ia(D->n_restraints); std::vector<float4> p(D->n_restraints);
             for (int k = 0; k < D->n_restraints; ++k) {
                 const int t = order[k];
@@ -852,11 +953,12 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)D->restraint_ref[3 * t + 2], (float)D->restraint_k[t]);
             }
             T.nr = D->n_restraints;
+            for (int k = 0; k < T.nr; ++k) S->term_idx[3].push_back(make_int4(ia[k], -1, -1, -1));
+            S->term_prm[3] = p;
             HIPCHK(S, upload(S, (int **)&T.r_i, ia)); HIPCHK(S, upload(S, (float4 **)&T.r_p, p));
-            HIPCHK(S, upload(S, (int **)&T.r_start, start));
         }
         {
-            sort_terms(D->pair14_atoms, D->n_pairs14, 2, n, order, start, T.p_span);
+            sort_terms(D->pair14_atoms, D->n_pairs14, 2, order);
             std::vector<int2> ij(D->n_pairs14); std::vector<float4> p(D->n_pairs14);
             for (int k = 0; k < D->n_pairs14; ++k) {
                 const int t = order[k];
@@ -868,14 +970,29 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)(COULOMB_F * D->charge[i] * D->charge[j] * D->scale14), 0.f);
             }
             T.n14 = D->n_pairs14;
+            for (int k = 0; k < T.n14; ++k) S->term_idx[4].push_back(make_int4(ij[k].x, ij[k].y, -1, -1));
+            S->term_prm[4] = p;
             S->p14_order = order;
             HIPCHK(S, upload(S, (int2 **)&T.p_ij, ij)); HIPCHK(S, upload(S, (float4 **)&T.p_p, p));
-            HIPCHK(S, upload(S, (int **)&T.p_start, start));
         }
     }
 
     // nonbonded constants and pair-list capacity
     d.cutoff_on = (D->kind == GPR_KIND_MOLECULAR && D->cutoff > 0) ? 1 : 0;
+    // list margins by mass: the light atoms (less than four times the lightest's mass) get half the
+    // skin, the others that times 1.35 sqrt(lightest mass / lightest heavy mass)
+    double mmin = D->mass[0], mheavy = INFINITY;
+    for (int i = 0; i < n; ++i) mmin = std::min(mmin, D->mass[i]);
+    for (int i = 0; i < n; ++i)
+        if (D->mass[i] >= 4.0 * mmin) mheavy = std::min(mheavy, D->mass[i]);
+    const double heavy = std::isfinite(mheavy) ? std::min(1.0, margin_heavy * std::sqrt(mmin / mheavy)) : 1.0;
+    d.im_light = std::isfinite(mheavy) ? (float)(0.5 / mmin) : 0.f;     // between 1/4 and 1 of the lightest's 1/m
+    {
+        std::vector<unsigned char> cls((n + BLK - 1) / BLK, 0);
+        for (int i = 0; i < n; ++i)
+            if ((float)(1.0 / D->mass[i]) > d.im_light) cls[i / BLK] |= (unsigned char)(1u << (i % BLK));
+        HIPCHK(S, upload(S, (unsigned char **)&d.cls, cls));
+    }
     if (d.cutoff_on) {
         const double rc = D->cutoff;
         const double krf = (D->eps_rf - 1.0) / ((2.0 * D->eps_rf + 1.0) * rc * rc * rc);
@@ -883,12 +1000,19 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         d.krf = (float)krf;
         d.crf = (float)(1.0 / rc + krf * rc * rc);
         d.rl = (float)(rc + D->skin + 1e-4);
-        d.rl2 = d.rl * d.rl;
-        d.half_skin2 = (float)(0.25 * D->skin * D->skin);
+        const double ml = 0.5 * D->skin, mh = ml * heavy, pad = 1e-4;
+        auto sq = [](double v) { return v * v; };
+        d.guard2_light = (float)sq(ml);
+        d.guard2_heavy = (float)sq(mh);
+        d.list2_light = (float)sq(rc + ml + mh + pad);
+        d.list2_heavy = (float)sq(rc + 2.0 * mh + pad);
+        // the larger of the two differences (light i): a heavy i lists light partners 2 (ml - mh)^2 too far
+        d.list2_j = (float)(sq(rc + 2.0 * ml + pad) - sq(rc + ml + mh + pad));
         d.period = std::max(1, D->nlist_period);
     } else {
-        d.rc2 = INFINITY; d.krf = 0.f; d.crf = 0.f; d.rl = INFINITY; d.rl2 = INFINITY;
-        d.half_skin2 = INFINITY; d.period = 1 << 30;
+        d.rc2 = INFINITY; d.krf = 0.f; d.crf = 0.f; d.rl = INFINITY;
+        d.guard2_light = d.guard2_heavy = INFINITY; d.list2_light = d.list2_heavy = 1.0e30f; d.list2_j = 0.f;
+        d.period = 1 << 30;
     }
     // capacity from the initial structure: the largest sub-list within r_list, doubled
     // per-atom work estimate for the persistent split: partners within r_list plus a constant
@@ -997,6 +1121,16 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         HIPCHK(S, upload(S, (int **)&d.tor_orig, orig));
     }
     HIPCHK(S, write_params(S));
+    {
+        // bonded units of the plain path's blocks of 256 atoms
+        std::vector<int> bnd;
+        for (int a = 0; a < n; a += 256) bnd.push_back(a);
+        bnd.push_back(n);
+        HIPCHK(S, make_units(S, bnd, S->units_plain));
+        d.pl_bi = S->units_plain.bi;
+        d.pl_bp = S->units_plain.bp;
+        HIPCHK(S, upload(S, (int **)&d.pl_first, S->units_plain.first));
+    }
     HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
 
     // scratch for the per-check bookkeeping
@@ -1058,8 +1192,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         // usable: the LDS fits and a workgroup can run; all_at_once: every replica's workgroups are
         // resident together (with fewer, sets of workgroups take the replicas in turn)
         auto usable = [&](int G, bool &ok, bool &all_at_once) -> hipError_t {
-            const int k = G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3;
-            const size_t lds = persist_lds(n, np, S->splits[k]);
+            const size_t lds = persist_lds(n, np, S->splits[split_index(G)]);
             ok = all_at_once = false;
             if ((int)lds > S->maxlds_persist) return hipSuccess;
             int per_cu = 0;
@@ -1088,7 +1221,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
             G = 1;
         }
         S->groups = G;
-        S->split = make_split(S->work, n, np, G);
+        S->split = S->splits[split_index(G)];
         for (int k = 0; k < 4; ++k) {
             bool all2 = false;
             HIPCHK(S, usable(1 << k, S->split_ok[k], all2));
@@ -1208,7 +1341,7 @@ extern "C" gpr_status gpr_set_launch(gpr_system *S, int32_t block_threads, int32
     const int bt = block_threads != 0 ? block_threads : S->bt_persist;
     {
         const int G = groups_per_replica != 0 ? groups_per_replica : S->groups;
-        const size_t lds = persist_lds(S->n, S->np, make_split(S->work, S->n, S->np, G));
+        const size_t lds = persist_lds(S->n, S->np, S->splits[split_index(G)]);
         if ((int)lds > S->maxlds_persist)
             return fail(S, GPR_EINVAL, "the per-workgroup LDS of this split exceeds the device limit");
         int per_cu = 0;
@@ -1221,7 +1354,7 @@ extern "C" gpr_status gpr_set_launch(gpr_system *S, int32_t block_threads, int32
     if (groups_per_replica != 0) {
         S->groups_from = 2;
         S->groups = groups_per_replica;
-        S->split = make_split(S->work, S->n, S->np, groups_per_replica);
+        S->split = S->splits[split_index(groups_per_replica)];
     }
     return GPR_OK;
 }
@@ -1290,7 +1423,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
     S->path = GPR_PATH_PERSISTENT;
     S->bt_from = S->groups_from = 1;                       // the shapes tried, then the one kept
     for (int G = 1; G <= 8 && rc == GPR_OK; G *= 2) {
-        const Split sp = make_split(S->work, S->n, S->np, G);
+        const Split sp = S->splits[split_index(G)];
         const size_t lds = persist_lds(S->n, S->np, sp);
         if ((int)lds > S->maxlds_persist) continue;
         for (int bt = 256; bt <= 1024 && rc == GPR_OK; bt += 256) {
@@ -1330,7 +1463,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
     }
     S->bt_persist = best_bt;
     S->groups = best_g;
-    S->split = make_split(S->work, S->n, S->np, best_g);
+    S->split = S->splits[split_index(best_g)];
     if (block_threads) *block_threads = best_bt;
     if (groups) *groups = best_g;
     return GPR_OK;

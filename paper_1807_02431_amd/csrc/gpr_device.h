@@ -28,8 +28,8 @@ namespace gpr {
 constexpr int P = 4;            // lanes per atom in the pair loop (sub-lists by j mod P)
 constexpr int MAX_OBS = 8;
 constexpr int CHMAX = 4;        // atoms per thread in the integrator mapping
-constexpr int BLK = 8;          // consecutive atoms per bounding sphere in the pair search (a multiple of P)
-constexpr int WBLK = 64;        // LDS ints per wave: the near blocks of one 64-block chunk in the pair search
+constexpr int BLK = 8;          // consecutive atoms per bounding box in the pair search (two per MFMA tile)
+constexpr int WBLK = 64;        // LDS ints per wave: the queue of near blocks in the pair search
 constexpr double FIX = 4294967296.0;          // 2^32
 constexpr double FIX_INV = 2.3283064365386963e-10;  // 2^-32
 constexpr float FMAX_FIX = 2.5e5f;             // |F| beyond this (kJ/mol/nm) counts as unstable
@@ -65,15 +65,27 @@ struct StateDesc {
     double radius;
 };
 
-// bonded terms, each type sorted by its smallest atom index; *_start[a] is the first term
-// whose smallest atom is >= a (length n+1); *_span the largest index spread of a term
+// bonded terms, each type sorted by its smallest atom index
 struct Topo {
-    int nb; const int2 *b_ij; const float2 *b_p; const int *b_start; int b_span;            // (r0, k)
-    int na; const int4 *a_ijk; const float2 *a_p; const int *a_start; int a_span;           // (theta0, k)
-    int nt; const int4 *t_ijkl; const float4 *t_p; const int *t_start; int t_span;          // (k, cos phi0, sin phi0, n)
-    int nr; const int *r_i; const float4 *r_p; const int *r_start;                          // (ref xyz, k)
-    int n14; const int2 *p_ij; const float4 *p_p; const int *p_start; int p_span;           // (s, 4e*sc, qq*sc)
+    int nb; const int2 *b_ij; const float2 *b_p;            // (r0, k)
+    int na; const int4 *a_ijk; const float2 *a_p;           // (theta0, k)
+    int nt; const int4 *t_ijkl; const float4 *t_p;          // (k, cos phi0, sin phi0, n)
+    int nr; const int *r_i; const float4 *r_p;              // (ref xyz, k)
+    int n14; const int2 *p_ij; const float4 *p_p;           // (s, 4e*sc, qq*sc)
 };
+
+// The bonded terms touching an atom range, laid out for waves: units of 64 terms of one kind, one
+// record per lane in unit order, so that a wave reads its unit with two coalesced loads and
+// branches on the kind once.  A record's word holds four 16-bit fields, the atoms of the term (13
+// bits; the LDS-staged kernels take fewer than 8,192 atoms) with flags above them:
+//   field 0: bit 13 the range owns the atom, bits 14-15 low bits of the unit's kind
+//   field 1: bit 13 owns, bits 14-15 high bits of the kind
+//   field 2: bit 13 owns, bit 14 the range counts the term's energy, bit 15 the record holds a term
+//   field 3: bit 13 owns
+// Kinds 0-4: bond, angle, torsion, restraint, 1-4, all atoms of every term owned; 5-9 the same with
+// terms that reach outside the range.
+constexpr int BONDED_ATOMS = 8192;
+constexpr int BONDED_EDGE = 5;                 // kind of an edge unit = BONDED_EDGE + kind of its terms
 
 struct Dev {
     int kind, n, np, R;
@@ -81,6 +93,8 @@ struct Dev {
     const float *sd;                       // sqrt((1 - c1^2) kT / m)
     const float *mass;
     const unsigned long long *excl;        // bit (j - i + 32) set: pair excluded or 1-4
+    int excl_span;                         // largest |j - i| among those bits
+    const unsigned char *cls;              // [blocks of BLK atoms] bit k: atom k of the block is light (see im_light)
     int has_far;                           // some excluded or 1-4 pair lies 32 or more indices apart:
     const int *far_start, *far_j;          // [n + 1] offsets and ascending partners of those pairs
     float *x, *v, *xb;
@@ -108,13 +122,22 @@ struct Dev {
     const ObsDesc *obs;                    // [MAX_OBS], device memory
     const StateDesc *st;                   // device memory
     Topo tp;
+    // bonded units of the plain path: of each range of 256 atoms, [pl_first[k], pl_first[k + 1])
+    const uint2 *pl_bi;
+    const float4 *pl_bp;
+    const int *pl_first;
     // force-field parameter gradient (molecular systems)
     long long *gacc;                       // [3][np] + [nt]: fixed-point sums for eps, sigma, charge, torsion k
     const double *inv2eps;                 // [n] 1 / (2 eps_i)
     const int *tor_orig;                   // [nt] caller's index of the k-th torsion in sorted order
     float scale14;
     double sqrt_f;                         // square root of the Coulomb constant
-    float h, c1, rc2, rl, rl2, krf, crf, half_skin2;
+    float h, c1, rc2, rl, krf, crf;
+    // List margins by mass: an atom lighter than 1/im_light may move half the skin between builds,
+    // a heavier one a smaller margin (slower in proportion to the root of its mass), and a pair is
+    // listed within the cutoff plus both atoms' margins.  guard2_*: the squared margins.  A pair
+    // (i, j) is listed when r^2 < list2_*[class of i] + (j light ? list2_j : 0).
+    float im_light, guard2_light, guard2_heavy, list2_light, list2_heavy, list2_j;
     int cutoff_on, period;
     uint32_t key0, key1;
     int t_gr;
@@ -130,6 +153,9 @@ template <class T>
 __device__ __forceinline__ const GPR_GLOBAL T *gconst(const T *p) { return (const GPR_GLOBAL T *)p; }
 template <class T>
 __device__ __forceinline__ GPR_GLOBAL T *gmut(T *p) { return (GPR_GLOBAL T *)p; }
+
+// the descriptor as constant memory (it does not change while a kernel runs): scalar loads
+#define GPR_CONST __attribute__((address_space(4)))
 
 // LDS address space, for arrays that a non-inlined function reads (so that it emits LDS, not
 // flat, instructions)
@@ -226,7 +252,6 @@ __device__ __forceinline__ bool bad_force(float f) { return !(fabsf(f) < FMAX_FI
 // ------------------------------------------------------------------ bonded terms (FP32)
 // Each returns the energy and writes the force on every atom of the term.
 
-// bond 1/2 k (r - r0)^2
 // arctangent on [0, 1] as a P(a^2), P of degree 8 fitted by iteratively reweighted least
 // squares to atan(a)/a (maximum error 6e-9 in exact arithmetic, 1e-7 evaluated in FP32)
 __device__ __forceinline__ float atan01(float a)
@@ -254,6 +279,7 @@ __device__ __forceinline__ float atan2_upper(float y, float x)
     return t;
 }
 
+// bond 1/2 k (r - r0)^2
 __device__ __forceinline__ float term_bond(float3 pi, float3 pj, float2 p, float3 &fi)
 {
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;

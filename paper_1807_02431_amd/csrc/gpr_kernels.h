@@ -47,6 +47,9 @@ struct Split {
     int G;          // workgroups per replica (1, 2, 4 or 8)
     int lmax;       // LDS length of the per-group arrays: the largest range, rounded up to 16
     int bnd[9];     // group g owns atoms [bnd[g], bnd[g + 1]); every bnd[g] < n is a multiple of 16
+    int bu[9];      // its bonded units are [bu[g], bu[g + 1]) of the records bi, bp
+    const uint2 *bi;
+    const float4 *bp;
 };
 
 __global__ void k_set_clock(const Dev *__restrict__ Sp, long long s, long long t);

@@ -43,153 +43,100 @@ struct PosGlob {
 
 __device__ __forceinline__ float3 neg3(float3 f) { return make_float3(-f.x, -f.y, -f.z); }
 
-// ------------------------------------------------------------------ bonded terms of an atom range
-// Terms touching atoms [a0, a1), by kind (bond, angle, torsion, restraint, 1-4).  Terms are
-// sorted by their smallest atom and span at most `span` atoms, so those touching [a0, a1) have
-// their smallest atom in [a0 - span, a1): of kind k the entries [lo[k], lo[k] + cnt[k]).  They
-// occupy the slots [off[k], off[k] + cnt[k]) of one flat index space in which every kind starts
-// at a multiple of 64 (so a wave sees one kind).
-struct BondedPlan {
-    int lo[5], cnt[5], off[6];
-};
-
-__device__ __forceinline__ BondedPlan bonded_plan(const Dev &S, int a0, int a1)
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni64(long long v)
 {
-    const Topo &T = S.tp;
-    BondedPlan bp;
-    // a molecular system has all five start arrays (n + 1 entries each, all zero for a kind
-    // without terms) and the toy none: one branch, then the ten reads go out together instead
-    // of one dependent round trip per kind
-    if (S.kind == KIND_MOL) {
-        const int *const start[5] = {T.b_start, T.a_start, T.t_start, T.r_start, T.p_start};
-        const int span[5] = {T.b_span, T.a_span, T.t_span, 0, T.p_span};
-        int lo[5], hi[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            lo[k] = gconst(start[k])[max(0, a0 - span[k])];
-            hi[k] = gconst(start[k])[a1];
-        }
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            bp.lo[k] = lo[k];
-            bp.cnt[k] = hi[k] - lo[k];
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) bp.lo[k] = bp.cnt[k] = 0;
-    }
-    bp.off[0] = 0;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) bp.off[k + 1] = bp.off[k] + (bp.cnt[k] + 63) / 64 * 64;
-    return bp;
+    const int lo = uni((int)(unsigned)v), hi = uni((int)(v >> 32));
+    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// Adds, for every term of the plan, the fixed-point forces on the atoms of [a0, a1) to
-// fa[3][len] (LDS, index a - a0); the energy of a term is counted by the range holding its
-// smallest atom.  Each thread takes up to U slots at a time and issues all their topology
-// loads before computing any of them.  nthr must be a multiple of 64.
-template <class Pos, int U = 4>
-__device__ void bonded_range(const Dev &S, const BondedPlan &bp, const Pos &pos, int a0, int a1, long long *fa,
-                             int len, long long *e_acc, int tid, int nthr)
+// ------------------------------------------------------------------ bonded terms of an atom range
+// One unit of 64 terms of a kind (records w, p of the lane): adds the fixed-point forces on the
+// atoms of the range to fa[3][len] (LDS, index a - a0); EDGE: only on the atoms the range owns.
+// Returns the lane's energy, counted by one range per term.
+template <int KIND, bool EDGE, class Pos>
+__device__ __forceinline__ long long bonded_terms(const uint2 w, const float4 p, const Pos &pos, int a0, long long *fa, int len)
 {
-    // the topology's pointers, read once per call (not again after each LDS atomic)
-    const Topo T = S.tp;
-    auto add = [&](int a, float3 f) {
-        if (a >= a0 && a < a1) {
-            lds_add(&fa[a - a0], fix_f(f.x));
-            lds_add(&fa[len + a - a0], fix_f(f.y));
-            lds_add(&fa[2 * len + a - a0], fix_f(f.z));
+    auto add = [&](unsigned field, float3 f) {
+        const int a = (int)(field & (BONDED_ATOMS - 1)) - a0;
+        if (!EDGE || (field & BONDED_ATOMS)) {
+            lds_add(&fa[a], fix_f(f.x));
+            lds_add(&fa[len + a], fix_f(f.y));
+            lds_add(&fa[2 * len + a], fix_f(f.z));
         }
     };
+    auto at = [&](unsigned field) { return pos((int)(field & (BONDED_ATOMS - 1))); };
+    if (!(w.y & 0x8000u)) return 0;
+    const unsigned f0 = w.x, f1 = w.x >> 16, f2 = w.y, f3 = w.y >> 16;
+    float u;
+    if (KIND == 0) {
+        float3 fi;
+        u = term_bond(at(f0), at(f1), make_float2(p.x, p.y), fi);
+        add(f0, fi);
+        add(f1, neg3(fi));
+    } else if (KIND == 1) {
+        float3 fi, fk;
+        u = term_angle(at(f0), at(f1), at(f2), make_float2(p.x, p.y), fi, fk);
+        add(f0, fi);
+        add(f2, fk);
+        add(f1, make_float3(-fi.x - fk.x, -fi.y - fk.y, -fi.z - fk.z));
+    } else if (KIND == 2) {
+        float3 fi, fj, fk, fl;
+        u = term_torsion(at(f0), at(f1), at(f2), at(f3), p, fi, fj, fk, fl);
+        add(f0, fi);
+        add(f1, fj);
+        add(f2, fk);
+        add(f3, fl);
+    } else if (KIND == 3) {
+        const float3 x = at(f0);
+        const float dx = x.x - p.x, dy = x.y - p.y, dz = x.z - p.z;
+        add(f0, make_float3(-p.w * dx, -p.w * dy, -p.w * dz));
+        u = 0.5f * p.w * (dx * dx + dy * dy + dz * dz);
+    } else {
+        float3 fi;
+        u = term_pair14(at(f0), at(f1), p, fi);
+        add(f0, fi);
+        add(f1, neg3(fi));
+    }
+    return (f2 & 0x4000u) ? fix_f(u) : 0;
+}
+
+// Units [u0, u1) of the records bi, bp, taken in turn by waves wv = 0 .. nwv - 1 of the range's
+// workgroup; each wave reads its next unit's records while it computes one, since what bounds the
+// terms otherwise is the latency of reading them (the records come from the L2: the pair lists
+// stream through the L1).
+template <class Pos>
+__device__ __forceinline__ void bonded_units(const uint2 *bi, const float4 *bp, int u0, int u1, const Pos &pos, int a0,
+                                             long long *fa, int len, long long *e_acc, int wv, int nwv, int lane)
+{
     long long e = 0;
-    const int total = bp.off[5];
-    for (int base = 0; base < total; base += U * nthr) {
-        int kind[U];
-        int4 idx[U];
-        float4 prm[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int slot = base + u * nthr + tid;
-            // kind and topology index of the slot (static indices into the plan: no scratch)
-            int k = -1, t = 0;
-            if (slot < total) {
-                int local, cnt, lo;
-                if (slot < bp.off[1]) { k = 0; local = slot; cnt = bp.cnt[0]; lo = bp.lo[0]; }
-                else if (slot < bp.off[2]) { k = 1; local = slot - bp.off[1]; cnt = bp.cnt[1]; lo = bp.lo[1]; }
-                else if (slot < bp.off[3]) { k = 2; local = slot - bp.off[2]; cnt = bp.cnt[2]; lo = bp.lo[2]; }
-                else if (slot < bp.off[4]) { k = 3; local = slot - bp.off[3]; cnt = bp.cnt[3]; lo = bp.lo[3]; }
-                else { k = 4; local = slot - bp.off[4]; cnt = bp.cnt[4]; lo = bp.lo[4]; }
-                if (local >= cnt) k = -1;
-                t = lo + local;
-            }
-            kind[u] = k;
-            idx[u] = make_int4(0, 0, 0, 0);
-            prm[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k < 0) continue;
-            if (k == 0) {
-                const int2 ij = gld(gconst(T.b_ij) + t);
-                const float2 p = gld(gconst(T.b_p) + t);
-                idx[u] = make_int4(ij.x, ij.y, 0, 0);
-                prm[u] = make_float4(p.x, p.y, 0.f, 0.f);
-            } else if (k == 1) {
-                idx[u] = gld(gconst(T.a_ijk) + t);
-                const float2 p = gld(gconst(T.a_p) + t);
-                prm[u] = make_float4(p.x, p.y, 0.f, 0.f);
-            } else if (k == 2) {
-                idx[u] = gld(gconst(T.t_ijkl) + t);
-                prm[u] = gld(gconst(T.t_p) + t);
-            } else if (k == 3) {
-                idx[u] = make_int4(gconst(T.r_i)[t], 0, 0, 0);
-                prm[u] = gld(gconst(T.r_p) + t);
-            } else {
-                const int2 ij = gld(gconst(T.p_ij) + t);
-                idx[u] = make_int4(ij.x, ij.y, 0, 0);
-                prm[u] = gld(gconst(T.p_p) + t);
-            }
+    int u = u0 + wv;
+    uint2 w = make_uint2(0u, 0u);
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (u < u1) {
+        w = gld(gconst(bi) + (64 * u + lane));
+        p = gld(gconst(bp) + (64 * u + lane));
+    }
+    while (u < u1) {
+        const uint2 cw = w;
+        const float4 cp = p;
+        u += nwv;
+        if (u < u1) {
+            w = gld(gconst(bi) + (64 * u + lane));
+            p = gld(gconst(bp) + (64 * u + lane));
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = kind[u];
-            if (k < 0) continue;
-            const int4 q = idx[u];
-            const float4 p = prm[u];
-            float u_e;
-            int mn;
-            if (k == 0) {
-                float3 fi;
-                u_e = term_bond(pos(q.x), pos(q.y), make_float2(p.x, p.y), fi);
-                add(q.x, fi);
-                add(q.y, neg3(fi));
-                mn = min(q.x, q.y);
-            } else if (k == 1) {
-                float3 fi, fk;
-                u_e = term_angle(pos(q.x), pos(q.y), pos(q.z), make_float2(p.x, p.y), fi, fk);
-                add(q.x, fi);
-                add(q.z, fk);
-                add(q.y, make_float3(-fi.x - fk.x, -fi.y - fk.y, -fi.z - fk.z));
-                mn = min(q.x, min(q.y, q.z));
-            } else if (k == 2) {
-                float3 fi, fj, fk, fl;
-                u_e = term_torsion(pos(q.x), pos(q.y), pos(q.z), pos(q.w), p, fi, fj, fk, fl);
-                add(q.x, fi);
-                add(q.y, fj);
-                add(q.z, fk);
-                add(q.w, fl);
-                mn = min(min(q.x, q.y), min(q.z, q.w));
-            } else if (k == 3) {
-                const float3 x = pos(q.x);
-                const float dx = x.x - p.x, dy = x.y - p.y, dz = x.z - p.z;
-                add(q.x, make_float3(-p.w * dx, -p.w * dy, -p.w * dz));
-                u_e = 0.5f * p.w * (dx * dx + dy * dy + dz * dz);
-                mn = q.x;
-            } else {
-                float3 fi;
-                u_e = term_pair14(pos(q.x), pos(q.y), p, fi);
-                add(q.x, fi);
-                add(q.y, neg3(fi));
-                mn = min(q.x, q.y);
-            }
-            if (e_acc && mn >= a0) e += fix_f(u_e);
+        const int kind = __builtin_amdgcn_readfirstlane((int)(((cw.x >> 14) & 3u) | ((cw.x >> 28) & 12u)));
+        switch (kind) {
+        case 0: e += bonded_terms<0, false>(cw, cp, pos, a0, fa, len); break;
+        case 1: e += bonded_terms<1, false>(cw, cp, pos, a0, fa, len); break;
+        case 2: e += bonded_terms<2, false>(cw, cp, pos, a0, fa, len); break;
+        case 3: e += bonded_terms<3, false>(cw, cp, pos, a0, fa, len); break;
+        case 4: e += bonded_terms<4, false>(cw, cp, pos, a0, fa, len); break;
+        case BONDED_EDGE + 0: e += bonded_terms<0, true>(cw, cp, pos, a0, fa, len); break;
+        case BONDED_EDGE + 1: e += bonded_terms<1, true>(cw, cp, pos, a0, fa, len); break;
+        case BONDED_EDGE + 2: e += bonded_terms<2, true>(cw, cp, pos, a0, fa, len); break;
+        case BONDED_EDGE + 3: e += bonded_terms<3, true>(cw, cp, pos, a0, fa, len); break;
+        default: e += bonded_terms<4, true>(cw, cp, pos, a0, fa, len); break;
         }
     }
     if (e_acc && e != 0) lds_add(e_acc, e);
@@ -205,249 +152,283 @@ __device__ __forceinline__ float toy_force(float x, float y, float &fx, float &f
 }
 
 // ------------------------------------------------------------------ pair search
-// Bounding spheres of blocks of BLK consecutive atoms (chain-local, so compact).  Each radius
-// is padded slightly so that rounding cannot drop a pair.
-__device__ void block_spheres(const Dev &S, const float4 *xs, float4 *sph, int tid, int nthr)
+// Bounding boxes of blocks of BLK consecutive atoms (chain-local, so compact): the middle, and in
+// one word the half extents in units of 1/128 nm, rounded up (a byte each; all three 255: too large
+// to say), with the block's mask of light atoms in the top byte.
+__device__ void block_boxes(const Dev &S, const float4 *xs, float4 *box, int tid, int nthr)
 {
     const int nblk = (S.n + BLK - 1) / BLK;
     for (int t = tid; t < nblk; t += nthr) {
         const int a0 = t * BLK, a1 = min(S.n, a0 + BLK);
-        float cx = 0.f, cy = 0.f, cz = 0.f;
-        for (int a = a0; a < a1; ++a) { cx += xs[a].x; cy += xs[a].y; cz += xs[a].z; }
-        const float inv = 1.0f / (float)(a1 - a0);
-        cx *= inv; cy *= inv; cz *= inv;
-        float r2 = 0.f;
-        for (int a = a0; a < a1; ++a) {
-            const float dx = xs[a].x - cx, dy = xs[a].y - cy, dz = xs[a].z - cz;
-            r2 = fmaxf(r2, dx * dx + dy * dy + dz * dz);
+        const unsigned light = gconst(S.cls)[t];
+        float3 lo = make_float3(xs[a0].x, xs[a0].y, xs[a0].z), hi = lo;
+        for (int a = a0 + 1; a < a1; ++a) {
+            const float4 x = xs[a];
+            lo.x = fminf(lo.x, x.x); lo.y = fminf(lo.y, x.y); lo.z = fminf(lo.z, x.z);
+            hi.x = fmaxf(hi.x, x.x); hi.y = fmaxf(hi.y, x.y); hi.z = fmaxf(hi.z, x.z);
         }
-        sph[t] = make_float4(cx, cy, cz, sqrtf(r2) * 1.0001f + 1e-6f);
+        // (half the box, and what rounding may take from the distance to it: 2^-20 of a coordinate)
+        const float3 m = make_float3(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z));
+        auto units = [](float l, float h) {
+            const float e = 0.5f * (h - l) + 9.5e-7f * fmaxf(fabsf(l), fabsf(h));
+            return e < 1.97f ? (unsigned)(e * 128.0f) + 1u : 255u;      // (a NaN too)
+        };
+        const unsigned ux = units(lo.x, hi.x), uy = units(lo.y, hi.y), uz = units(lo.z, hi.z);
+        const unsigned ext = (ux == 255u || uy == 255u || uz == 255u) ? 0xFFFFFFu : ux | (uy << 8) | (uz << 16);
+        box[t] = make_float4(m.x, m.y, m.z, __uint_as_float(ext | (light << 24)));
     }
 }
 
 // a value that every lane holds alike, as a scalar
 __device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 
-// min / max over the 16 atoms of a wave (the four lanes of an atom hold the same value)
-__device__ __forceinline__ float wave16_min(float v)
+// min / max over each row of 16 lanes, in every lane
+template <int N>
+__device__ __forceinline__ float row_ror(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 | N, 0xF, 0xF, true)); }
+__device__ __forceinline__ float row_min(float v)
 {
-#pragma unroll
-    for (int o = 4; o < 64; o <<= 1) v = fminf(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fminf(v, row_ror<8>(v));
+    v = fminf(v, row_ror<4>(v));
+    v = fminf(v, row_ror<2>(v));
+    return fminf(v, row_ror<1>(v));
 }
-__device__ __forceinline__ float wave16_max(float v)
+__device__ __forceinline__ float row_max(float v)
 {
-#pragma unroll
-    for (int o = 4; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    return fmaxf(v, row_ror<1>(v));
 }
 
-// Pair lists of the 16 atoms of one wave; lane = 4 (i - i0) + q for the wave's first atom
-// i0.  All 64 lanes call it together: the culling is wave-wide (each lane tests a block
-// sphere against the bounding box of the wave's atoms, and the wave visits the blocks that
-// any lane found near); lanes with valid == false take part but own no list.
-// Sub-list (i, q): partners j = q (mod P), j != i, not excluded, |x_i - x_j| < r_list, in
-// ascending order; entry k is the 16-bit word k % 4 of group k / 4; the last group is padded
-// with the dummy atom n.  allpairs: no distance tests (vacuum, no cutoff; r_list^2 = inf).
-// Per 64-block chunk the near blocks are listed in the wave's LDS scratch wblk (ascending);
-// their candidates are tested without branches, the outcomes kept as bits (BLK / P per block,
-// 32 blocks per batch), and each lane then appends the entries it keeps, four per pass.
-// Itself and excluded partners within 32 atoms of it are dropped in the tests, only for
-// blocks near the wave's own atoms; farther excluded partners are merged out entry by entry
-// (only while some lane of the wave still has one ahead); atoms past n are staged far away,
-// so the distance test drops them.  UNR blocks are read at a time (more registers, fewer
-// exposed LDS latencies); the plain path's pair kernel uses 1 to keep its occupancy.
-template <int UNR, bool PAD>
-__device__ __noinline__ int build_wave(const Dev &S, int r, int i, int q, bool valid, const GPR_LDS gv_f4 *xs,
-                                       const GPR_LDS gv_f4 *sph, GPR_LDS int *wblk, bool allpairs)
+// Entry p of the table that packs a lane's kept candidates: of the four 16-bit values in (X, Y)
+// those whose bit is set in p, in order, as the byte selectors of two v_perm_b32 (zeros after them)
+struct PickTable {
+    unsigned lo[16], hi[16];
+};
+constexpr PickTable make_pick()
 {
-    const int n = S.n;
-    const size_t stride = (size_t)S.np * P;
+    PickTable t{};
+    for (int p = 0; p < 16; ++p) {
+        unsigned sel[4] = {0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu};
+        int c = 0;
+        for (unsigned v = 0; v < 4; ++v)
+            if ((p >> v) & 1) sel[c++] = 2 * v | ((2 * v + 1) << 8);
+        t.lo[p] = sel[0] | (sel[1] << 16);
+        t.hi[p] = sel[2] | (sel[3] << 16);
+    }
+    return t;
+}
+__device__ __constant__ const PickTable pick_table = make_pick();
+
+// Pair lists of the atoms [iw, iw + 16) below iend, by one wave; all 64 lanes call it together with
+// the same arguments.  Lane 16 q + k owns sub-list (i, q) of atom i = iw + k: partners j = q (mod P),
+// j != i, not excluded, r^2 < list2 of the two atoms' classes, in ascending order; entry e is the
+// 16-bit word e % 4 of group e / 4; the last group is padded with the dummy atom n.  allpairs: no
+// distance tests (vacuum, no cutoff).
+//
+// Culling is wave-wide: each lane tests one block's box against the box of the wave's atoms, and
+// the near blocks queue up in the wave's LDS scratch wblk (ascending).  Two blocks at a time are
+// tested by one v_mfma_f32_16x16x4_f32: with d the positions relative to the middle of the wave's
+// box, D = |d_j|^2 + |d_i|^2 - list2 - 2 d_i . d_j for 16 partners (rows) x 16 atoms (columns), the
+// sum over K = 4 taking (d_x, d_y, d_z, |d_j|^2 - list2_j) of the partner against (-2 d_i, 1) of the
+// atom, and a pair is listed when D < 0.  Row 4 q + v holds atom 4 (v % 2) + q of block v / 2, so the
+// four values a lane gets are its own candidates in order, one sign bit each; the vector unit does
+// 16 instructions for 256 pairs instead of nine for 64.  A list may hold more pairs than needed but
+// never fewer: the squares are taken 2^-20 short, which covers the rounding of D (each of its six
+// terms is at most |d_i|^2 + |d_j|^2), and boxes wider than 64 nm, where that would admit pairs
+// 0.004 nm^2 and more too far, take the distances directly.
+// The kept candidates of a lane (at most four per tile) are packed by two byte permutes whose
+// selectors the lanes hold (entry `lane` of the 16) and read from each other, and merged into the
+// pending group with one shift.
+// Excluded partners within 32 atoms (and the atom itself) are dropped only in tiles that may hold
+// some; farther ones are merged out against the atom's ascending list far_j.
+// Bound by VALU issue: 25-30 instructions per tile and about 17 tiles a task on the 2,432-atom
+// system.  UNR tiles are read at a time (more registers, fewer exposed LDS latencies); the plain
+// path's pair kernel uses 2 to keep its occupancy.
+template <int UNR, bool PAD>
+__device__ __noinline__ int build_wave(const Dev *Sv, int r_, int iw_, int iend_, const GPR_LDS gv_f4 *xs,
+                                       const GPR_LDS gv_f4 *box, GPR_LDS int *wblk, int allpairs_)
+{
+    const GPR_CONST Dev &S = *(const GPR_CONST Dev *)uni64((long long)Sv);
+    const int r = uni(r_), iw = uni(iw_), iend = uni(iend_);
+    const bool allpairs = uni(allpairs_) != 0;
+    const int n = S.n, Kg = S.Kg, span = S.excl_span;
+    const unsigned stride = (unsigned)S.np * P;
+    const int lane = threadIdx.x & 63, q = lane >> 4, k16 = lane & 15;
+    const int i = iw + k16;
+    const bool valid = i < iend;
+    const int sel_lo = (int)pick_table.lo[k16], sel_hi = (int)pick_table.hi[k16];
     const gv_f4 pi = xs[valid ? i : n];
-    // bounding box of the wave's valid atoms
+    // box of the wave's valid atoms (the same in every row of lanes)
     const float big = 3.0e38f;
-    // (the same in every lane: held as scalars)
-    const float mnx = uniform_f(wave16_min(valid ? pi.x : big)), mxx = uniform_f(wave16_max(valid ? pi.x : -big));
-    if (!(mnx <= mxx)) return 0;                                // no valid lane in this wave
-    const float mny = uniform_f(wave16_min(valid ? pi.y : big)), mxy = uniform_f(wave16_max(valid ? pi.y : -big));
-    const float mnz = uniform_f(wave16_min(valid ? pi.z : big)), mxz = uniform_f(wave16_max(valid ? pi.z : -big));
-    const float rlb = S.rl;
-    // finite even without a cutoff, so that the far-away atoms past n never pass
-    const float rl2 = fminf(S.rl2, 1.0e30f);
-    // atoms [iw, iw + 16) of the wave (lane 0 holds the first)
-    const int iw = __builtin_amdgcn_readfirstlane(i);
-    // partners to drop: excluded and 1-4 pairs within +-32 of i, and i itself (bit 32)
+    const float mnx = uniform_f(row_min(valid ? pi.x : big)), mxx = uniform_f(row_max(valid ? pi.x : -big));
+    if (!(mnx <= mxx)) return 0;                                // no valid atom in this wave
+    const float mny = uniform_f(row_min(valid ? pi.y : big)), mxy = uniform_f(row_max(valid ? pi.y : -big));
+    const float mnz = uniform_f(row_min(valid ? pi.z : big)), mxz = uniform_f(row_max(valid ? pi.z : -big));
+    const float cx = 0.5f * (mnx + mxx), cy = 0.5f * (mny + mxy), cz = 0.5f * (mnz + mxz);
+    // half the box plus the list radius (and the rounding of both): blocks farther off are culled
+    const float rly = 0.5f * (mxy - mny) * 1.00001f + 1e-6f * fabsf(cy), rlz = 0.5f * (mxz - mnz) * 1.00001f + 1e-6f * fabsf(cz);
+    const float rhx = 0.5f * (mxx - mnx) * 1.00001f + 1e-6f * fabsf(cx);
+    const float rl2 = S.rl * S.rl * 1.00001f;
+    const bool wide = !(fmaxf(mxx - mnx, fmaxf(mxy - mny, mxz - mnz)) < 64.0f);
+    // atom i: exclusions, list radius, MFMA operand and accumulator start
     const unsigned long long ex = (valid ? gconst(S.excl)[i] : 0ull) | (1ull << 32);
-    // excluded and 1-4 partners farther than that: i's ascending list far_j[far_start[i] ..
-    // far_start[i + 1]), merged against the entries as they are emitted (also ascending)
+    const bool ilight = (__float_as_uint(box[(valid ? i : iw) >> 3].w) >> (24 + (i & 7))) & 1u;
+    constexpr float SHORT = 1.0f - 9.5367431640625e-7f;        // 1 - 2^-20
+    const float list2 = allpairs ? 1.0e30f : (ilight ? S.list2_light : S.list2_heavy);
+    const float list2_j = S.list2_j;
+    const float dix = pi.x - cx, diy = pi.y - cy, diz = pi.z - cz;
+    const float ci = valid ? fmaf(fmaf(diz, diz, fmaf(diy, diy, dix * dix)), SHORT, -list2) : 1.0e30f;
+    const float bop = q == 0 ? -2.0f * dix : (q == 1 ? -2.0f * diy : (q == 2 ? -2.0f * diz : 1.0f));
+    // the partner this lane feeds as row k16: atom `jt` of the tile's block `jb`
+    const int jb = (k16 >> 1) & 1, jt = 4 * (k16 & 1) + (k16 >> 2);
     int flo = 0, fhi = 0;
-    const GPR_GLOBAL int *fj = gconst(S.far_j);
-    if (S.has_far && valid) { flo = gconst(S.far_start)[i]; fhi = gconst(S.far_start)[i + 1]; }
-    const int cap = 4 * S.Kg;
-    // the replica's lists (a scalar base) and this lane's column in them: group g of sub-list
-    // (i, q) is word g * np * P + i * P + q
-    GPR_GLOBAL unsigned long long *const Lr = (GPR_GLOBAL unsigned long long *)gmut(S.nbl) + (size_t)r * S.Kg * stride;
-    const unsigned col = (unsigned)((valid ? i : 0) * P + q), stride32 = (unsigned)stride;
-    const int lane = threadIdx.x & 63;
+    const GPR_GLOBAL int *const fj = gconst(S.far_j);
+    const bool has_far = S.has_far != 0;
+    if (has_far && valid) { flo = gconst(S.far_start)[i]; fhi = gconst(S.far_start)[i + 1]; }
+    const int cap = 4 * Kg;
+    // the replica's lists (a scalar base) and this lane's word in them: group g of sub-list (i, q) is
+    // word g * np * P + i * P + q
+    GPR_GLOBAL unsigned long long *const Lr = (GPR_GLOBAL unsigned long long *)gmut(S.nbl) + (size_t)r * Kg * stride;
+    unsigned off = (unsigned)((valid ? i : 0) * P + q);
     const int nblk = (n + BLK - 1) / BLK;
-    constexpr int CPB = BLK / P;                                // candidates per block and lane
-    constexpr int BATCH = 64 / CPB;                             // blocks per batch of bits
-    static_assert(CPB == 2, "a half batch is 32 candidates of 16 blocks");
-    static_assert(BATCH % UNR == 0, "a batch holds whole groups of UNR blocks");
-    unsigned long long bits = 0ull;
-    // entries so far; the cnt % 4 entries of the unfinished group sit in the low 16-bit words
-    // of pend, in order; group g = cnt / 4 goes to word g * stride + col, if g < Kg
-    unsigned long long pend = 0ull;
+    unsigned long long pend = 0ull;                             // the cnt % 4 entries of the unfinished group
     int cnt = 0;
-    auto emit = [&](int base) {
-        __builtin_amdgcn_wave_barrier();
-        const bool merge = __ballot(flo < fhi) != 0ull;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            unsigned b32 = h ? (unsigned)(bits >> 32) : (unsigned)bits;
-            const int hb = base + 16 * h;
-            if (!merge) {
-                // candidate k of the half is partner wblk[hb + k / 2] * BLK + (k % 2) * P + q:
-                // lane k < 32 holds that base, which the lanes read through the crossbar.  The
-                // passes are wave-uniform (a lane out of entries takes none), so that every lane
-                // is active at the crossbar read: an inactive source lane would read as zero.
-                const int jt = lane < 32 ? wblk[hb + (lane >> 1)] * BLK + (lane & 1) * P : 0;
-                while (__ballot(b32 != 0u) != 0ull) {
-                    const int c = min(4, __popc(b32));
-                    unsigned jv[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int k = __ffs(b32) - 1;           // -1 once no bit is left
-                        b32 &= b32 - 1u;
-                        const int j = __shfl(jt, k & 31, 64) + q;
-                        jv[e] = k >= 0 ? (unsigned)j : 0u;
-                    }
-                    const unsigned long long ch = (unsigned long long)(jv[0] | (jv[1] << 16)) |
-                                                  ((unsigned long long)(jv[2] | (jv[3] << 16)) << 32);
-                    const int sh = 16 * (cnt & 3);
-                    const unsigned long long lo = pend | (ch << sh);
-                    if ((cnt & 3) + c >= 4) {
-                        if (cnt < cap) gst(Lr + ((unsigned)(cnt >> 2) * stride32 + col), lo);
-                        pend = sh ? ch >> (64 - sh) : 0ull;
-                    } else {
-                        pend = lo;
-                    }
-                    cnt += c;
-                }
-            } else {
-                while (b32) {
-                    const int k = __ffs(b32) - 1;
-                    b32 &= b32 - 1u;
-                    const unsigned j = (unsigned)(wblk[hb + k / CPB] * BLK + q + (k % CPB) * P);
-                    if (flo < fhi) {
-                        while (flo < fhi && (unsigned)fj[flo] < j) ++flo;
-                        if (flo < fhi && (unsigned)fj[flo] == j) continue;
-                    }
-                    pend |= (unsigned long long)j << (16 * (cnt & 3));
-                    if ((cnt & 3) == 3) {
-                        if (cnt < cap) gst(Lr + ((unsigned)(cnt >> 2) * stride32 + col), pend);
-                        pend = 0ull;
-                    }
-                    ++cnt;
-                }
-            }
-        }
-        bits = 0ull;
-        __builtin_amdgcn_wave_barrier();
-    };
-    for (int cb = 0; cb < nblk; cb += 64) {
+    // near blocks queued in wblk: the byte offset of the block's positions, its light atoms in the top byte
+    static_assert(BLK * 16 == 128, "block indices are taken from bit 7");
+    int nq = 0;
+    constexpr int CHUNK = WBLK - 8;                             // the rest of a batch waits in the queue
+    static_assert(2 * UNR <= 8, "the queue holds a chunk and the rest of a batch");
+    for (int cb = 0; cb < nblk; cb += CHUNK) {
         const int b = cb + lane;
-        bool near = b < nblk;
-        if (near && !allpairs) {
-            // distance from the block's centre to the wave's box, against r_list + its radius
-            const gv_f4 c = sph[b];
-            const float dx = fmaxf(0.f, fmaxf(mnx - c.x, c.x - mxx));
-            const float dy = fmaxf(0.f, fmaxf(mny - c.y, c.y - mxy));
-            const float dz = fmaxf(0.f, fmaxf(mnz - c.z, c.z - mxz));
-            const float lim = (rlb + c.w) * 1.0001f + 1e-6f;
-            near = dx * dx + dy * dy + dz * dz < lim * lim;
+        bool near = b < nblk && lane < CHUNK;
+        unsigned light = 0u;
+        if (near) {
+            const gv_f4 m = box[b];
+            const unsigned w = __float_as_uint(m.w);
+            light = w >> 24;
+            if (!allpairs) {
+                // distance between the two boxes, per axis
+                const float dx = fmaxf(0.f, fabsf(m.x - cx) - fmaf((float)(w & 255u), 0.0078125f, rhx));
+                const float dy = fmaxf(0.f, fabsf(m.y - cy) - fmaf((float)((w >> 8) & 255u), 0.0078125f, rly));
+                const float dz = fmaxf(0.f, fabsf(m.z - cz) - fmaf((float)((w >> 16) & 255u), 0.0078125f, rlz));
+                near = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < rl2 || (w & 0xFFFFFFu) == 0xFFFFFFu;
+            }
         }
         const unsigned long long m = __ballot(near);
-        const int cntm = __popcll(m);
-        if (cntm == 0) continue;
         __builtin_amdgcn_wave_barrier();
-        if (near) wblk[__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = b;
+        if (near) wblk[nq + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (int)((unsigned)(b * (BLK * 16)) | (light << 24));
+        nq += __popcll(m);
         __builtin_amdgcn_wave_barrier();
-        int base = 0;
-        for (int k0 = 0; k0 < cntm; k0 += UNR) {
-            // the next UNR blocks; past the last one (cntm) the last block again, whose test bits
-            // the mask `live` drops.  Every lane reads the same entries, so the block indices and
-            // what follows from them (candidate bases, the exclusion test below) stay scalar; all
-            // reads are in flight before the first use.
-            int raw[UNR], bb[UNR];
+        const bool last = cb + CHUNK >= nblk;
+        int k0 = 0;
+        while (nq - k0 >= 2 * UNR || (last && k0 < nq)) {
+            // UNR tiles; slots past the queue's end read its last block, and their bits are masked
+            int ent[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) raw[u] = wblk[min(k0 + u, cntm - 1)];
+            for (int u = 0; u < UNR; ++u) ent[u] = wblk[min(k0 + 2 * u + jb, nq - 1)];
+            gv_f3 pj[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) bb[u] = __builtin_amdgcn_readfirstlane(raw[u]);
-            const int nlive = min(UNR, cntm - k0);
-            const unsigned live = nlive == UNR ? ~0u : (1u << (nlive * CPB)) - 1u;
-            // (x, y, z) only: a 12-byte read leaves no unused destination register that the
-            // compiler could reuse, and so wait for, before the read completes
-            gv_f3 pj[UNR][CPB];
-            const GPR_LDS gv_f3 *x3 = (const GPR_LDS gv_f3 *)xs;
-#pragma unroll
-            for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                for (int t = 0; t < CPB; ++t)
-                    pj[u][t] = x3[bb[u] * BLK + q + t * P];
+            for (int u = 0; u < UNR; ++u) pj[u] = *(const GPR_LDS gv_f3 *)((const GPR_LDS char *)xs + ((ent[u] & 0xFFFFFF) + 16 * jt));
             __builtin_amdgcn_sched_barrier(0);                  // keep the reads ahead of the tests
-            // a slot past n in the last block holds a far-away position and fails the test; a
-            // lane without an atom (its position also the far-away one) keeps no bit
-            unsigned tb = 0u;
+            gv_f4 D[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
+            for (int u = 0; u < UNR; ++u) {
+                const float dx = pj[u].x - cx, dy = pj[u].y - cy, dz = pj[u].z - cz;
+                const float lj = __int_as_float(__float_as_int(list2_j) & -((ent[u] >> (24 + jt)) & 1));
+                const float n2 = fmaf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), SHORT, -lj);
+                const float aop = q == 0 ? dx : (q == 1 ? dy : (q == 2 ? dz : n2));
+                const gv_f4 c4 = {ci, ci, ci, ci};
+                D[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop, c4, 0, 0, 0);
+            }
 #pragma unroll
-                for (int t = 0; t < CPB; ++t) {
-                    const float dx = pi.x - pj[u][t].x, dy = pi.y - pj[u][t].y, dz = pi.z - pj[u][t].z;
-                    tb |= (unsigned)(fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < rl2) << (u * CPB + t);
-                }
-            tb = valid ? tb & live : 0u;
-            // blocks that may hold the wave's atoms or their excluded partners (wave-uniform)
-            bool self = false;
+            for (int u = 0; u < UNR; ++u) {
+                const int left = nq - (k0 + 2 * u);             // blocks of the tile that are in the queue
+                if (left <= 0) continue;
+                const int e0 = __builtin_amdgcn_readlane(ent[u], 0), e1 = __builtin_amdgcn_readlane(ent[u], 2);
+                const int b0 = (e0 >> 7) & 0x1FFFF, b1 = (e1 >> 7) & 0x1FFFF;
+                if (wide) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
-                self |= u < nlive && bb[u] * BLK + BLK > iw - 32 && bb[u] * BLK < iw + 16 + 32;
-            if (self) {
-#pragma unroll
-                for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                    for (int t = 0; t < CPB; ++t) {
-                        const int off = bb[u] * BLK + q + t * P - i + 32;
-                        const unsigned drop = (unsigned)((unsigned)off < 64u) & (unsigned)((ex >> (off & 63)) & 1ull);
-                        tb &= ~(drop << (u * CPB + t));
+                    for (int v = 0; v < 4; ++v) {
+                        const int t = 4 * (v & 1) + q;
+                        const gv_f4 xj = xs[(v < 2 ? b0 : b1) * BLK + t];
+                        const float dx = pi.x - xj.x, dy = pi.y - xj.y, dz = pi.z - xj.z;
+                        const float lj = (((v < 2 ? e0 : e1) >> (24 + t)) & 1) ? list2_j : 0.f;
+                        const float lim = valid ? list2 + lj : -1.0f;
+                        D[u][v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) - lim;
                     }
+                }
+                // bit v: candidate v is within its list radius
+                unsigned p = __float_as_uint(D[u][3]) >> 31;
+                p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][2]), 31);
+                p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][1]), 31);
+                p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][0]), 31);
+                if (left == 1) p &= 3u;
+                if ((b0 * BLK + BLK > iw - span && b0 * BLK < iw + 16 + span) ||
+                    (b1 * BLK + BLK > iw - span && b1 * BLK < iw + 16 + span)) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int o = (v < 2 ? b0 : b1) * BLK + 4 * (v & 1) + q - i + 32;
+                        const unsigned drop = (unsigned)((unsigned)o < 64u) & (unsigned)(ex >> (o & 63));
+                        p &= ~((drop & 1u) << v);
+                    }
+                }
+                if (has_far && __ballot(flo < fhi) != 0ull) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int j = (v < 2 ? b0 : b1) * BLK + 4 * (v & 1) + q;
+                        if ((p >> v) & 1u) {
+                            while (flo < fhi && fj[flo] < j) ++flo;
+                            if (flo < fhi && fj[flo] == j) p &= ~(1u << v);
+                        }
+                    }
+                }
+                const unsigned pick_lo = (unsigned)__builtin_amdgcn_ds_bpermute((int)(p << 2), sel_lo);
+                const unsigned pick_hi = (unsigned)__builtin_amdgcn_ds_bpermute((int)(p << 2), sel_hi);
+                const unsigned X = (unsigned)(b0 * (BLK * 0x10001) + 0x40000) + (unsigned)q * 0x10001u;
+                const unsigned Y = (unsigned)(b1 * (BLK * 0x10001) + 0x40000) + (unsigned)q * 0x10001u;
+                const unsigned long long ch = (unsigned long long)__builtin_amdgcn_perm(Y, X, pick_lo) |
+                                              ((unsigned long long)__builtin_amdgcn_perm(Y, X, pick_hi) << 32);
+                const int sh = 16 * (cnt & 3), nc = cnt + __popc(p);
+                const unsigned long long low = pend | (ch << sh);
+                const bool full = ((nc ^ cnt) & ~3) != 0;       // the pending group is complete
+                if (full && cnt < cap) gst(Lr + off, low);
+                off += full ? stride : 0u;
+                pend = full ? (ch >> 16) >> (48 - sh) : low;    // (ch >> (64 - sh), zero for sh = 0)
+                cnt = nc;
             }
-            bits |= (unsigned long long)tb << (((k0 - base) % BATCH) * CPB);
-            if (k0 + UNR - base == BATCH) {
-                emit(base);
-                base += BATCH;
-            }
+            k0 += 2 * UNR;
         }
-        emit(base);
+        if (!last) {
+            // blocks short of a batch wait for the next chunk's
+            __builtin_amdgcn_wave_barrier();
+            const int rest = nq - k0;
+            const int t = lane < rest ? wblk[k0 + lane] : 0;
+            __builtin_amdgcn_wave_barrier();
+            if (lane < rest) wblk[lane] = t;
+            nq = rest;
+        }
     }
-    if (!valid) return 0;
-    const int ng = min((cnt + 3) >> 2, S.Kg);
-    if ((cnt & 3) != 0 && cnt < cap) {
-        const unsigned long long pad = (unsigned long long)n * 0x0001000100010001ull;
-        gst(Lr + ((unsigned)(cnt >> 2) * stride32 + col), pend | (pad << (16 * (cnt & 3))));
-    }
-    // PAD: the four sub-lists of an atom padded to the same number of groups with the
-    // far-away atom n (exact zeros), so that one count (the largest, returned) serves the
+    // a partial group is padded; PAD: the four sub-lists of an atom to the same number of groups
+    // with the far-away atom n (exact zeros), so that one count (the largest, returned) serves the
     // atom's four lanes; the counts array keeps each sub-list's own count
+    const int ng = min((cnt + 3) >> 2, Kg);
+    const unsigned long long pad = (unsigned long long)n * 0x0001000100010001ull;
+    if (valid && (cnt & 3) != 0 && cnt < cap) {
+        gst(Lr + off, pend | (pad << (16 * (cnt & 3))));
+        off += stride;
+    }
     int kq = ng;
     if (PAD) {
-        kq = max(ng, __shfl_xor(ng, 1, 64));
-        kq = max(kq, __shfl_xor(kq, 2, 64));
-        const unsigned long long pad = (unsigned long long)n * 0x0001000100010001ull;
-        for (int w = ng; w < kq; ++w) gst(Lr + ((unsigned)w * stride32 + col), pad);
+        kq = max(ng, __shfl_xor(ng, 16, 64));
+        kq = max(kq, __shfl_xor(kq, 32, 64));
+        if (valid)
+            for (int w = ng; w < kq; ++w, off += stride) gst(Lr + off, pad);
     }
-    gmut(S.nbc)[(size_t)r * stride + (size_t)i * P + q] = (unsigned short)ng;
-    if (cnt > cap) atomicOr(&S.err[ERR_LIST], 1);
+    if (valid) {
+        gmut(S.nbc)[(size_t)r * stride + (size_t)i * P + q] = (unsigned short)ng;
+        if (cnt > cap) atomicOr(&S.err[ERR_LIST], 1);
+    }
     return kq;
 }
 
@@ -801,7 +782,7 @@ __global__ void __launch_bounds__(256) k_integrate(const Dev *__restrict__ Sp, l
     if (!finite3(x) || !finite3(v)) atomicOr(&S.err[ERR_UNSTABLE], 1);
     if (S.cutoff_on) {
         const float dx = x.x - XB[a], dy = x.y - XB[np + a], dz = x.z - XB[2 * np + a];
-        if (!(dx * dx + dy * dy + dz * dz <= S.half_skin2)) atomicOr(guard, 1);
+        if (!(dx * dx + dy * dy + dz * dz <= (im > S.im_light ? S.guard2_light : S.guard2_heavy))) atomicOr(guard, 1);
     }
 }
 
@@ -831,8 +812,9 @@ __global__ void __launch_bounds__(256) k_bonded(const Dev *__restrict__ Sp, long
             if (energy) e_acc = fix_f(u);
         }
     } else {
-        bonded_range(S, bonded_plan(S, a0, a1), PosGlob{gconst(S.x) + b, S.np}, a0, a1, fa, len,
-                     energy ? &e_acc : nullptr, tid, len);
+        const int u0 = gconst(S.pl_first)[blockIdx.x], u1 = gconst(S.pl_first)[blockIdx.x + 1];
+        bonded_units(S.pl_bi, S.pl_bp, u0, u1, PosGlob{gconst(S.x) + b, S.np}, a0, fa, len, energy ? &e_acc : nullptr,
+                     __builtin_amdgcn_readfirstlane(tid >> 6), len >> 6, tid & 63);
     }
     __syncthreads();
     const int a = a0 + tid;
@@ -855,8 +837,8 @@ __global__ void __launch_bounds__(1024) k_nonbonded(const Dev *__restrict__ Sp, 
     extern __shared__ __align__(16) unsigned char lds_raw[];
     float4 *xs = (float4 *)lds_raw;
     float2 *pp = (float2 *)(xs + S.np);
-    float4 *sph = (float4 *)(pp + S.np);
-    int *wscr = (int *)(sph + (S.n + BLK - 1) / BLK);      // [16][WBLK] build scratch per wave
+    float4 *box = (float4 *)(pp + S.np);
+    int *wscr = (int *)(box + (S.n + BLK - 1) / BLK);      // [16][WBLK] build scratch per wave
     __shared__ long long e_acc;
     const int r = r_off + blockIdx.y;
     const int tid = threadIdx.x, nthr = blockDim.x;
@@ -889,10 +871,11 @@ __global__ void __launch_bounds__(1024) k_nonbonded(const Dev *__restrict__ Sp, 
     const int q = tid % P;
     const size_t b = (size_t)r * 3 * S.np;
     if (rebuild) {
-        block_spheres(S, xs, sph, tid, nthr);
+        block_boxes(S, xs, box, tid, nthr);
         __syncthreads();
-        build_wave<1, false>(S, r, i, q, i < S.n, (const GPR_LDS gv_f4 *)xs, (const GPR_LDS gv_f4 *)sph,
-                   (GPR_LDS int *)wscr + (tid >> 6) * WBLK, !S.cutoff_on);
+        build_wave<2, false>(Sp, r, blockIdx.x * (nthr / P) + 16 * (tid >> 6), S.n, (const GPR_LDS gv_f4 *)xs,
+                             (const GPR_LDS gv_f4 *)box, (GPR_LDS int *)wscr + (tid >> 6) * WBLK,
+                             !S.cutoff_on);
         if (i < S.n && q == 0) {
             S.xb[b + i] = xs[i].x; S.xb[b + S.np + i] = xs[i].y; S.xb[b + 2 * S.np + i] = xs[i].z;
         }
@@ -1234,8 +1217,9 @@ __device__ void order_atoms(const unsigned short *key, unsigned short *perm, int
     __syncthreads();
 }
 
-__device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, int a0, int a1, int r, int g,
-                                                long long s0, int nsteps, int t0, int sample, int state_end)
+constexpr int NBW = 8;          // waves of a workgroup that start with the bonded units
+__device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, int a0, int a1, int u0, int u1,
+                                                const uint2 *bi, const float4 *bp, int r, int g, long long s0, int nsteps, int t0, int sample, int state_end)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int np = S.np, n = S.n;
@@ -1248,9 +1232,9 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
     float *iml = vs + 3 * lmax;                            // [lmax] 1/m of own atoms
     float *sdl = iml + lmax;                               // [lmax] noise amplitude of own atoms
     float *xbl = sdl + lmax;                               // [3][lmax] own positions at the last list build
-    float4 *sph = (float4 *)(xbl + 3 * lmax);              // [nblk]
-    int *wscr = (int *)(sph + (n + BLK - 1) / BLK);        // [16][WBLK] build scratch per wave
-    unsigned short *perm = (unsigned short *)(wscr + 16 * WBLK);   // [16 ceil(lmax / 16)] pair-loop order
+    float4 *box = (float4 *)(xbl + 3 * lmax);              // [nblk]
+    int *wscr = (int *)(box + (n + BLK - 1) / BLK);        // [16][WBLK] build scratch per wave
+    unsigned short *perm = (unsigned short *)(wscr + 16 * WBLK);  // [16 ceil(lmax / 16)] pair-loop order
     unsigned short *keyl = perm + 16 * ((lmax + 15) >> 4);  // [lmax] groups in each of an atom's sub-lists
     __shared__ int sbuf, bbuf, hbuf, hist[64], ptask, btask;
 
@@ -1312,15 +1296,14 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
     // descriptor fields used every step, held in registers for the launch
     const IntConsts ik = int_consts(S);
     const int t_gr = S.t_gr, need_energy = S.need_energy, cutoff_on = S.cutoff_on, period = S.period;
-    const float half_skin2 = S.half_skin2;
+    const float im_light = S.im_light, guard2_light = S.guard2_light, guard2_heavy = S.guard2_heavy;
     int *const errp = S.err;
     // with several groups every wave waits at the barrier on its own and then takes its share
     // of the other groups' positions: one round trip of device-coherent reads per step
     const bool split = G > 1 && !toy && BT >= 128;
-    // the bonded terms touching the group's atoms, on its last (up to) eight waves: their
-    // topology loads wait on memory, and the other waves meanwhile start the pair tasks
-    const BondedPlan bplan = bonded_plan(S, a0, a1);
-    const int nwv = BT >> 6, nbw = min(nwv, 8), bw0 = nwv - nbw;
+    // the bonded units of the group's atoms go to its last (up to) NBW waves; the other waves
+    // meanwhile start the pair tasks
+    const int nwv = BT >> 6, nbw = min(nwv, NBW), bw0 = nwv - nbw;
     long long *eacc = red + MAX_OBS * 8;
     bool alive = true;
     bool pend = false;                                      // the previous step's closing B is due
@@ -1354,7 +1337,7 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
             bad |= !(finite3(x) && finite3(v));
             if (cutoff_on) {
                 const float dx = x.x - xbl[l], dy = x.y - xbl[lmax + l], dz = x.z - xbl[2 * lmax + l];
-                hit |= !(dx * dx + dy * dy + dz * dz <= half_skin2);
+                hit |= !(dx * dx + dy * dy + dz * dz <= (iml[l] > im_light ? guard2_light : guard2_heavy));
             }
         }
         if (bad) atomicOr(&errp[ERR_UNSTABLE], 1);
@@ -1446,7 +1429,7 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
                 tcost[c] = sum;
             }
             if (tid == 0) btask = 0;
-            block_spheres(S, xs, sph, tid, BT);
+            block_boxes(S, xs, box, tid, BT);
             __syncthreads();
             for (int c = tid; c < ntk; c += BT) {
                 const int mine = tcost[c];
@@ -1461,15 +1444,13 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
                 t = __builtin_amdgcn_readfirstlane(__shfl(t, 0, 64));
                 if (t >= ntk) break;
                 const int c = __builtin_amdgcn_readfirstlane((int)perm[t]);
-                const int L = a0 * P + 64 * c + (tid & 63), i = L / P, q = L % P;
-                const bool valid = L < a1 * P;
-                const int ngw = build_wave<4, true>(S, r, i, q, valid, (const GPR_LDS gv_f4 *)xs,
-                                              (const GPR_LDS gv_f4 *)sph, (GPR_LDS int *)wscr + (tid >> 6) * WBLK,
-                                              false);
-                if (valid && q == 0) {
-                    const int l = i - a0;
-                    xbl[l] = xs[i].x; xbl[lmax + l] = xs[i].y; xbl[2 * lmax + l] = xs[i].z;
-                    keyl[l] = (unsigned short)ngw;
+                const int kq = build_wave<4, true>(&S, r, a0 + 16 * c, a1, (const GPR_LDS gv_f4 *)xs, (const GPR_LDS gv_f4 *)box,
+                                                   (GPR_LDS int *)wscr + (tid >> 6) * WBLK, 0);
+                const int l = 16 * c + (tid & 63);
+                if ((tid & 63) < 16 && l < nl) {
+                    const float4 x = xs[a0 + l];
+                    xbl[l] = x.x; xbl[lmax + l] = x.y; xbl[2 * lmax + l] = x.z;
+                    keyl[l] = (unsigned short)kq;
                 }
             }
             __syncthreads();                     // every task has read its entry of perm
@@ -1494,9 +1475,9 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
         } else {
             // bonded terms on the last waves, then the pair loop, whose tasks (16 atoms each,
             // longest lists first) the waves take from a shared counter as they come free
-            if ((tid >> 6) >= bw0)
-                bonded_range<PosLDS, 2>(S, bplan, PosLDS{xs}, a0, a1, fa, lmax, energy ? eacc : nullptr, tid - bw0 * 64,
-                                        nbw * 64);
+            const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+            if (wv >= bw0)
+                bonded_units(bi, bp, u0, u1, PosLDS{xs}, a0, fa, lmax, energy ? eacc : nullptr, wv - bw0, nbw, tid & 63);
             const int ntask = nslot >> 4;
             const NbConsts nbk = nb_consts(S);
             for (;;) {
@@ -1637,8 +1618,8 @@ __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
     long long s0 = it.s0;
     int t0 = it.t0;
     if (it.cyc && !cycle_start(it, s0, t0)) return;
-    persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], set + it.roff, g, s0, it.nsteps,
-                    t0, it.sample, it.state_end);
+    persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1], it.sp.bi,
+                    it.sp.bp, set + it.roff, g, s0, it.nsteps, t0, it.sample, it.state_end);
 }
 
 // ------------------------------------------------------------------ small systems
@@ -2043,23 +2024,18 @@ __global__ void __launch_bounds__(1024) k_persist_small(PersistItem it)
     persist_small(*it.dev, r, s0, it.nsteps, t0, it.sample, it.state_end);
 }
 
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ long long uni64(long long v)
-{
-    const int lo = uni((int)(unsigned)v), hi = uni((int)(v >> 32));
-    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
 // the per-replica body as a function of its own (one call per replica and launch), so that
 // the loop around it in k_persist_batch does not add to the body's register pressure.  The
 // arguments of a call arrive in vector registers; they are wave-uniform, and made so again,
 // so that the values and branches that depend on them stay scalar.
-__device__ __noinline__ void persist_replica_call(const Dev *dev, int G, int lmax, int a0, int a1, int r, int g,
-                                                  long long s0, int nsteps, int t0, int sample, int state_end)
+__device__ __noinline__ void persist_replica_call(const Dev *dev, int G, int lmax, int a0, int a1, int u0, int u1,
+                                                  const uint2 *bi, const float4 *bp, int r, int g, long long s0, int nsteps,
+                                                  int t0, int sample, int state_end)
 {
     const Dev *d = (const Dev *)uni64((long long)dev);
-    persist_replica(*d, uni(G), uni(lmax), uni(a0), uni(a1), uni(r), uni(g), uni64(s0), uni(nsteps), uni(t0),
-                    uni(sample), uni(state_end));
+    persist_replica(*d, uni(G), uni(lmax), uni(a0), uni(a1), uni(u0), uni(u1), (const uint2 *)uni64((long long)bi),
+                    (const float4 *)uni64((long long)bp), uni(r), uni(g), uni64(s0), uni(nsteps), uni(t0), uni(sample),
+                    uni(state_end));
 }
 
 // Several systems, each item's sets taking its replicas r = set, set + nsets, ... in turn.
@@ -2071,8 +2047,8 @@ __global__ void __launch_bounds__(1024) k_persist_batch(PersistBatch pb)
     int set, g;
     if (!persist_place(it, (int)blockIdx.x - it.boff, set, g)) return;
     for (int r = set; r < it.nrep; r += it.nsets) {
-        persist_replica_call(it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], r, g, it.s0, it.nsteps,
-                             it.t0, it.sample, it.state_end);
+        persist_replica_call(it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1],
+                             it.sp.bi, it.sp.bp, r, g, it.s0, it.nsteps, it.t0, it.sample, it.state_end);
         __syncthreads();
     }
 }
