@@ -258,13 +258,15 @@ static Split make_split(const std::vector<double> &work, int n, int np, int G)
 
 static int split_index(int G) { return G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3; }
 
-static size_t persist_lds(int n, int np, const Split &sp)
+static size_t persist_lds(int n, int np, const Split &sp) { return (size_t)persist_off(n, np, sp.lmax).gn; }
+
+// Whether workgroups of bt threads keep the next step's Gaussians in LDS too: where it fits and
+// leaves as many workgroups on a compute unit (16 waves at the kernel's register count)
+static bool noise_fits(int n, int np, const Split &sp, int bt, int maxlds)
 {
-    const int lmax = sp.lmax;
-    const int nblk = (n + BLK - 1) / BLK;
-    return (size_t)3 * lmax * 8 + (MAX_OBS * 8 + 8) * 8 + MAX_OBS * 8 + (size_t)np * 16 + (size_t)np * 8 +
-           (size_t)8 * lmax * 4 + (size_t)nblk * 16 + (size_t)16 * WBLK * 4 + (size_t)32 * ((lmax + 15) / 16) +
-           (size_t)2 * lmax;
+    const PersistOff o = persist_off(n, np, sp.lmax);
+    const int waves = std::max(1, 1024 / bt);
+    return o.end <= maxlds && std::min(waves, maxlds / o.end) == std::min(waves, maxlds / o.gn);
 }
 
 // LDS of k_persist_small (the order of small_lds_layout) and its units of work per step
@@ -294,13 +296,14 @@ struct RunShape {
     int bt;
     const Split *sp;
     bool small;                // k_persist_small, else k_persist
+    bool noise_ahead;          // k_persist: the next step's Gaussians in LDS
     size_t lds;
 };
 static RunShape run_shape(const gpr_system *S, int nrep)
 {
     auto chosen = [&](int from) { return from == 2 || (from == 1 && nrep == S->R); };
     const int cus = std::max(1, S->max_coresident);
-    RunShape sh{S->bt_persist, &S->split, false, 0};
+    RunShape sh{S->bt_persist, &S->split, false, false, 0};
     if (S->small_ok && S->groups == 1) {
         sh.small = true;
         if (!chosen(S->bt_from)) {
@@ -315,7 +318,8 @@ static RunShape run_shape(const gpr_system *S, int nrep)
             const int G = 1 << k;
             if (G > sh.sp->G && S->split_ok[k] && S->n >= 64 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
         }
-    sh.lds = persist_lds(S->n, S->np, *sh.sp);
+    sh.noise_ahead = noise_fits(S->n, S->np, *sh.sp, sh.bt, S->maxlds_persist);
+    sh.lds = sh.noise_ahead ? (size_t)persist_off(S->n, S->np, sh.sp->lmax).end : persist_lds(S->n, S->np, *sh.sp);
     return sh;
 }
 
@@ -391,8 +395,9 @@ static hipError_t make_units(gpr_system *S, const std::vector<int> &bnd, gpr_sys
     return e;
 }
 
-// the split with its bonded units, laid out when a launch first needs them (never under capture:
-// captured launches take them before the capture begins)
+// The split with its bonded units.  Those of the shapes that launches take by themselves are laid out
+// when the path or the shape is set (0.1 ms each), others when a launch first needs them (never under
+// capture: captured launches take them before the capture begins).
 static gpr_status split_units(gpr_system *S, Split &sp)
 {
     gpr_system::Units &U = S->units_split[split_index(sp.G)];
@@ -400,6 +405,17 @@ static gpr_status split_units(gpr_system *S, Split &sp)
     for (int g = 0; g <= sp.G; ++g) sp.bu[g] = U.first[g];
     sp.bi = U.bi;
     sp.bp = U.bp;
+    return GPR_OK;
+}
+static gpr_status shape_units(gpr_system *S)
+{
+    for (const int nrep : {S->R, 1}) {
+        const RunShape sh = run_shape(S, nrep);
+        if (sh.small) continue;
+        Split sp = *sh.sp;
+        const gpr_status rc = split_units(S, sp);
+        if (rc) return rc;
+    }
     return GPR_OK;
 }
 
@@ -686,6 +702,7 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
         const RunShape sh = run_shape(S, nrep);
         gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, pb.it[0], nblocks);
         if (rc) return rc;
+        pb.it[0].noise_ahead = sh.noise_ahead ? 1 : 0;
         // more replicas than sets that fit at once: rounds of launches, each set taking one
         // replica per launch (replicas are independent between checks)
         const int rounds = (nrep + pb.it[0].nsets - 1) / pb.it[0].nsets;
@@ -1326,6 +1343,10 @@ extern "C" gpr_status gpr_set_path(gpr_system *S, int32_t path)
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
     if (path != GPR_PATH_PLAIN && path != GPR_PATH_PERSISTENT) return fail(S, GPR_EINVAL, "bad path");
     if (path == GPR_PATH_PERSISTENT && !S->persist_ok) return fail(S, GPR_EINVAL, "system too large for the persistent path");
+    if (path == GPR_PATH_PERSISTENT) {
+        const gpr_status rc = shape_units(S);
+        if (rc) return rc;
+    }
     S->path = path;
     return GPR_OK;
 }
@@ -1356,7 +1377,7 @@ extern "C" gpr_status gpr_set_launch(gpr_system *S, int32_t block_threads, int32
         S->groups = groups_per_replica;
         S->split = S->splits[split_index(groups_per_replica)];
     }
-    return GPR_OK;
+    return S->path == GPR_PATH_PERSISTENT ? shape_units(S) : GPR_OK;
 }
 
 // Launch-shape autotuner of the persistent path: every (threads per workgroup, workgroups per
@@ -1980,6 +2001,7 @@ static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
     const RunShape sh = run_shape(S, nrep);
     gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, pb.it[0], nblocks);
     if (rc) return rc;
+    pb.it[0].noise_ahead = sh.noise_ahead ? 1 : 0;
     const int rounds = (nrep + pb.it[0].nsets - 1) / pb.it[0].nsets;
     rc = check_layout(S, pb, nblocks, sh.bt, true);
     if (rc) return rc;

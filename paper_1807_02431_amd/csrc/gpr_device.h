@@ -166,6 +166,7 @@ __device__ __forceinline__ GPR_GLOBAL T *gmut(T *p) { return (GPR_GLOBAL T *)p; 
 typedef int gv_i2 __attribute__((ext_vector_type(2)));
 typedef int gv_i4 __attribute__((ext_vector_type(4)));
 typedef unsigned gv_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned gv_u4 __attribute__((ext_vector_type(4)));
 typedef float gv_f2 __attribute__((ext_vector_type(2)));
 typedef float gv_f4 __attribute__((ext_vector_type(4)));
 typedef float gv_f3 __attribute__((ext_vector_type(3)));   // 16-byte size and alignment, 12-byte loads
@@ -227,6 +228,22 @@ __device__ __forceinline__ float3 gauss3(uint4 w)
 // f 2^32 + 1.5 2^52 lies in [2^52, 2^53), where the spacing is 1, so one rounding leaves the
 // integer in the low bits of the mantissa: exact while |f| < 2^19.  Larger values (and NaN)
 // saturate at +-FSAT, which the FMAX_FIX test on the summed force reports as unstable.
+// FixConsts: the scale and the offset in registers, so that a conversion is four instructions (the
+// compiler otherwise writes the offset into the FMA's destination each time, two more).
+struct FixConsts {
+    double scale, offset;
+};
+__device__ __forceinline__ FixConsts fix_consts()
+{
+    FixConsts k{FIX, 6755399441055744.0};
+    asm volatile("" : "+s"(k.scale), "+v"(k.offset));
+    return k;
+}
+__device__ __forceinline__ long long fix_f(const FixConsts &k, float f)
+{
+    const double y = __builtin_fma((double)__builtin_amdgcn_fmed3f(f, -FSAT, FSAT), k.scale, k.offset);
+    return __double_as_longlong(y) - 0x4338000000000000LL;
+}
 __device__ __forceinline__ long long fix_f(float f)
 {
     const float c = fminf(fmaxf(f, -FSAT), FSAT);
@@ -246,6 +263,9 @@ __device__ __forceinline__ void lds_add(long long *p, long long v)
 {
     atomicAdd((unsigned long long *)p, (unsigned long long)v);
 }
+
+// *p++ of an LDS counter
+__device__ __forceinline__ int lds_inc(GPR_LDS int *p) { return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
 __device__ __forceinline__ bool bad_force(float f) { return !(fabsf(f) < FMAX_FIX); }
 

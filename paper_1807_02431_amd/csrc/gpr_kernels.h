@@ -59,6 +59,31 @@ __global__ void k_bonded(const Dev *__restrict__ Sp, long long s, int r_off, int
 __global__ void k_nonbonded(const Dev *__restrict__ Sp, long long s, int r_off, int energy, int apply_b, int force_build);
 __global__ void k_obs(const Dev *__restrict__ Sp, int r_off, int mode, double *out, int k);
 __global__ void k_state(const Dev *__restrict__ Sp, int r_off);
+// LDS of a workgroup of the persistent kernel: byte offsets of its arrays (the LJ parameters, float2
+// [np], come first: a list entry is an offset into them) and the end with the next step's Gaussians
+struct PersistOff {
+    int fa, red, vals, xs, vs, iml, sdl, xbl, box, wscr, perm, keyl, gn, end;
+};
+__host__ __device__ inline PersistOff persist_off(int n, int np, int lmax)
+{
+    PersistOff o;
+    o.fa = np * 8;                                    // int64 [lmax][3] force accumulators
+    o.red = o.fa + 3 * lmax * 8;                       // int64 [MAX_OBS * 8 + 8]
+    o.vals = o.red + (MAX_OBS * 8 + 8) * 8;            // double [MAX_OBS]
+    o.xs = o.vals + MAX_OBS * 8;                       // float4 [np] (x, y, z, q sqrt f)
+    o.vs = o.xs + np * 16;                             // float [3][lmax]
+    o.iml = o.vs + 3 * lmax * 4;                       // float [lmax]
+    o.sdl = o.iml + lmax * 4;                          // float [lmax]
+    o.xbl = o.sdl + lmax * 4;                          // float [3][lmax]
+    o.box = o.xbl + 3 * lmax * 4;                      // float4 [blocks]
+    o.wscr = o.box + (n + BLK - 1) / BLK * 16;         // int [16][WBLK]
+    o.perm = o.wscr + 16 * WBLK * 4;                   // uint16 [16 ceil(lmax / 16)]
+    o.keyl = o.perm + 32 * ((lmax + 15) / 16);         // uint16 [lmax]
+    o.gn = o.keyl + 2 * lmax;                          // float [3][lmax]
+    o.end = o.gn + 3 * lmax * 4;
+    return o;
+}
+
 // one system's share of a persistent launch (see k_persist)
 struct PersistItem {
     const Dev *dev;     // device descriptor of the system
@@ -67,6 +92,7 @@ struct PersistItem {
     int nsteps, t0;     // steps of this launch; steps already taken in the current call
     int sample;         // accumulate worker observables every t_GR steps (t counted from t0)
     int state_end;      // write each replica's state id at the end
+    int noise_ahead;    // the LDS holds the next step's Gaussians, drawn off the critical path
     int nrep;           // replicas of the system
     int nsets;          // sets of sp.G workgroups that share the replicas
     int roff;           // k_persist: set k takes replica roff + k

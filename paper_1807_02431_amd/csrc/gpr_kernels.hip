@@ -50,25 +50,36 @@ __device__ __forceinline__ long long uni64(long long v)
     return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
+// The value again, with its origin hidden: what is computed from it inside a loop stays there.  The
+// step loops of the persistent kernels take their array addresses from such values, a few
+// instructions per phase; hoisted out of the loop, as the compiler does with invariants, the
+// addresses of all phases together exceed the registers, and every step reloads them from scratch.
+__device__ __forceinline__ int fresh_s(int v) { v = uni(v); asm volatile("" : "+s"(v)); return v; }
+__device__ __forceinline__ int fresh_v(int v) { asm volatile("" : "+v"(v)); return v; }
+
 // ------------------------------------------------------------------ bonded terms of an atom range
 // One unit of 64 terms of a kind (records w, p of the lane): adds the fixed-point forces on the
-// atoms of the range to fa[3][len] (LDS, index a - a0); EDGE: only on the atoms the range owns.
-// Returns the lane's energy, counted by one range per term.
-template <int KIND, bool EDGE, class Pos>
-__device__ __forceinline__ long long bonded_terms(const uint2 w, const float4 p, const Pos &pos, int a0, long long *fa, int len)
+// atoms of the range to fa (LDS; component d of atom a at fa[(a - a0) sa + d sd]); EDGE: only on the
+// atoms the range owns.  ENERGY: returns the lane's energy, counted by one range per term.
+struct ForceLDS {
+    long long *fa;
+    int a0, sa, sd;
+};
+template <int KIND, bool EDGE, bool ENERGY, class Pos>
+__device__ __forceinline__ long long bonded_terms(const uint2 w, const float4 p, const Pos &pos, const ForceLDS &F, const FixConsts &K)
 {
     auto add = [&](unsigned field, float3 f) {
-        const int a = (int)(field & (BONDED_ATOMS - 1)) - a0;
         if (!EDGE || (field & BONDED_ATOMS)) {
-            lds_add(&fa[a], fix_f(f.x));
-            lds_add(&fa[len + a], fix_f(f.y));
-            lds_add(&fa[2 * len + a], fix_f(f.z));
+            long long *const t = F.fa + ((int)(field & (BONDED_ATOMS - 1)) - F.a0) * F.sa;
+            lds_add(t, fix_f(K, f.x));
+            lds_add(t + F.sd, fix_f(K, f.y));
+            lds_add(t + 2 * F.sd, fix_f(K, f.z));
         }
     };
     auto at = [&](unsigned field) { return pos((int)(field & (BONDED_ATOMS - 1))); };
     if (!(w.y & 0x8000u)) return 0;
     const unsigned f0 = w.x, f1 = w.x >> 16, f2 = w.y, f3 = w.y >> 16;
-    float u;
+    float u = 0.f;
     if (KIND == 0) {
         float3 fi;
         u = term_bond(at(f0), at(f1), make_float2(p.x, p.y), fi);
@@ -91,24 +102,25 @@ __device__ __forceinline__ long long bonded_terms(const uint2 w, const float4 p,
         const float3 x = at(f0);
         const float dx = x.x - p.x, dy = x.y - p.y, dz = x.z - p.z;
         add(f0, make_float3(-p.w * dx, -p.w * dy, -p.w * dz));
-        u = 0.5f * p.w * (dx * dx + dy * dy + dz * dz);
+        if (ENERGY) u = 0.5f * p.w * (dx * dx + dy * dy + dz * dz);
     } else {
         float3 fi;
         u = term_pair14(at(f0), at(f1), p, fi);
         add(f0, fi);
         add(f1, neg3(fi));
     }
-    return (f2 & 0x4000u) ? fix_f(u) : 0;
+    return ENERGY && (f2 & 0x4000u) ? fix_f(K, u) : 0;
 }
 
 // Units [u0, u1) of the records bi, bp, taken in turn by waves wv = 0 .. nwv - 1 of the range's
 // workgroup; each wave reads its next unit's records while it computes one, since what bounds the
 // terms otherwise is the latency of reading them (the records come from the L2: the pair lists
 // stream through the L1).
-template <class Pos>
-__device__ __forceinline__ void bonded_units(const uint2 *bi, const float4 *bp, int u0, int u1, const Pos &pos, int a0,
-                                             long long *fa, int len, long long *e_acc, int wv, int nwv, int lane)
+template <bool ENERGY, class Pos>
+__device__ __forceinline__ long long bonded_units(const uint2 *bi, const float4 *bp, int u0, int u1, const Pos &pos,
+                                                  const ForceLDS &F, int wv, int nwv, int lane)
 {
+    const FixConsts K = fix_consts();
     long long e = 0;
     int u = u0 + wv;
     uint2 w = make_uint2(0u, 0u);
@@ -127,19 +139,19 @@ __device__ __forceinline__ void bonded_units(const uint2 *bi, const float4 *bp, 
         }
         const int kind = __builtin_amdgcn_readfirstlane((int)(((cw.x >> 14) & 3u) | ((cw.x >> 28) & 12u)));
         switch (kind) {
-        case 0: e += bonded_terms<0, false>(cw, cp, pos, a0, fa, len); break;
-        case 1: e += bonded_terms<1, false>(cw, cp, pos, a0, fa, len); break;
-        case 2: e += bonded_terms<2, false>(cw, cp, pos, a0, fa, len); break;
-        case 3: e += bonded_terms<3, false>(cw, cp, pos, a0, fa, len); break;
-        case 4: e += bonded_terms<4, false>(cw, cp, pos, a0, fa, len); break;
-        case BONDED_EDGE + 0: e += bonded_terms<0, true>(cw, cp, pos, a0, fa, len); break;
-        case BONDED_EDGE + 1: e += bonded_terms<1, true>(cw, cp, pos, a0, fa, len); break;
-        case BONDED_EDGE + 2: e += bonded_terms<2, true>(cw, cp, pos, a0, fa, len); break;
-        case BONDED_EDGE + 3: e += bonded_terms<3, true>(cw, cp, pos, a0, fa, len); break;
-        default: e += bonded_terms<4, true>(cw, cp, pos, a0, fa, len); break;
+        case 0: e += bonded_terms<0, false, ENERGY>(cw, cp, pos, F, K); break;
+        case 1: e += bonded_terms<1, false, ENERGY>(cw, cp, pos, F, K); break;
+        case 2: e += bonded_terms<2, false, ENERGY>(cw, cp, pos, F, K); break;
+        case 3: e += bonded_terms<3, false, ENERGY>(cw, cp, pos, F, K); break;
+        case 4: e += bonded_terms<4, false, ENERGY>(cw, cp, pos, F, K); break;
+        case BONDED_EDGE + 0: e += bonded_terms<0, true, ENERGY>(cw, cp, pos, F, K); break;
+        case BONDED_EDGE + 1: e += bonded_terms<1, true, ENERGY>(cw, cp, pos, F, K); break;
+        case BONDED_EDGE + 2: e += bonded_terms<2, true, ENERGY>(cw, cp, pos, F, K); break;
+        case BONDED_EDGE + 3: e += bonded_terms<3, true, ENERGY>(cw, cp, pos, F, K); break;
+        default: e += bonded_terms<4, true, ENERGY>(cw, cp, pos, F, K); break;
         }
     }
-    if (e_acc && e != 0) lds_add(e_acc, e);
+    return e;
 }
 
 // the double well of the toy system, U = (x^2 - 1)^2 + 2 y^2
@@ -152,69 +164,107 @@ __device__ __forceinline__ float toy_force(float x, float y, float &fx, float &f
 }
 
 // ------------------------------------------------------------------ pair search
-// Bounding boxes of blocks of BLK consecutive atoms (chain-local, so compact): the middle, and in
-// one word the half extents in units of 1/128 nm, rounded up (a byte each; all three 255: too large
-// to say), with the block's mask of light atoms in the top byte.
-__device__ void block_boxes(const Dev &S, const float4 *xs, float4 *box, int tid, int nthr)
+// A value that every lane holds alike, as a scalar
+__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
+// min / max over each row of 16 lanes and over each eight lanes, in every lane
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)); }
+constexpr int ROR8 = 0x128, ROR4 = 0x124, ROR2 = 0x122, ROR1 = 0x121, SWAP1 = 0xB1, SWAP2 = 0x4E, HALF_MIRROR = 0x141;
+__device__ __forceinline__ float row_min(float v)
 {
-    const int nblk = (S.n + BLK - 1) / BLK;
-    for (int t = tid; t < nblk; t += nthr) {
-        const int a0 = t * BLK, a1 = min(S.n, a0 + BLK);
-        const unsigned light = gconst(S.cls)[t];
-        float3 lo = make_float3(xs[a0].x, xs[a0].y, xs[a0].z), hi = lo;
-        for (int a = a0 + 1; a < a1; ++a) {
-            const float4 x = xs[a];
-            lo.x = fminf(lo.x, x.x); lo.y = fminf(lo.y, x.y); lo.z = fminf(lo.z, x.z);
-            hi.x = fmaxf(hi.x, x.x); hi.y = fmaxf(hi.y, x.y); hi.z = fmaxf(hi.z, x.z);
-        }
+    v = fminf(v, dpp_f<ROR8>(v));
+    v = fminf(v, dpp_f<ROR4>(v));
+    v = fminf(v, dpp_f<ROR2>(v));
+    return fminf(v, dpp_f<ROR1>(v));
+}
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, dpp_f<ROR8>(v));
+    v = fmaxf(v, dpp_f<ROR4>(v));
+    v = fmaxf(v, dpp_f<ROR2>(v));
+    return fmaxf(v, dpp_f<ROR1>(v));
+}
+__device__ __forceinline__ float oct_min(float v)
+{
+    v = fminf(v, dpp_f<SWAP1>(v));
+    v = fminf(v, dpp_f<SWAP2>(v));
+    return fminf(v, dpp_f<HALF_MIRROR>(v));
+}
+__device__ __forceinline__ float oct_max(float v)
+{
+    v = fmaxf(v, dpp_f<SWAP1>(v));
+    v = fmaxf(v, dpp_f<SWAP2>(v));
+    return fmaxf(v, dpp_f<HALF_MIRROR>(v));
+}
+
+// The point that the search's tiles take positions relative to: near the middle of the replica
+__device__ __forceinline__ float3 search_centre(const GPR_LDS gv_f4 *xs, int n)
+{
+    const gv_f4 a = xs[0], b = xs[n / 3], c = xs[(2 * n) / 3], d = xs[n - 1];
+    return make_float3(uniform_f(0.25f * (a.x + b.x + c.x + d.x)), uniform_f(0.25f * (a.y + b.y + c.y + d.y)),
+                       uniform_f(0.25f * (a.z + b.z + c.z + d.z)));
+}
+
+constexpr float TILE_SHORT = 1.0f - 9.5367431640625e-7f;       // 1 - 2^-20 (see search_task)
+constexpr float TILE_MAX2 = 4096.0f;                           // (64 nm)^2 (see search_task)
+
+// Bounding boxes of blocks of BLK consecutive atoms (chain-local, so compact), eight lanes a block:
+// the middle, and in one word the half extents in units of 1/128 nm, rounded up (a byte each; all
+// three 255: too large to say) under the block's mask of light atoms, which is kept from what the
+// word held (the caller set it once).  Each atom's |d|^2 - list2_j for the tiles (d from the centre
+// c) takes the place of its sigma/2, which the caller restores after the search.  True when an atom is too far out
+// for the tiles.
+__device__ __forceinline__ bool block_boxes(const GPR_CONST Dev &S, const GPR_LDS gv_f4 *xs, GPR_LDS gv_f2 *pp, GPR_LDS gv_f4 *box,
+                                            float3 c, int tid, int nthr)
+{
+    const int n = S.n, nblk = (n + BLK - 1) / BLK;
+    const float list2_j = S.list2_j;
+    bool out = false;
+    for (int a = tid; a < BLK * nblk; a += nthr) {
+        const int t = a / BLK, k = a % BLK;
+        const unsigned light = __float_as_uint(box[t].w) >> 24;
+        const gv_f4 x = xs[a];
+        const bool real = a < n;
+        const float dx = x.x - c.x, dy = x.y - c.y, dz = x.z - c.z;
+        const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        pp[a].x = fmaf(d2, TILE_SHORT, ((light >> k) & 1u) ? -list2_j : 0.0f);
+        out |= real && !(d2 < TILE_MAX2);
+        const float big = 3.0e38f;
+        const float lx = oct_min(real ? x.x : big), hx = oct_max(real ? x.x : -big);
+        const float ly = oct_min(real ? x.y : big), hy = oct_max(real ? x.y : -big);
+        const float lz = oct_min(real ? x.z : big), hz = oct_max(real ? x.z : -big);
         // (half the box, and what rounding may take from the distance to it: 2^-20 of a coordinate)
-        const float3 m = make_float3(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z));
         auto units = [](float l, float h) {
             const float e = 0.5f * (h - l) + 9.5e-7f * fmaxf(fabsf(l), fabsf(h));
             return e < 1.97f ? (unsigned)(e * 128.0f) + 1u : 255u;      // (a NaN too)
         };
-        const unsigned ux = units(lo.x, hi.x), uy = units(lo.y, hi.y), uz = units(lo.z, hi.z);
+        const unsigned ux = units(lx, hx), uy = units(ly, hy), uz = units(lz, hz);
         const unsigned ext = (ux == 255u || uy == 255u || uz == 255u) ? 0xFFFFFFu : ux | (uy << 8) | (uz << 16);
-        box[t] = make_float4(m.x, m.y, m.z, __uint_as_float(ext | (light << 24)));
+        if (k == 0) {
+            const gv_f4 b = {0.5f * (lx + hx), 0.5f * (ly + hy), 0.5f * (lz + hz), __uint_as_float(ext | (light << 24))};
+            box[t] = b;
+        }
     }
+    return out;
 }
 
-// a value that every lane holds alike, as a scalar
-__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
-
-// min / max over each row of 16 lanes, in every lane
-template <int N>
-__device__ __forceinline__ float row_ror(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 | N, 0xF, 0xF, true)); }
-__device__ __forceinline__ float row_min(float v)
-{
-    v = fminf(v, row_ror<8>(v));
-    v = fminf(v, row_ror<4>(v));
-    v = fminf(v, row_ror<2>(v));
-    return fminf(v, row_ror<1>(v));
-}
-__device__ __forceinline__ float row_max(float v)
-{
-    v = fmaxf(v, row_ror<8>(v));
-    v = fmaxf(v, row_ror<4>(v));
-    v = fmaxf(v, row_ror<2>(v));
-    return fmaxf(v, row_ror<1>(v));
-}
-
-// Entry p of the table that packs a lane's kept candidates: of the four 16-bit values in (X, Y)
-// those whose bit is set in p, in order, as the byte selectors of two v_perm_b32 (zeros after them)
+// Entry 4 p + c of the table that packs a lane's kept candidates after the c entries of its pending
+// group: of the four 16-bit values in (X, Y) those whose bit is set in p, in order, from slot c of
+// eight; as the byte selectors of four v_perm_b32 (zeros in the other slots): the pending group's
+// two words, then the two of the group after it
 struct PickTable {
-    unsigned lo[16], hi[16];
+    unsigned w[64][4];
 };
 constexpr PickTable make_pick()
 {
     PickTable t{};
-    for (int p = 0; p < 16; ++p) {
-        unsigned sel[4] = {0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu};
-        int c = 0;
+    for (int e = 0; e < 64; ++e) {
+        unsigned slot[8] = {0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu, 0x0C0Cu};
+        int m = e & 3;
         for (unsigned v = 0; v < 4; ++v)
-            if ((p >> v) & 1) sel[c++] = 2 * v | ((2 * v + 1) << 8);
-        t.lo[p] = sel[0] | (sel[1] << 16);
-        t.hi[p] = sel[2] | (sel[3] << 16);
+            if ((e >> (2 + v)) & 1) slot[m++] = 2 * v | ((2 * v + 1) << 8);
+        for (int k = 0; k < 4; ++k) t.w[e][k] = slot[2 * k] | (slot[2 * k + 1] << 16);
     }
     return t;
 }
@@ -223,41 +273,38 @@ __device__ __constant__ const PickTable pick_table = make_pick();
 // Pair lists of the atoms [iw, iw + 16) below iend, by one wave; all 64 lanes call it together with
 // the same arguments.  Lane 16 q + k owns sub-list (i, q) of atom i = iw + k: partners j = q (mod P),
 // j != i, not excluded, r^2 < list2 of the two atoms' classes, in ascending order; entry e is the
-// 16-bit word e % 4 of group e / 4; the last group is padded with the dummy atom n.  allpairs: no
-// distance tests (vacuum, no cutoff).
+// 16-bit word e % 4 of group e / 4, holding 8 j (the byte offset of j's LJ parameters in LDS, half
+// that of its position); the last group is padded with the dummy atom n.  allpairs: no
+// distance tests (vacuum, no cutoff).  After block_boxes, with its boxes and centre.
 //
 // Culling is wave-wide: each lane tests one block's box against the box of the wave's atoms, and
 // the near blocks queue up in the wave's LDS scratch wblk (ascending).  Two blocks at a time are
-// tested by one v_mfma_f32_16x16x4_f32: with d the positions relative to the middle of the wave's
-// box, D = |d_j|^2 + |d_i|^2 - list2 - 2 d_i . d_j for 16 partners (rows) x 16 atoms (columns), the
-// sum over K = 4 taking (d_x, d_y, d_z, |d_j|^2 - list2_j) of the partner against (-2 d_i, 1) of the
-// atom, and a pair is listed when D < 0.  Row 4 q + v holds atom 4 (v % 2) + q of block v / 2, so the
-// four values a lane gets are its own candidates in order, one sign bit each; the vector unit does
-// 16 instructions for 256 pairs instead of nine for 64.  A list may hold more pairs than needed but
-// never fewer: the squares are taken 2^-20 short, which covers the rounding of D (each of its six
-// terms is at most |d_i|^2 + |d_j|^2), and boxes wider than 64 nm, where that would admit pairs
-// 0.004 nm^2 and more too far, take the distances directly.
-// The kept candidates of a lane (at most four per tile) are packed by two byte permutes whose
-// selectors the lanes hold (entry `lane` of the 16) and read from each other, and merged into the
-// pending group with one shift.
+// tested by one v_mfma_f32_16x16x4_f32: with d the positions relative to c, D = |d_j|^2 + |d_i|^2 -
+// list2 - 2 d_i . d_j for 16 partners (rows) x 16 atoms (columns), the sum over K = 4 taking (d_x,
+// d_y, d_z, |d_j|^2 - list2_j) of the partner against (-2 d_i, 1) of the atom, and a pair is listed when D < 0.
+// Row 4 q + v holds atom 4 (v % 2) + q of block v / 2, so the four values a lane gets are its own
+// candidates in order, one sign bit each: seven vector instructions for 256 pairs, where testing
+// them one by one takes nine for 64.  A list may hold more pairs than needed but never fewer: the
+// squares are taken 2^-20 short, which covers the rounding of D (each of its six terms is at most
+// |d_i|^2 + |d_j|^2); with an atom more than 64 nm from c (`wide`), where that would admit pairs
+// 0.008 nm^2 too far, the tiles take the distances directly.
+// The kept candidates of a lane (at most four per tile) are packed and shifted into place by byte
+// permutes whose selectors the lanes hold (entry `lane` of the table) and read from each other.
 // Excluded partners within 32 atoms (and the atom itself) are dropped only in tiles that may hold
 // some; farther ones are merged out against the atom's ascending list far_j.
-// Bound by VALU issue: 25-30 instructions per tile and about 17 tiles a task on the 2,432-atom
-// system.  UNR tiles are read at a time (more registers, fewer exposed LDS latencies); the plain
-// path's pair kernel uses 2 to keep its occupancy.
+// Bound by VALU issue: about 27 instructions per tile and 17 tiles a task on the 2,432-atom system.
+// UNR tiles are read at a time (more registers, fewer exposed LDS latencies).
 template <int UNR, bool PAD>
-__device__ __noinline__ int build_wave(const Dev *Sv, int r_, int iw_, int iend_, const GPR_LDS gv_f4 *xs,
-                                       const GPR_LDS gv_f4 *box, GPR_LDS int *wblk, int allpairs_)
+__device__ __forceinline__ int search_task(const GPR_CONST Dev &S, int r, int iw, int iend, const GPR_LDS gv_f4 *xs,
+                                           const GPR_LDS gv_f2 *pp, const GPR_LDS gv_f4 *box, GPR_LDS int *wblk, float3 c,
+                                           bool wide, bool allpairs)
 {
-    const GPR_CONST Dev &S = *(const GPR_CONST Dev *)uni64((long long)Sv);
-    const int r = uni(r_), iw = uni(iw_), iend = uni(iend_);
-    const bool allpairs = uni(allpairs_) != 0;
     const int n = S.n, Kg = S.Kg, span = S.excl_span;
     const unsigned stride = (unsigned)S.np * P;
     const int lane = threadIdx.x & 63, q = lane >> 4, k16 = lane & 15;
     const int i = iw + k16;
     const bool valid = i < iend;
-    const int sel_lo = (int)pick_table.lo[k16], sel_hi = (int)pick_table.hi[k16];
+    const gv_u4 sel = *(const GPR_GLOBAL gv_u4 *)gconst(&pick_table.w[lane][0]);
     const gv_f4 pi = xs[valid ? i : n];
     // box of the wave's valid atoms (the same in every row of lanes)
     const float big = 3.0e38f;
@@ -265,137 +312,135 @@ __device__ __noinline__ int build_wave(const Dev *Sv, int r_, int iw_, int iend_
     if (!(mnx <= mxx)) return 0;                                // no valid atom in this wave
     const float mny = uniform_f(row_min(valid ? pi.y : big)), mxy = uniform_f(row_max(valid ? pi.y : -big));
     const float mnz = uniform_f(row_min(valid ? pi.z : big)), mxz = uniform_f(row_max(valid ? pi.z : -big));
-    const float cx = 0.5f * (mnx + mxx), cy = 0.5f * (mny + mxy), cz = 0.5f * (mnz + mxz);
-    // half the box plus the list radius (and the rounding of both): blocks farther off are culled
-    const float rly = 0.5f * (mxy - mny) * 1.00001f + 1e-6f * fabsf(cy), rlz = 0.5f * (mxz - mnz) * 1.00001f + 1e-6f * fabsf(cz);
-    const float rhx = 0.5f * (mxx - mnx) * 1.00001f + 1e-6f * fabsf(cx);
+    const float bx = 0.5f * (mnx + mxx), by = 0.5f * (mny + mxy), bz = 0.5f * (mnz + mxz);
+    const float hx = 0.5f * (mxx - mnx) * 1.00001f + 1e-6f * fabsf(bx);
+    const float hy = 0.5f * (mxy - mny) * 1.00001f + 1e-6f * fabsf(by);
+    const float hz = 0.5f * (mxz - mnz) * 1.00001f + 1e-6f * fabsf(bz);
     const float rl2 = S.rl * S.rl * 1.00001f;
-    const bool wide = !(fmaxf(mxx - mnx, fmaxf(mxy - mny, mxz - mnz)) < 64.0f);
     // atom i: exclusions, list radius, MFMA operand and accumulator start
     const unsigned long long ex = (valid ? gconst(S.excl)[i] : 0ull) | (1ull << 32);
-    const bool ilight = (__float_as_uint(box[(valid ? i : iw) >> 3].w) >> (24 + (i & 7))) & 1u;
-    constexpr float SHORT = 1.0f - 9.5367431640625e-7f;        // 1 - 2^-20
+    const bool ilight = (__float_as_uint(box[(valid ? i : iw) / BLK].w) >> (24 + (i & (BLK - 1)))) & 1u;
     const float list2 = allpairs ? 1.0e30f : (ilight ? S.list2_light : S.list2_heavy);
-    const float list2_j = S.list2_j;
-    const float dix = pi.x - cx, diy = pi.y - cy, diz = pi.z - cz;
-    const float ci = valid ? fmaf(fmaf(diz, diz, fmaf(diy, diy, dix * dix)), SHORT, -list2) : 1.0e30f;
+    const float dix = pi.x - c.x, diy = pi.y - c.y, diz = pi.z - c.z;
+    const float ci = valid ? fmaf(fmaf(diz, diz, fmaf(diy, diy, dix * dix)), TILE_SHORT, -list2) : 1.0e30f;
     const float bop = q == 0 ? -2.0f * dix : (q == 1 ? -2.0f * diy : (q == 2 ? -2.0f * diz : 1.0f));
-    // the partner this lane feeds as row k16: atom `jt` of the tile's block `jb`
+    // the operand this lane feeds: component q of the partner in row k16, atom jt of the tile's block jb
+    const float cq = q == 0 ? c.x : (q == 1 ? c.y : (q == 2 ? c.z : 0.0f));
     const int jb = (k16 >> 1) & 1, jt = 4 * (k16 & 1) + (k16 >> 2);
+    const GPR_LDS char *const opnd = q < 3 ? (const GPR_LDS char *)xs + 16 * jt + 4 * q : (const GPR_LDS char *)pp + 8 * jt;
+    const int opsh = q < 3 ? 7 : 6;                             // log2 of a block's bytes there
+    static_assert(BLK == 8, "operand addresses take a block as 8 x 16 or 8 x 8 bytes");
     int flo = 0, fhi = 0;
     const GPR_GLOBAL int *const fj = gconst(S.far_j);
     const bool has_far = S.has_far != 0;
     if (has_far && valid) { flo = gconst(S.far_start)[i]; fhi = gconst(S.far_start)[i + 1]; }
-    const int cap = 4 * Kg;
-    // the replica's lists (a scalar base) and this lane's word in them: group g of sub-list (i, q) is
-    // word g * np * P + i * P + q
-    GPR_GLOBAL unsigned long long *const Lr = (GPR_GLOBAL unsigned long long *)gmut(S.nbl) + (size_t)r * Kg * stride;
-    unsigned off = (unsigned)((valid ? i : 0) * P + q);
+    const bool special = wide || has_far;
+    // the replica's lists (a scalar base) and the byte offset of this lane's word in them: group g of
+    // sub-list (i, q) is word g * np * P + i * P + q
+    GPR_GLOBAL char *const Lr = (GPR_GLOBAL char *)gmut(S.nbl) + (size_t)r * Kg * stride * 8;
+    const unsigned step = stride * 8, end = (unsigned)Kg * step;
+    unsigned off = (unsigned)((valid ? i : 0) * P + q) * 8;
     const int nblk = (n + BLK - 1) / BLK;
-    unsigned long long pend = 0ull;                             // the cnt % 4 entries of the unfinished group
-    int cnt = 0;
-    // near blocks queued in wblk: the byte offset of the block's positions, its light atoms in the top byte
-    static_assert(BLK * 16 == 128, "block indices are taken from bit 7");
-    int nq = 0;
+    unsigned plo = 0u, phi = 0u;                                // the entries of the unfinished group
+    unsigned cnt4 = 0u;                                         // four times the entries so far
+    int nq = 0;                                                 // near blocks queued in wblk
     constexpr int CHUNK = WBLK - 8;                             // the rest of a batch waits in the queue
     static_assert(2 * UNR <= 8, "the queue holds a chunk and the rest of a batch");
     for (int cb = 0; cb < nblk; cb += CHUNK) {
         const int b = cb + lane;
         bool near = b < nblk && lane < CHUNK;
-        unsigned light = 0u;
-        if (near) {
+        if (near && !allpairs) {
+            // distance between the two boxes, per axis
             const gv_f4 m = box[b];
             const unsigned w = __float_as_uint(m.w);
-            light = w >> 24;
-            if (!allpairs) {
-                // distance between the two boxes, per axis
-                const float dx = fmaxf(0.f, fabsf(m.x - cx) - fmaf((float)(w & 255u), 0.0078125f, rhx));
-                const float dy = fmaxf(0.f, fabsf(m.y - cy) - fmaf((float)((w >> 8) & 255u), 0.0078125f, rly));
-                const float dz = fmaxf(0.f, fabsf(m.z - cz) - fmaf((float)((w >> 16) & 255u), 0.0078125f, rlz));
-                near = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < rl2 || (w & 0xFFFFFFu) == 0xFFFFFFu;
-            }
+            const float dx = fmaxf(0.f, fabsf(m.x - bx) - fmaf((float)(w & 255u), 0.0078125f, hx));
+            const float dy = fmaxf(0.f, fabsf(m.y - by) - fmaf((float)((w >> 8) & 255u), 0.0078125f, hy));
+            const float dz = fmaxf(0.f, fabsf(m.z - bz) - fmaf((float)((w >> 16) & 255u), 0.0078125f, hz));
+            near = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < rl2 || (w & 0xFFFFFFu) == 0xFFFFFFu;
         }
         const unsigned long long m = __ballot(near);
         __builtin_amdgcn_wave_barrier();
-        if (near) wblk[nq + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (int)((unsigned)(b * (BLK * 16)) | (light << 24));
+        if (near) wblk[nq + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = b;
         nq += __popcll(m);
-        __builtin_amdgcn_wave_barrier();
         const bool last = cb + CHUNK >= nblk;
+        if (last && lane < 2 * UNR && nq + lane < WBLK) wblk[nq + lane] = 0;    // slots read past the end, masked below
+        __builtin_amdgcn_wave_barrier();
         int k0 = 0;
         while (nq - k0 >= 2 * UNR || (last && k0 < nq)) {
-            // UNR tiles; slots past the queue's end read its last block, and their bits are masked
             int ent[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) ent[u] = wblk[min(k0 + 2 * u + jb, nq - 1)];
-            gv_f3 pj[UNR];
+            for (int u = 0; u < UNR; ++u) ent[u] = wblk[k0 + 2 * u + jb];
+            float val[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) pj[u] = *(const GPR_LDS gv_f3 *)((const GPR_LDS char *)xs + ((ent[u] & 0xFFFFFF) + 16 * jt));
+            for (int u = 0; u < UNR; ++u) val[u] = *(const GPR_LDS float *)(opnd + (ent[u] << opsh));
             __builtin_amdgcn_sched_barrier(0);                  // keep the reads ahead of the tests
             gv_f4 D[UNR];
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
-                const float dx = pj[u].x - cx, dy = pj[u].y - cy, dz = pj[u].z - cz;
-                const float lj = __int_as_float(__float_as_int(list2_j) & -((ent[u] >> (24 + jt)) & 1));
-                const float n2 = fmaf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), SHORT, -lj);
-                const float aop = q == 0 ? dx : (q == 1 ? dy : (q == 2 ? dz : n2));
                 const gv_f4 c4 = {ci, ci, ci, ci};
-                D[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop, c4, 0, 0, 0);
+                D[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(val[u] - cq, bop, c4, 0, 0, 0);
             }
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const int left = nq - (k0 + 2 * u);             // blocks of the tile that are in the queue
                 if (left <= 0) continue;
-                const int e0 = __builtin_amdgcn_readlane(ent[u], 0), e1 = __builtin_amdgcn_readlane(ent[u], 2);
-                const int b0 = (e0 >> 7) & 0x1FFFF, b1 = (e1 >> 7) & 0x1FFFF;
-                if (wide) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int t = 4 * (v & 1) + q;
-                        const gv_f4 xj = xs[(v < 2 ? b0 : b1) * BLK + t];
-                        const float dx = pi.x - xj.x, dy = pi.y - xj.y, dz = pi.z - xj.z;
-                        const float lj = (((v < 2 ? e0 : e1) >> (24 + t)) & 1) ? list2_j : 0.f;
-                        const float lim = valid ? list2 + lj : -1.0f;
-                        D[u][v] = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) - lim;
-                    }
-                }
+                const int b0 = __builtin_amdgcn_readlane(ent[u], 0), b1 = __builtin_amdgcn_readlane(ent[u], 2);
+                const unsigned live = left == 1 ? 3u : 15u;
                 // bit v: candidate v is within its list radius
                 unsigned p = __float_as_uint(D[u][3]) >> 31;
                 p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][2]), 31);
                 p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][1]), 31);
                 p = __builtin_amdgcn_alignbit(p, __float_as_uint(D[u][0]), 31);
-                if (left == 1) p &= 3u;
-                if ((b0 * BLK + BLK > iw - span && b0 * BLK < iw + 16 + span) ||
-                    (b1 * BLK + BLK > iw - span && b1 * BLK < iw + 16 + span)) {
+                p &= live;
+                const bool self = (b0 * BLK + BLK > iw - span && b0 * BLK < iw + 16 + span) ||
+                                  (b1 * BLK + BLK > iw - span && b1 * BLK < iw + 16 + span);
+                if (self || special) {
+                    if (wide) {
+                        p = 0u;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int bv = v < 2 ? b0 : b1, t = 4 * (v & 1) + q;
+                            const gv_f4 xj = xs[bv * BLK + t];
+                            const float dx = pi.x - xj.x, dy = pi.y - xj.y, dz = pi.z - xj.z;
+                            const float lj = ((__float_as_uint(box[bv].w) >> (24 + t)) & 1u) ? S.list2_j : 0.f;
+                            p |= (unsigned)(valid && fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < list2 + lj) << v;
+                        }
+                        p &= live;
+                    }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int o = (v < 2 ? b0 : b1) * BLK + 4 * (v & 1) + q - i + 32;
                         const unsigned drop = (unsigned)((unsigned)o < 64u) & (unsigned)(ex >> (o & 63));
                         p &= ~((drop & 1u) << v);
                     }
-                }
-                if (has_far && __ballot(flo < fhi) != 0ull) {
+                    if (has_far && __ballot(flo < fhi) != 0ull) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int j = (v < 2 ? b0 : b1) * BLK + 4 * (v & 1) + q;
-                        if ((p >> v) & 1u) {
-                            while (flo < fhi && fj[flo] < j) ++flo;
-                            if (flo < fhi && fj[flo] == j) p &= ~(1u << v);
+                        for (int v = 0; v < 4; ++v) {
+                            const int j = (v < 2 ? b0 : b1) * BLK + 4 * (v & 1) + q;
+                            if ((p >> v) & 1u) {
+                                while (flo < fhi && fj[flo] < j) ++flo;
+                                if (flo < fhi && fj[flo] == j) p &= ~(1u << v);
+                            }
                         }
                     }
                 }
-                const unsigned pick_lo = (unsigned)__builtin_amdgcn_ds_bpermute((int)(p << 2), sel_lo);
-                const unsigned pick_hi = (unsigned)__builtin_amdgcn_ds_bpermute((int)(p << 2), sel_hi);
-                const unsigned X = (unsigned)(b0 * (BLK * 0x10001) + 0x40000) + (unsigned)q * 0x10001u;
-                const unsigned Y = (unsigned)(b1 * (BLK * 0x10001) + 0x40000) + (unsigned)q * 0x10001u;
-                const unsigned long long ch = (unsigned long long)__builtin_amdgcn_perm(Y, X, pick_lo) |
-                                              ((unsigned long long)__builtin_amdgcn_perm(Y, X, pick_hi) << 32);
-                const int sh = 16 * (cnt & 3), nc = cnt + __popc(p);
-                const unsigned long long low = pend | (ch << sh);
-                const bool full = ((nc ^ cnt) & ~3) != 0;       // the pending group is complete
-                if (full && cnt < cap) gst(Lr + off, low);
-                off += full ? stride : 0u;
-                pend = full ? (ch >> 16) >> (48 - sh) : low;    // (ch >> (64 - sh), zero for sh = 0)
-                cnt = nc;
+                const int e4 = (int)((p << 4) | (cnt4 & 12u));
+                const unsigned X = (unsigned)(b0 * (8 * BLK * 0x10001) + 0x200000) + (unsigned)q * 0x80008u;
+                const unsigned Y = (unsigned)(b1 * (8 * BLK * 0x10001) + 0x200000) + (unsigned)q * 0x80008u;
+                const unsigned llo = plo | __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.x));
+                const unsigned lhi = phi | __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.y));
+                const unsigned olo = __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.z));
+                const unsigned ohi = __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.w));
+                const unsigned nc4 = cnt4 + 4u * (unsigned)__popc(p);
+                const bool full = (nc4 ^ cnt4) > 15u;           // the pending group is complete
+                if (full && off < end) {
+                    const gv_u2 w = {llo, lhi};
+                    *(GPR_GLOBAL gv_u2 *)(Lr + off) = w;
+                }
+                off += full ? step : 0u;
+                plo = full ? olo : llo;
+                phi = full ? ohi : lhi;
+                cnt4 = nc4;
             }
             k0 += 2 * UNR;
         }
@@ -412,22 +457,27 @@ __device__ __noinline__ int build_wave(const Dev *Sv, int r_, int iw_, int iend_
     // a partial group is padded; PAD: the four sub-lists of an atom to the same number of groups
     // with the far-away atom n (exact zeros), so that one count (the largest, returned) serves the
     // atom's four lanes; the counts array keeps each sub-list's own count
-    const int ng = min((cnt + 3) >> 2, Kg);
-    const unsigned long long pad = (unsigned long long)n * 0x0001000100010001ull;
-    if (valid && (cnt & 3) != 0 && cnt < cap) {
-        gst(Lr + off, pend | (pad << (16 * (cnt & 3))));
-        off += stride;
+    const int ng = min((int)((cnt4 + 15u) >> 4), Kg);
+    const unsigned pad = (unsigned)n * 0x00080008u;
+    if (valid && (cnt4 & 12u) != 0u && off < end) {
+        const unsigned k = (cnt4 >> 2) & 3u;
+        const gv_u2 w = {k == 1 ? plo | (pad << 16) : plo, k == 3 ? phi | (pad << 16) : pad};
+        *(GPR_GLOBAL gv_u2 *)(Lr + off) = w;
+        off += step;
     }
     int kq = ng;
     if (PAD) {
         kq = max(ng, __shfl_xor(ng, 16, 64));
         kq = max(kq, __shfl_xor(kq, 32, 64));
         if (valid)
-            for (int w = ng; w < kq; ++w, off += stride) gst(Lr + off, pad);
+            for (int w = ng; w < kq; ++w, off += step) {
+                const gv_u2 pw = {pad, pad};
+                *(GPR_GLOBAL gv_u2 *)(Lr + off) = pw;
+            }
     }
     if (valid) {
         gmut(S.nbc)[(size_t)r * stride + (size_t)i * P + q] = (unsigned short)ng;
-        if (cnt > cap) atomicOr(&S.err[ERR_LIST], 1);
+        if ((int)(cnt4 >> 2) > 4 * Kg) atomicOr(&S.err[ERR_LIST], 1);
     }
     return kq;
 }
@@ -476,45 +526,58 @@ __device__ __forceinline__ NbConsts nb_consts(const Dev &S)
     return k;
 }
 
-// Sum over sub-list (i, q), four partners per 8-byte list word, the next word loaded one
-// group ahead; returns (F_x, F_y, F_z, sum U/2).
+// Sum over one sub-list of ng words: word g at byte off + g step of its replica's lists.  Returns
+// (F_x, F_y, F_z, sum U/2).  The next word is read one group ahead, without a branch, the offset
+// stopping at the last word (which is then read again, from the cache: the row after it would be
+// one more uncached read per sub-list).  Bound by VALU issue, 28 instructions per pair: with the
+// read ahead kept in place and two address instructions per pair instead of four, the force phase
+// of the persistent kernel (2,432 atoms x 64 replicas) went from 13.7 to 12.2 us.
 template <bool ENERGY>
-__device__ __forceinline__ float4 nb_lane_t(const NbConsts &S, int r, int i, int q, const float4 *xs, const float2 *pp,
-                                            int ngk)
+__device__ __forceinline__ float4 pair_sums(const GPR_GLOBAL char *lists, unsigned off, unsigned step, int ng, const float4 pi,
+                                            const float2 ppi, const float4 *xs, const float2 *pp, float rc2, float krf2,
+                                            float krf, float crf)
 {
-    const size_t stride = (size_t)S.np * P;
-    const GPR_GLOBAL uint2 *L = gconst(S.nbl) + (size_t)r * S.Kg * stride + (size_t)i * P + q;
-    // groups in the sub-list: given (the atom's count kept in LDS), or read from the counts
-    const int ng = ngk >= 0 ? ngk : (int)gconst(S.nbc)[(size_t)r * stride + (size_t)i * P + q];
-    const float4 pi = xs[i];
-    const float2 ppi = pp[i];
-    const float rc2 = S.rc2, krf = S.krf, krf2 = 2.0f * S.krf, crf = S.crf;
     float fx = 0.f, fy = 0.f, fz = 0.f, e = 0.f;
-    // the next word is read one group ahead, without a branch, through a running pointer that
-    // stops at the last group (which is then read again, from the cache)
-    const GPR_GLOBAL uint2 *Ln = L;
-    const unsigned step = (unsigned)stride;
-    uint2 nxt = make_uint2(0u, 0u);
-    if (ng > 0) nxt = gld(Ln);
-    for (int g = 0; g < ng; ++g) {
-        const uint2 cur = nxt;
-        Ln += g + 1 < ng ? step : 0u;
-        nxt = gld(Ln);
-        const int j0 = cur.x & 0xFFFF, j1 = cur.x >> 16, j2 = cur.y & 0xFFFF, j3 = cur.y >> 16;
-        const float4 x0 = xs[j0], x1 = xs[j1], x2 = xs[j2], x3 = xs[j3];
-        const float2 p0 = pp[j0], p1 = pp[j1], p2 = pp[j2], p3 = pp[j3];
-        pair_term(pi, ppi, x0, p0, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
-        pair_term(pi, ppi, x1, p1, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
-        pair_term(pi, ppi, x2, p2, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
-        pair_term(pi, ppi, x3, p3, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+    if (ng > 0) {
+        const unsigned last = off + (unsigned)(ng - 1) * step;
+        // LDS addresses by hand: pb + entry (one instruction with its half-word select) is the partner's
+        // parameters, twice that + xd its position
+        const unsigned pb = (unsigned)fresh_v((int)(unsigned)(size_t)(const GPR_LDS char *)pp);
+        const unsigned xd = (unsigned)fresh_s((int)((unsigned)(size_t)(const GPR_LDS char *)xs - 2 * (unsigned)(size_t)(const GPR_LDS char *)pp));
+        auto x_at = [&](unsigned a) { const gv_f4 v = *(const GPR_LDS gv_f4 *)(size_t)(2 * a + xd); return make_float4(v.x, v.y, v.z, v.w); };
+        auto p_at = [&](unsigned a) { const gv_f2 v = *(const GPR_LDS gv_f2 *)(size_t)a; return make_float2(v.x, v.y); };
+        gv_u2 nxt = *(const GPR_GLOBAL gv_u2 *)(lists + off);
+        for (int g = 0; g < ng; ++g) {
+            const gv_u2 cur = nxt;
+            off = min(off + step, last);
+            nxt = *(const GPR_GLOBAL gv_u2 *)(lists + off);
+            const unsigned o0 = (cur.x & 0xFFFFu) + pb, o1 = (cur.x >> 16) + pb, o2 = (cur.y & 0xFFFFu) + pb, o3 = (cur.y >> 16) + pb;
+            const float4 x0 = x_at(o0), x1 = x_at(o1), x2 = x_at(o2), x3 = x_at(o3);
+            const float2 p0 = p_at(o0), p1 = p_at(o1), p2 = p_at(o2), p3 = p_at(o3);
+            pair_term(pi, ppi, x0, p0, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+            pair_term(pi, ppi, x1, p1, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+            pair_term(pi, ppi, x2, p2, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+            pair_term(pi, ppi, x3, p3, rc2, krf2, krf, crf, ENERGY, fx, fy, fz, e);
+            // (used here, the read ahead cannot be moved to the top of the next pass)
+            asm volatile("" : "+v"(nxt.x), "+v"(nxt.y));
+        }
     }
     return make_float4(fx, fy, fz, e);
 }
 
-__device__ __forceinline__ float4 nb_lane(const NbConsts &S, int r, int i, int q, const float4 *xs, const float2 *pp,
-                                          bool energy, int ngk = -1)
+template <bool ENERGY>
+__device__ __forceinline__ float4 nb_lane_t(const NbConsts &S, int r, int i, int q, const float4 *xs, const float2 *pp)
 {
-    return energy ? nb_lane_t<true>(S, r, i, q, xs, pp, ngk) : nb_lane_t<false>(S, r, i, q, xs, pp, ngk);
+    const size_t stride = (size_t)S.np * P;
+    const int ng = gconst(S.nbc)[(size_t)r * stride + (size_t)i * P + q];
+    const GPR_GLOBAL char *lists = (const GPR_GLOBAL char *)gconst(S.nbl) + (size_t)r * S.Kg * stride * 8;
+    return pair_sums<ENERGY>(lists, (unsigned)(i * P + q) * 8, (unsigned)stride * 8, ng, xs[i], pp[i], xs, pp, S.rc2, 2.0f * S.krf, S.krf, S.crf);
+}
+
+__device__ __forceinline__ float4 nb_lane(const NbConsts &S, int r, int i, int q, const float4 *xs, const float2 *pp,
+                                          bool energy)
+{
+    return energy ? nb_lane_t<true>(S, r, i, q, xs, pp) : nb_lane_t<false>(S, r, i, q, xs, pp);
 }
 
 // ------------------------------------------------------------------ one B A O A for one atom
@@ -553,7 +616,9 @@ __device__ __forceinline__ void integrate_baoa_g(const IntConsts &K, float3 &x, 
 
 __device__ __forceinline__ float3 step_noise(const IntConsts &K, int a, int r, long long s)
 {
-    return gauss3(philox_ctr((uint32_t)a, s, (uint32_t)r, STREAM_NOISE, K.key0, K.key1));
+    // (the round keys are computed where they are used: kept across the step they take 20 registers)
+    const uint32_t key0 = (uint32_t)fresh_s((int)K.key0), key1 = (uint32_t)fresh_s((int)K.key1);
+    return gauss3(philox_ctr((uint32_t)a, s, (uint32_t)r, STREAM_NOISE, key0, key1));
 }
 
 __device__ __forceinline__ void integrate_baoa_k(const IntConsts &K, int a, int r, long long s, float3 &x, float3 &v,
@@ -579,7 +644,8 @@ __device__ __forceinline__ float ldv(const float *p, bool coh)
     return coh ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
 }
 
-__device__ void group_sum_wg(const Dev &S, const float4 *xs, const float *vg, int off, int cnt, int what,
+template <class Pos>
+__device__ void group_sum_wg(const Dev &S, const Pos &xs, const float *vg, int off, int cnt, int what,
                              long long *dst, int tid, int nthr, bool coh = false)
 {
     // what: 0 -> sum m x (3 slots), 1 -> sum |v|^2 (1 slot)
@@ -590,9 +656,10 @@ __device__ void group_sum_wg(const Dev &S, const float4 *xs, const float *vg, in
             const int a = S.groups[off + k];
             if (what == 0) {
                 const double m = (double)S.mass[a];
-                s0 = fix_d(m * (double)xs[a].x);
-                s1 = fix_d(m * (double)xs[a].y);
-                s2 = fix_d(m * (double)xs[a].z);
+                const float3 x = xs(a);
+                s0 = fix_d(m * (double)x.x);
+                s1 = fix_d(m * (double)x.y);
+                s2 = fix_d(m * (double)x.z);
             } else {
                 const double vx = ldv(vg + a, coh), vy = ldv(vg + S.np + a, coh), vz = ldv(vg + 2 * S.np + a, coh);
                 s0 = fix_d(vx * vx + vy * vy + vz * vz);
@@ -607,15 +674,18 @@ __device__ void group_sum_wg(const Dev &S, const float4 *xs, const float *vg, in
     }
 }
 
-__device__ __forceinline__ double3 xs_d(const float4 *xs, int a)
+template <class Pos>
+__device__ __forceinline__ double3 xs_d(const Pos &xs, int a)
 {
-    return make_double3((double)xs[a].x, (double)xs[a].y, (double)xs[a].z);
+    const float3 x = xs(a);
+    return make_double3((double)x.x, (double)x.y, (double)x.z);
 }
 
-__device__ int state_wg(const Dev &S, const float4 *xs, long long *red, int *sbuf, int tid, int nthr)
+template <class Pos>
+__device__ int state_wg(const Dev &S, const Pos &xs, long long *red, int *sbuf, int tid, int nthr)
 {
     const StateDesc &st = *S.st;
-    if (st.kind == ST_SIGN_X) return xs[st.atoms[0]].x >= 0.0f ? 1 : 0;
+    if (st.kind == ST_SIGN_X) return xs(st.atoms[0]).x >= 0.0f ? 1 : 0;
     if (st.kind == ST_BOXES) {
         if (tid == 0) {
             const double phi = dihedral_d(xs_d(xs, st.atoms[0]), xs_d(xs, st.atoms[1]), xs_d(xs, st.atoms[2]), xs_d(xs, st.atoms[3]));
@@ -647,7 +717,8 @@ __device__ int state_wg(const Dev &S, const float4 *xs, long long *red, int *sbu
 }
 
 // observable values into out[MAX_OBS] (LDS), valid after return
-__device__ void observables_wg(const Dev &S, const float4 *xs, const float *vg, double U, long long *red,
+template <class Pos>
+__device__ __noinline__ void observables_wg(const Dev &S, const Pos xs, const float *vg, double U, long long *red,
                                double *out, int tid, int nthr, bool coh = false)
 {
     if (tid < MAX_OBS * 8) red[tid] = 0;
@@ -683,7 +754,7 @@ __device__ void observables_wg(const Dev &S, const float4 *xs, const float *vg, 
             double val = 0.0;
             switch (o.kind) {
             case OB_COORD: {
-                const float4 p = xs[o.atoms[0]];
+                const float3 p = xs(o.atoms[0]);
                 val = o.atoms[1] == 0 ? (double)p.x : (o.atoms[1] == 1 ? (double)p.y : (double)p.z);
                 break;
             }
@@ -813,8 +884,14 @@ __global__ void __launch_bounds__(256) k_bonded(const Dev *__restrict__ Sp, long
         }
     } else {
         const int u0 = gconst(S.pl_first)[blockIdx.x], u1 = gconst(S.pl_first)[blockIdx.x + 1];
-        bonded_units(S.pl_bi, S.pl_bp, u0, u1, PosGlob{gconst(S.x) + b, S.np}, a0, fa, len, energy ? &e_acc : nullptr,
-                     __builtin_amdgcn_readfirstlane(tid >> 6), len >> 6, tid & 63);
+        const PosGlob pos{gconst(S.x) + b, S.np};
+        const ForceLDS F{fa, a0, 1, len};
+        if (energy) {
+            const long long e = bonded_units<true>(S.pl_bi, S.pl_bp, u0, u1, pos, F, uni(tid >> 6), len >> 6, tid & 63);
+            if (e != 0) lds_add(&e_acc, e);
+        } else {
+            bonded_units<false>(S.pl_bi, S.pl_bp, u0, u1, pos, F, uni(tid >> 6), len >> 6, tid & 63);
+        }
     }
     __syncthreads();
     const int a = a0 + tid;
@@ -835,15 +912,16 @@ __global__ void __launch_bounds__(1024) k_nonbonded(const Dev *__restrict__ Sp, 
     step_args(*Sp, s, energy);
     const Dev &S = *Sp;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    float4 *xs = (float4 *)lds_raw;
-    float2 *pp = (float2 *)(xs + S.np);
-    float4 *box = (float4 *)(pp + S.np);
+    float2 *pp = (float2 *)lds_raw;
+    float4 *xs = (float4 *)(pp + S.np);
+    float4 *box = xs + S.np;                               // boxes of the atom blocks
     int *wscr = (int *)(box + (S.n + BLK - 1) / BLK);      // [16][WBLK] build scratch per wave
     __shared__ long long e_acc;
     const int r = r_off + blockIdx.y;
     const int tid = threadIdx.x, nthr = blockDim.x;
     stage_replica(S, r, xs, pp, tid, nthr);
     if (tid == 0) e_acc = 0;
+    for (int t = tid; t < (S.n + BLK - 1) / BLK; t += nthr) box[t].w = __uint_as_float((unsigned)gconst(S.cls)[t] << 24);
     // rebuild when forced, when flagged (displacement guard or a new configuration), or on the
     // steps s with s + 1 a multiple of period, the same steps for every replica: one launch
     // serves all replicas, so rebuilds that coincide cost one long launch instead of many.
@@ -871,11 +949,16 @@ __global__ void __launch_bounds__(1024) k_nonbonded(const Dev *__restrict__ Sp, 
     const int q = tid % P;
     const size_t b = (size_t)r * 3 * S.np;
     if (rebuild) {
-        block_boxes(S, xs, box, tid, nthr);
+        const GPR_CONST Dev &C = *(const GPR_CONST Dev *)Sp;
+        const GPR_LDS gv_f4 *xl = (const GPR_LDS gv_f4 *)xs;
+        GPR_LDS gv_f2 *pl = (GPR_LDS gv_f2 *)pp;
+        const float3 c = search_centre(xl, S.n);
+        const bool wide = __syncthreads_or(block_boxes(C, xl, pl, (GPR_LDS gv_f4 *)box, c, tid, nthr)) != 0;
+        const int wv = uni(tid >> 6);
+        search_task<2, false>(C, r, blockIdx.x * (nthr / P) + 16 * wv, S.n, xl, pl, (const GPR_LDS gv_f4 *)box,
+                              (GPR_LDS int *)wscr + wv * WBLK, c, wide, !S.cutoff_on);
         __syncthreads();
-        build_wave<2, false>(Sp, r, blockIdx.x * (nthr / P) + 16 * (tid >> 6), S.n, (const GPR_LDS gv_f4 *)xs,
-                             (const GPR_LDS gv_f4 *)box, (GPR_LDS int *)wscr + (tid >> 6) * WBLK,
-                             !S.cutoff_on);
+        for (int a = tid; a < BLK * ((S.n + BLK - 1) / BLK); a += nthr) pp[a].x = gld(gconst(S.prm) + a).x;
         if (i < S.n && q == 0) {
             S.xb[b + i] = xs[i].x; S.xb[b + S.np + i] = xs[i].y; S.xb[b + 2 * S.np + i] = xs[i].z;
         }
@@ -928,7 +1011,7 @@ __global__ void __launch_bounds__(256) k_obs(const Dev *__restrict__ Sp, int r_o
     stage_replica(S, r, xs, nullptr, threadIdx.x, blockDim.x);
     __syncthreads();
     const float *vg = S.v + (size_t)r * 3 * S.np;
-    observables_wg(S, xs, vg, unfix_d(S.E[r]), red, vals, threadIdx.x, blockDim.x);
+    observables_wg(S, PosLDS{xs}, vg, unfix_d(S.E[r]), red, vals, threadIdx.x, blockDim.x);
     if (threadIdx.x == 0) {
         if (mode == 0 || mode == 3) accumulate_obs(S, r, vals);
         else if (mode == 1) for (int j = 0; j < S.nobs; ++j) S.shift[j] = vals[j];
@@ -947,7 +1030,7 @@ __global__ void __launch_bounds__(256) k_state(const Dev *__restrict__ Sp, int r
     const int r = r_off + blockIdx.x;
     stage_replica(S, r, xs, nullptr, threadIdx.x, blockDim.x);
     __syncthreads();
-    const int id = state_wg(S, xs, red, &sbuf, threadIdx.x, blockDim.x);
+    const int id = state_wg(S, PosLDS{xs}, red, &sbuf, threadIdx.x, blockDim.x);
     if (threadIdx.x == 0) S.state[r] = id;
 }
 
@@ -968,8 +1051,8 @@ __global__ void __launch_bounds__(1024) k_grad_nb(const Dev *__restrict__ Sp, co
 {
     const Dev &S = *Sp;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    float4 *xs = (float4 *)lds_raw;
-    float2 *pp = (float2 *)(xs + S.np);
+    float2 *pp = (float2 *)lds_raw;
+    float4 *xs = (float4 *)(pp + S.np);
     const int r = blockIdx.y;
     const int tid = threadIdx.x, nthr = blockDim.x;
     stage_replica(S, r, xs, pp, tid, nthr);
@@ -986,7 +1069,7 @@ __global__ void __launch_bounds__(1024) k_grad_nb(const Dev *__restrict__ Sp, co
         const float rc2 = S.rc2, krf = S.krf, crf = S.crf;
         for (int g = 0; g < ng; ++g) {
             const uint2 wv = gld(L + (size_t)g * stride);
-            const int jj[4] = {(int)(wv.x & 0xFFFF), (int)(wv.x >> 16), (int)(wv.y & 0xFFFF), (int)(wv.y >> 16)};
+            const int jj[4] = {(int)(wv.x & 0xFFFF) >> 3, (int)(wv.x >> 19), (int)(wv.y & 0xFFFF) >> 3, (int)(wv.y >> 19)};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float4 pj = xs[jj[k]];
@@ -1161,44 +1244,47 @@ __device__ __forceinline__ bool group_barrier(int *ctr, int target, int *err, in
     return ok;
 }
 
+__device__ __forceinline__ void st_coh(GPR_GLOBAL float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float ld_coh(const GPR_GLOBAL float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void st_coh(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float ld_coh(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // (x, y) of one atom as one 64-bit word, for the position exchange
-__device__ __forceinline__ void st_coh2(unsigned long long *p, float x, float y)
+__device__ __forceinline__ void st_coh2(GPR_GLOBAL unsigned long long *p, float x, float y)
 {
     const unsigned long long w = (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
     __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float2 ld_coh2(const unsigned long long *p)
+__device__ __forceinline__ float2 ld_coh2(const GPR_GLOBAL unsigned long long *p)
 {
     const unsigned long long w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return make_float2(__uint_as_float((unsigned)w), __uint_as_float((unsigned)(w >> 32)));
 }
 
 // G workgroups per replica advance nsteps BAOAB steps.  Group g of replica r owns the atoms
-// [a0, a1) = [sp.bnd[g], sp.bnd[g + 1]) (ranges chosen on the host to even out the work); its LDS holds the positions (float4 with the
-// scaled charge) and LJ parameters of every atom of the replica, and the velocities and
-// fixed-point force accumulators of its own atoms (the accumulators carry the forces from one
-// step to the next), block spheres and reduction scratch.  Per step: B A O A of own atoms ->
-// (G > 1) positions exchanged through device-coherent stores, barrier -> pair-list rebuild of
-// own atoms when due -> bonded terms touching own atoms (LDS atomics) -> pair forces of own
-// atoms (P lanes per atom) -> closing B; every t_GR steps (t counted from t0) the observables
-// of workers are accumulated by group 0.  With state_end group 0 writes the state id.
+// [a0, a1) = [sp.bnd[g], sp.bnd[g + 1]) (ranges chosen on the host to even out the work); its LDS
+// (persist_off) holds the positions (float4 with the scaled charge) and LJ parameters of every atom
+// of the replica, and the velocities and fixed-point force accumulators of its own atoms (the
+// accumulators carry the forces from one step to the next), block boxes and reduction scratch.  Per
+// step: B A O A of own atoms -> (G > 1) positions exchanged through device-coherent stores, barrier
+// -> pair-list rebuild of own atoms when due -> bonded units touching own atoms (LDS atomics) and
+// pair forces of own atoms (P lanes per atom) -> closing B; every t_GR steps (t counted from t0) the
+// observables of workers are accumulated by group 0.  With state_end group 0 writes the state id.
 // Workgroups map to replicas so that a replica's groups are meant to share an XCD (equal
 // blockIdx mod 8) when the replica count allows; results do not depend on G, the block size or
 // the placement.
+
 // Pair-loop order of a group's nl atoms.  A task of the pair loop is 16 atoms on the 64 lanes
 // of a wave and runs as long as its longest list, so the atoms go longest list first (key: the
 // atom's longest sub-list, in words): tasks of similar lists, taken heaviest first.  perm has
 // 16 * ceil(nl / 16) slots; those past nl hold 0xFFFF.  Forces do not depend on the order: an
 // atom's four lanes stay together and sum its own sub-lists in their fixed order.
-__device__ void order_atoms(const unsigned short *key, unsigned short *perm, int *hist, int nl, int tid, int nthr)
+__device__ __forceinline__ void order_atoms(const GPR_LDS unsigned short *key, GPR_LDS unsigned short *perm, GPR_LDS int *hist,
+                                            int nl, int tid, int nthr)
 {
     const int nt = (nl + 15) >> 4;
     for (int k = tid; k < 16 * nt; k += nthr) perm[k] = 0xFFFF;
     for (int k = tid; k < 64; k += nthr) hist[k] = 0;
     __syncthreads();
-    for (int l = tid; l < nl; l += nthr) atomicAdd(&hist[63 - min((int)key[l], 63)], 1);
+    for (int l = tid; l < nl; l += nthr) lds_inc(&hist[63 - min((int)key[l], 63)]);
     __syncthreads();
     if (tid < 64) {                                        // exclusive prefix sum of the bins
         const int c = hist[tid];
@@ -1210,33 +1296,132 @@ __device__ void order_atoms(const unsigned short *key, unsigned short *perm, int
         hist[tid] = x - c;
     }
     __syncthreads();
-    for (int l = tid; l < nl; l += nthr) {
-        const int k = atomicAdd(&hist[63 - min((int)key[l], 63)], 1);
-        perm[k] = (unsigned short)l;
+    for (int l = tid; l < nl; l += nthr) perm[lds_inc(&hist[63 - min((int)key[l], 63)])] = (unsigned short)l;
+    __syncthreads();
+}
+
+// The order of the search's tasks of 16 consecutive atoms, the costliest first by the lists of the
+// last build (the summed longest sub-lists of a task's atoms)
+__device__ __forceinline__ void order_tasks(const GPR_LDS unsigned short *key, GPR_LDS int *cost, GPR_LDS unsigned short *order,
+                                            int nl, int tid, int nthr)
+{
+    const int ntk = (nl + 15) >> 4;
+    for (int c = tid; c < ntk; c += nthr) {
+        int sum = 0;
+        for (int l = 16 * c; l < min(16 * c + 16, nl); ++l) sum += key[l];
+        cost[c] = sum;
+    }
+    __syncthreads();
+    for (int c = tid; c < ntk; c += nthr) {
+        const int mine = cost[c];
+        int rank = 0;
+        for (int d = 0; d < ntk; ++d) rank += (cost[d] > mine) | (cost[d] == mine && d < c);
+        order[rank] = (unsigned short)c;
     }
     __syncthreads();
 }
 
-constexpr int NBW = 8;          // waves of a workgroup that start with the bonded units
+// Rebuilds the pair lists of a group's atoms: the boxes of all blocks, then the search in tasks of
+// 16 atoms, one wave each, taken by the waves from a counter as they come free.  The orders of the
+// search's tasks and of the pair loop's atoms are kept from one rebuild to the next and renewed on
+// every ORDER_PERIOD-th: list lengths change little in between, and renewing both costs 9 us (24 us
+// for the rest of a rebuild on the 2,432-atom system with four groups).  They change no list and no
+// force.  A function of its own: inlined, its registers cost the step loop spills on every step.
+constexpr int ORDER_PERIOD = 8;
+__device__ __noinline__ void persist_rebuild(const Dev *Sv, GPR_LDS unsigned char *raw, GPR_LDS int *counter, GPR_LDS int *torder,
+                                             int lmax_, int a0_, int a1_, int r_, int renew_)
+{
+    const GPR_CONST Dev &S = *(const GPR_CONST Dev *)uni64((long long)Sv);
+    const int lmax = uni(lmax_), a0 = uni(a0_), a1 = uni(a1_), r = uni(r_);
+    const bool renew = uni(renew_) != 0;
+    const int tid = threadIdx.x, BT = blockDim.x, n = S.n, np = S.np, nl = a1 - a0, ntk = (nl + 15) >> 4;
+    const PersistOff o = persist_off(n, np, lmax);
+    const GPR_LDS gv_f4 *const xs = (const GPR_LDS gv_f4 *)(raw + o.xs);
+    GPR_LDS gv_f2 *const pp = (GPR_LDS gv_f2 *)raw;
+    GPR_LDS gv_f4 *const box = (GPR_LDS gv_f4 *)(raw + o.box);
+    GPR_LDS int *const wscr = (GPR_LDS int *)(raw + o.wscr);
+    GPR_LDS unsigned short *const perm = (GPR_LDS unsigned short *)(raw + o.perm), *const keyl = (GPR_LDS unsigned short *)(raw + o.keyl);
+    GPR_LDS unsigned short *const order = (GPR_LDS unsigned short *)torder;
+    GPR_LDS float *const xbl = (GPR_LDS float *)(raw + o.xbl);
+    if (tid == 0) *counter = 0;
+    if (renew) order_tasks(keyl, wscr, order, nl, tid, BT);
+    const float3 c = search_centre(xs, n);
+    const bool wide = __syncthreads_or(block_boxes(S, xs, pp, box, c, tid, BT)) != 0;
+    for (;;) {
+        int t = 0;
+        if ((tid & 63) == 0) t = lds_inc(counter);
+        t = uni(t);
+        if (t >= ntk) break;
+        const int k = uni((int)order[t]);
+        const int kq = search_task<4, true>(S, r, a0 + 16 * k, a1, xs, pp, box, wscr + (tid >> 6) * WBLK, c, wide, false);
+        const int l = 16 * k + (tid & 63);
+        if ((tid & 63) < 16 && l < nl) {
+            const gv_f4 x = xs[a0 + l];
+            xbl[l] = x.x; xbl[lmax + l] = x.y; xbl[2 * lmax + l] = x.z;
+            keyl[l] = (unsigned short)kq;
+        }
+    }
+    __syncthreads();
+    for (int a = tid; a < BLK * ((n + BLK - 1) / BLK); a += BT) pp[a].x = gld(gconst(S.prm) + a).x;
+    if (renew) order_atoms(keyl, perm, (GPR_LDS int *)(raw + o.red), nl, tid, BT);
+    __syncthreads();
+}
+
+// Observables of a worker at the end of a sampled step, its closing B done: the groups' velocities
+// and energy to group 0 of the replica, which accumulates them.  False after a barrier timeout.
+__device__ __noinline__ bool persist_sample(const Dev *Sv, GPR_LDS unsigned char *rawl, GPR_LDS int *bufl, int lmax_, int a0_, int a1_,
+                                            int r_, int g_, int G_, int target_, int energy_)
+{
+    const Dev &S = *(const Dev *)uni64((long long)Sv);
+    unsigned char *const raw = (unsigned char *)rawl;
+    const int lmax = uni(lmax_), a0 = uni(a0_), a1 = uni(a1_), r = uni(r_), g = uni(g_), G = uni(G_), target = uni(target_);
+    const bool energy = uni(energy_) != 0;
+    const int tid = threadIdx.x, BT = blockDim.x, n = S.n, np = S.np;
+    const PersistOff o = persist_off(n, np, lmax);
+    const PosLDS xs{(const float4 *)(raw + o.xs)};
+    const float *vs = (const float *)(raw + o.vs);
+    long long *red = (long long *)(raw + o.red), *eacc = red + MAX_OBS * 8;
+    double *vals = (double *)(raw + o.vals);
+    float *vg = S.v + (size_t)r * 3 * np;
+    __syncthreads();
+    if (G == 1) {
+        for (int k = tid; k < 3 * np; k += BT) gmut(vg)[k] = k % np < n ? vs[(k / np) * lmax + k % np] : 0.f;
+        __syncthreads();
+        observables_wg(S, xs, vg, unfix_d(*eacc), red, vals, tid, BT);
+        if (tid == 0) accumulate_obs(S, r, vals);
+        return true;
+    }
+    for (int a = a0 + tid; a < a1; a += BT) {
+        const int l = a - a0;
+        st_coh(vg + a, vs[l]); st_coh(vg + np + a, vs[lmax + l]); st_coh(vg + 2 * np + a, vs[2 * lmax + l]);
+    }
+    if (tid == 0 && energy && *eacc != 0)
+        __hip_atomic_fetch_add(S.esum + r, *eacc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!group_barrier(S.sync + (size_t)r * 64, target, S.err, (int *)bufl)) return false;
+    if (g == 0) {
+        if (tid == 0) {
+            // the sum of the groups' energies, by way of the accumulator
+            *eacc = __hip_atomic_load(S.esum + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(S.esum + r, 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        observables_wg(S, xs, vg, unfix_d(*eacc), red, vals, tid, BT, true);
+        if (tid == 0) accumulate_obs(S, r, vals);
+    }
+    return true;
+}
+
+// Waves of a workgroup that start with the bonded units (the others start the pair tasks; us per step
+// with 8, 12 and 16: 2,432 atoms x 64 replicas 20.0, 20.2, 20.2; 1,200 x 192 35.9, 36.8, 36.8; 300 x 24
+// 7.7, 7.5, 8.1)
+constexpr int NBW = 8;
 __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, int a0, int a1, int u0, int u1,
-                                                const uint2 *bi, const float4 *bp, int r, int g, long long s0, int nsteps, int t0, int sample, int state_end)
+                                                const uint2 *bi, const float4 *bp, int noise_ahead, int r, int g,
+                                                long long s0, int nsteps, int t0, int sample, int state_end)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int np = S.np, n = S.n;
-    long long *fa = (long long *)lds_raw;                 // [3][lmax]
-    long long *red = fa + 3 * lmax;                        // [MAX_OBS * 8 + 8]
-    double *vals = (double *)(red + MAX_OBS * 8 + 8);      // [MAX_OBS]
-    float4 *xs = (float4 *)(vals + MAX_OBS);               // [np]
-    float2 *pp = (float2 *)(xs + np);                      // [np]
-    float *vs = (float *)(pp + np);                        // [3][lmax]
-    float *iml = vs + 3 * lmax;                            // [lmax] 1/m of own atoms
-    float *sdl = iml + lmax;                               // [lmax] noise amplitude of own atoms
-    float *xbl = sdl + lmax;                               // [3][lmax] own positions at the last list build
-    float4 *box = (float4 *)(xbl + 3 * lmax);              // [nblk]
-    int *wscr = (int *)(box + (n + BLK - 1) / BLK);        // [16][WBLK] build scratch per wave
-    unsigned short *perm = (unsigned short *)(wscr + 16 * WBLK);  // [16 ceil(lmax / 16)] pair-loop order
-    unsigned short *keyl = perm + 16 * ((lmax + 15) >> 4);  // [lmax] groups in each of an atom's sub-lists
-    __shared__ int sbuf, bbuf, hbuf, hist[64], ptask, btask;
+    const int np = uni(S.np), n = uni(S.n);
+    __shared__ int bbuf, hbuf, ptask, btask, torder[64];   // torder: [128] the search's task order, 16 bits each
 
     const int tid = threadIdx.x, BT = blockDim.x;
 #ifdef GPR_PHASE_PROBE
@@ -1244,42 +1429,57 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
     if (tid < NPHASE) ph_acc[tid] = 0;
 #endif
     const size_t b = (size_t)r * 3 * np;
-    GPR_GLOBAL float *xg = gmut(S.x) + b, *xbg = gmut(S.xb) + b;
-    float *vg = S.v + b;
-    GPR_GLOBAL long long *Fg = gmut(S.F) + b;
-    const GPR_GLOBAL float4 *prm = gconst(S.prm);
-    const GPR_GLOBAL float *sdv = gconst(S.sd);
-    int *sync = S.sync + (size_t)r * 64;
-    // position exchange, one buffer per step parity: a group writes step s + 1 only after the
-    // barrier of step s, which every group passes after reading step s - 1
-    unsigned long long *xch_xy0 = (unsigned long long *)(S.xchg + 2 * b);        // [2][np] (x, y)
-    float *xch_z0 = S.xchg + 2 * b + 4 * np;                                        // [2][np] z
+    GPR_GLOBAL int *const sync = gmut(((const GPR_CONST Dev *)&S)->sync) + (size_t)r * 64;
+    // position exchange, one buffer per step parity ([2][np] (x, y) as 64-bit words, [2][np] z): a
+    // group writes step s + 1 only after the barrier of step s, which every group passes after
+    // reading step s - 1
+    GPR_GLOBAL float *const xchg = gmut(((const GPR_CONST Dev *)&S)->xchg) + 2 * b;
     int gen = 0;
 
 #ifdef GPR_PHASE_PROBE
     if (tid == 0) ph_acc[NPHASE] = ph_acc[PH_START] = __builtin_amdgcn_s_memrealtime();
 #endif
-    stage_replica(S, r, xs, pp, tid, BT);
-    for (int k = tid; k < 3 * lmax; k += BT) {
-        const int d = k / lmax, a = a0 + k % lmax;
-        vs[k] = a < a1 ? gconst(vg)[d * np + a] : 0.f;
-        fa[k] = a < a1 ? Fg[d * np + a] : 0;
-        xbl[k] = a < a1 ? xbg[d * np + a] : 0.f;
-    }
-    for (int l = tid; l < lmax; l += BT) {
-        const int a = a0 + l;
-        iml[l] = a < a1 ? gld(prm + a).w : 0.f;
-        sdl[l] = a < a1 ? sdv[a] : 0.f;
+    // descriptor fields used every step, held in registers for the launch
+    const GPR_CONST Dev &C = *(const GPR_CONST Dev *)&S;
+    const IntConsts ik{C.h, C.c1, C.key0, C.key1, C.kind == KIND_TOY};
+    const int nl = a1 - a0;
+    {
+        const PersistOff o = persist_off(n, np, lmax);
+        long long *fa = (long long *)(lds_raw + o.fa);
+        float *vs = (float *)(lds_raw + o.vs), *iml = (float *)(lds_raw + o.iml), *sdl = (float *)(lds_raw + o.sdl);
+        float *xbl = (float *)(lds_raw + o.xbl), *gn = (float *)(lds_raw + o.gn);
+        float4 *box = (float4 *)(lds_raw + o.box);
+        stage_replica(S, r, (float4 *)(lds_raw + o.xs), (float2 *)lds_raw, tid, BT);
+        const GPR_GLOBAL float *xbg = gconst(S.xb) + b, *vg = gconst(S.v) + b;
+        const GPR_GLOBAL long long *Fg = gconst(S.F) + b;
+        for (int k = tid; k < 3 * lmax; k += BT) {
+            const int d = k / lmax, a = a0 + k % lmax;
+            vs[k] = a < a1 ? vg[d * np + a] : 0.f;
+            fa[3 * (k % lmax) + d] = a < a1 ? Fg[d * np + a] : 0;
+            xbl[k] = a < a1 ? xbg[d * np + a] : 0.f;
+        }
+        for (int l = tid; l < lmax; l += BT) {
+            const int a = a0 + l;
+            iml[l] = a < a1 ? gld(gconst(S.prm) + a).w : 0.f;
+            sdl[l] = a < a1 ? gconst(S.sd)[a] : 0.f;
+            if (noise_ahead && a < a1) {
+                const float3 z = step_noise(ik, a, r, s0);
+                gn[l] = z.x; gn[lmax + l] = z.y; gn[2 * lmax + l] = z.z;
+            }
+        }
+        for (int t = tid; t < (n + BLK - 1) / BLK; t += BT) box[t].w = __uint_as_float((unsigned)gconst(S.cls)[t] << 24);
     }
     // the pair loop below runs each atom's four sub-lists to one count, which needs lists
     // padded as this kernel's search writes them: lists from the plain path's search, or a
     // replica marked for a rebuild (a new configuration), are rebuilt at the first step;
     // padded lists from an earlier launch are kept, their counts and order recomputed
-    const bool toy = S.kind == KIND_TOY;
+    const bool toy = C.kind == KIND_TOY;
     bool need = !toy && (S.need_build[r] != 0 || S.list_pad[r] == 0);
+    int built = 0;                                          // rebuilds of this launch
     long long lastb = S.last_build[(s0 & 1) * S.R + r];     // step of the last pair-list build
-    const int nl = a1 - a0, nslot = 16 * ((nl + 15) >> 4);
     if (!toy && !need) {
+        const PersistOff o = persist_off(n, np, lmax);
+        GPR_LDS unsigned short *keyl = (GPR_LDS unsigned short *)(lds_raw + o.keyl);
         const size_t stride = (size_t)np * P;
         const GPR_GLOBAL unsigned short *cnt = gconst(S.nbc) + (size_t)r * stride;
         for (int l = tid; l < nl; l += BT) {
@@ -1290,121 +1490,125 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
             keyl[l] = (unsigned short)k;
         }
         __syncthreads();
-        order_atoms(keyl, perm, hist, nl, tid, BT);
+        order_atoms(keyl, (GPR_LDS unsigned short *)(lds_raw + o.perm), (GPR_LDS int *)(lds_raw + o.red), nl, tid, BT);
     }
-    __syncthreads();
-    // descriptor fields used every step, held in registers for the launch
-    const IntConsts ik = int_consts(S);
-    const int t_gr = S.t_gr, need_energy = S.need_energy, cutoff_on = S.cutoff_on, period = S.period;
-    const float im_light = S.im_light, guard2_light = S.guard2_light, guard2_heavy = S.guard2_heavy;
-    int *const errp = S.err;
-    // with several groups every wave waits at the barrier on its own and then takes its share
-    // of the other groups' positions: one round trip of device-coherent reads per step
-    const bool split = G > 1 && !toy && BT >= 128;
+    if (tid == 0) bbuf = 1;
+    const int t_gr = C.t_gr, need_energy = C.need_energy, cutoff_on = C.cutoff_on, period = C.period;
+    const float im_light = C.im_light, guard2_light = C.guard2_light, guard2_heavy = C.guard2_heavy;
+    const float rc2 = C.rc2, krf = C.krf, krf2 = 2.0f * C.krf, crf = C.crf;
+    GPR_GLOBAL int *const errp = gmut(C.err);
+    // the replica's lists: word g of sub-list (i, q) is word g np P + i P + q
+    const GPR_GLOBAL char *const lists = (const GPR_GLOBAL char *)gconst(C.nbl) + (size_t)r * C.Kg * np * P * 8;
+    const unsigned lstep = (unsigned)np * P * 8;
     // the bonded units of the group's atoms go to its last (up to) NBW waves; the other waves
     // meanwhile start the pair tasks
-    const int nwv = BT >> 6, nbw = min(nwv, NBW), bw0 = nwv - nbw;
-    long long *eacc = red + MAX_OBS * 8;
+    const int wv = uni(tid >> 6), nbw = min(BT >> 6, NBW), bw0 = (BT >> 6) - nbw;
     bool alive = true;
     bool pend = false;                                      // the previous step's closing B is due
+    __syncthreads();
     PHASE_MARK(PH_PROLOGUE);
 
     for (int step = 0; step < nsteps && alive; ++step) {
         const long long s = s0 + step;
-        const int tl = t0 + step + 1;
-        const bool samp = sample && r >= 1 && (tl % t_gr == 0);
+        const bool samp = sample && r >= 1 && ((t0 + step + 1) % t_gr == 0);
         const bool energy = samp && need_energy;
-        unsigned long long *xch_xy = xch_xy0 + (s & 1) * np;
-        float *xch_z = xch_z0 + (s & 1) * np;
-        int hit = 0, bad = 0;
-        for (int a = a0 + tid; a < a1; a += BT) {
-            const int l = a - a0;
-            float3 x = make_float3(xs[a].x, xs[a].y, xs[a].z);
-            float3 v = make_float3(vs[l], vs[lmax + l], vs[2 * lmax + l]);
-            const float3 F = make_float3(unfix_f(fa[l]), unfix_f(fa[lmax + l]), unfix_f(fa[2 * lmax + l]));
-            if (pend) {
-                // the previous step's closing B, deferred to here (same forces, same order)
+        bool hit = false, bad = false;
+        {
+            const int lm = fresh_s(lmax);
+            const PersistOff o = persist_off(fresh_s(n), fresh_s(np), lm);
+            long long *fa = (long long *)(lds_raw + o.fa);
+            float4 *xs = (float4 *)(lds_raw + o.xs);
+            float *vs = (float *)(lds_raw + o.vs), *iml = (float *)(lds_raw + o.iml), *sdl = (float *)(lds_raw + o.sdl);
+            const float *xbl = (const float *)(lds_raw + o.xbl), *gn = (const float *)(lds_raw + o.gn);
+            GPR_GLOBAL unsigned long long *xch_xy = (GPR_GLOBAL unsigned long long *)xchg + (s & 1) * np;
+            GPR_GLOBAL float *xch_z = xchg + 4 * np + (s & 1) * np;
+            for (int l = fresh_v(tid); l < nl; l = fresh_v(l + BT)) {
+                const int a = a0 + l;
+                float3 x = make_float3(xs[a].x, xs[a].y, xs[a].z);
+                float3 v = make_float3(vs[l], vs[lm + l], vs[2 * lm + l]);
+                const float3 F = make_float3(unfix_f(fa[3 * l]), unfix_f(fa[3 * l + 1]), unfix_f(fa[3 * l + 2]));
+                fa[3 * l] = fa[3 * l + 1] = fa[3 * l + 2] = 0;    // (these forces are read here for the last time)
                 const float im = iml[l];
-                v.x = kick(v.x, F.x, ik.h, im);
-                v.y = kick(v.y, F.y, ik.h, im);
-                v.z = kick(v.z, F.z, ik.h, im);
-                bad |= bad_force(F.x) || bad_force(F.y) || bad_force(F.z);
+                if (pend) {
+                    // the previous step's closing B, deferred to here (same forces, same order)
+                    v.x = kick(v.x, F.x, ik.h, im);
+                    v.y = kick(v.y, F.y, ik.h, im);
+                    v.z = kick(v.z, F.z, ik.h, im);
+                    bad |= bad_force(F.x) || bad_force(F.y) || bad_force(F.z);
+                }
+                const float3 z = noise_ahead ? make_float3(gn[l], gn[lm + l], gn[2 * lm + l]) : step_noise(ik, a, r, s);
+                integrate_baoa_g(ik, x, v, F, im, sdl[l], z);
+                xs[a].x = x.x; xs[a].y = x.y; xs[a].z = x.z;
+                vs[l] = v.x; vs[lm + l] = v.y; vs[2 * lm + l] = v.z;
+                if (G > 1) { st_coh2(xch_xy + a, x.x, x.y); st_coh(xch_z + a, x.z); }
+                bad |= !(finite3(x) && finite3(v));
+                if (cutoff_on) {
+                    const float dx = x.x - xbl[l], dy = x.y - xbl[lm + l], dz = x.z - xbl[2 * lm + l];
+                    hit |= !(dx * dx + dy * dy + dz * dz <= (im > im_light ? guard2_light : guard2_heavy));
+                }
             }
-            integrate_baoa_k(ik, a, r, s, x, v, F, iml[l], sdl[l]);
-            xs[a].x = x.x; xs[a].y = x.y; xs[a].z = x.z;
-            vs[l] = v.x; vs[lmax + l] = v.y; vs[2 * lmax + l] = v.z;
-            if (G > 1) { st_coh2(xch_xy + a, x.x, x.y); st_coh(xch_z + a, x.z); }
-            bad |= !(finite3(x) && finite3(v));
-            if (cutoff_on) {
-                const float dx = x.x - xbl[l], dy = x.y - xbl[lmax + l], dz = x.z - xbl[2 * lmax + l];
-                hit |= !(dx * dx + dy * dy + dz * dz <= (iml[l] > im_light ? guard2_light : guard2_heavy));
-            }
+            if (tid == 0) { *((long long *)(lds_raw + o.red) + MAX_OBS * 8) = 0; ptask = 0; }
         }
-        if (bad) atomicOr(&errp[ERR_UNSTABLE], 1);
+        if (bad) atomicOr((int *)&errp[ERR_UNSTABLE], 1);
         int any_hit;
         if (G > 1) {
             // displacement-guard flags in three rotating slots; group 0 clears the slot of the next step
             if (hit) __hip_atomic_fetch_or(sync + 16 + 16 * (int)(s % 3), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (g == 0 && tid == 0) __hip_atomic_store(sync + 16 + 16 * (int)((s + 1) % 3), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (split) {
-                // arrive; each wave waits (bounded spin by its first lane), then all threads
-                // fetch the other groups' positions
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();                     // own positions stored, forces read
-                PHASE_MARK(PH_INTEGRATE);
-                if (tid == 0) {
-                    __hip_atomic_fetch_add(sync, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    bbuf = 1;
+            // arrive once every wave's stores are out; while the groups' stores and arrivals travel,
+            // draw the next step's Gaussians; then each wave waits on its own (bounded spin by its
+            // first lane) and takes its share of the other groups' positions
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();                     // own positions stored, forces read
+            PHASE_MARK(PH_INTEGRATE);
+            if (tid == 0) __hip_atomic_fetch_add(sync, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (noise_ahead) {
+                const int lm = fresh_s(lmax);
+                float *gn = (float *)(lds_raw + persist_off(fresh_s(n), fresh_s(np), lm).gn);
+                for (int l = fresh_v(tid); l < nl; l = fresh_v(l + BT)) {
+                    const float3 z = step_noise(ik, a0 + l, r, s + 1);
+                    gn[l] = z.x; gn[lm + l] = z.y; gn[2 * lm + l] = z.z;
                 }
-                for (int k = tid; k < 3 * lmax; k += BT) fa[k] = 0;
-                if (tid == 0) { *eacc = 0; ptask = 0; }
-                __syncthreads();
-                const int target = G * ++gen;
-                if ((tid & 63) == 0) {
-                    int spins = 0;
-                    while (__hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-                        if (++spins > SPIN_MAX) {
-                            atomicOr(errp + ERR_BARRIER, 1);
-                            bbuf = 0;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(1);
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (tid == 0) hbuf = __hip_atomic_load(sync + 16 + 16 * (int)(s % 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // all loads of a batch in flight before the first LDS write
-                constexpr int XU = 4;
-                for (int a0x = 0; a0x < n; a0x += XU * BT) {
-                    float2 xy[XU];
-                    float z[XU];
-#pragma unroll
-                    for (int u = 0; u < XU; ++u) {
-                        const int a = a0x + u * BT + tid;
-                        const bool other = a < n && (a < a0 || a >= a1);
-                        xy[u] = other ? ld_coh2(xch_xy + a) : make_float2(0.f, 0.f);
-                        z[u] = other ? ld_coh(xch_z + a) : 0.f;
-                    }
-#pragma unroll
-                    for (int u = 0; u < XU; ++u) {
-                        const int a = a0x + u * BT + tid;
-                        if (a < n && (a < a0 || a >= a1)) { xs[a].x = xy[u].x; xs[a].y = xy[u].y; xs[a].z = z[u]; }
-                    }
-                }
-                __syncthreads();
-                alive = bbuf != 0;
-                if (!alive) break;
-            } else {
-                alive = group_barrier(sync, G * ++gen, errp, &bbuf);
-                if (!alive) break;
-                if (tid == 0) hbuf = __hip_atomic_load(sync + 16 + 16 * (int)(s % 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                for (int a = tid; a < n; a += BT) {
-                    if (a >= a0 && a < a1) continue;
-                    const float2 xy = ld_coh2(xch_xy + a);
-                    xs[a].x = xy.x; xs[a].y = xy.y; xs[a].z = ld_coh(xch_z + a);
-                }
-                __syncthreads();
             }
+            const int target = G * ++gen;
+            if ((tid & 63) == 0) {
+                int spins = 0;
+                while (__hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+                    if (++spins > SPIN_MAX) {
+                        atomicOr((int *)errp + ERR_BARRIER, 1);
+                        bbuf = 0;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (tid == 0) hbuf = __hip_atomic_load(sync + 16 + 16 * (int)(s % 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // all loads of a batch in flight before the first LDS write
+            const int nn = fresh_s(n), npp = fresh_s(np);
+            float4 *xs = (float4 *)(lds_raw + persist_off(nn, npp, fresh_s(lmax)).xs);
+            const GPR_GLOBAL unsigned long long *xch_xy = (const GPR_GLOBAL unsigned long long *)xchg + (s & 1) * npp;
+            const GPR_GLOBAL float *xch_z = xchg + 4 * npp + (s & 1) * npp;
+            constexpr int XU = 4;
+            for (int ax = fresh_v(tid); ax < nn; ax = fresh_v(ax + XU * BT)) {
+                float2 xy[XU];
+                float z[XU];
+#pragma unroll
+                for (int u = 0; u < XU; ++u) {
+                    const int a = ax + u * BT;
+                    const bool other = a < nn && (a < a0 || a >= a1);
+                    xy[u] = other ? ld_coh2(xch_xy + a) : make_float2(0.f, 0.f);
+                    z[u] = other ? ld_coh(xch_z + a) : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < XU; ++u) {
+                    const int a = ax + u * BT;
+                    if (a < nn && (a < a0 || a >= a1)) { xs[a].x = xy[u].x; xs[a].y = xy[u].y; xs[a].z = z[u]; }
+                }
+            }
+            __syncthreads();
+            alive = bbuf != 0;
+            if (!alive) break;
             any_hit = hbuf;
         } else {
             any_hit = __syncthreads_or(hit);
@@ -1416,95 +1620,76 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
         if (need || (cutoff_on && (any_hit || s - lastb >= period))) {
             PHASE_COUNT(PH_NREBUILD);
             lastb = s;
-            // The search in tasks of 16 consecutive atoms (one wave each), costliest first by
-            // the lists of the last build (the summed longest sub-lists of the task's atoms),
-            // taken by the waves from a counter as they come free.  The order changes no list:
-            // each lane builds its own sub-list.  The costs sit in the waves' search scratch
-            // until the search starts (16 WBLK ints hold the tasks of 16,384 atoms).
-            const int ntk = (nl + 15) >> 4;
-            int *tcost = wscr;
-            for (int c = tid; c < ntk; c += BT) {
-                int sum = 0;
-                for (int l = 16 * c; l < min(16 * c + 16, nl); ++l) sum += keyl[l];
-                tcost[c] = sum;
-            }
-            if (tid == 0) btask = 0;
-            block_boxes(S, xs, box, tid, BT);
-            __syncthreads();
-            for (int c = tid; c < ntk; c += BT) {
-                const int mine = tcost[c];
-                int rank = 0;
-                for (int d = 0; d < ntk; ++d) rank += (tcost[d] > mine) | (tcost[d] == mine && d < c);
-                perm[rank] = (unsigned short)c;
-            }
-            __syncthreads();
-            for (;;) {
-                int t = 0;
-                if ((tid & 63) == 0) t = atomicAdd(&btask, 1);
-                t = __builtin_amdgcn_readfirstlane(__shfl(t, 0, 64));
-                if (t >= ntk) break;
-                const int c = __builtin_amdgcn_readfirstlane((int)perm[t]);
-                const int kq = build_wave<4, true>(&S, r, a0 + 16 * c, a1, (const GPR_LDS gv_f4 *)xs, (const GPR_LDS gv_f4 *)box,
-                                                   (GPR_LDS int *)wscr + (tid >> 6) * WBLK, 0);
-                const int l = 16 * c + (tid & 63);
-                if ((tid & 63) < 16 && l < nl) {
-                    const float4 x = xs[a0 + l];
-                    xbl[l] = x.x; xbl[lmax + l] = x.y; xbl[2 * lmax + l] = x.z;
-                    keyl[l] = (unsigned short)kq;
-                }
-            }
-            __syncthreads();                     // every task has read its entry of perm
-            order_atoms(keyl, perm, hist, nl, tid, BT);
+            persist_rebuild(&S, (GPR_LDS unsigned char *)lds_raw, (GPR_LDS int *)&btask, (GPR_LDS int *)torder, lmax, a0, a1, r,
+                            built % ORDER_PERIOD == 0);
+            ++built;
             if (need && g == 0 && tid == 0) S.list_pad[r] = 1;
             need = false;
         }
         PHASE_MARK(PH_REBUILD);
-        if (!split) {
-            for (int k = tid; k < 3 * lmax; k += BT) fa[k] = 0;
-            if (tid == 0) { *eacc = 0; ptask = 0; }
-            __syncthreads();
-        }
+        const int lm = fresh_s(lmax);
+        const PersistOff o = persist_off(fresh_s(n), fresh_s(np), lm);
+        long long *const fa = (long long *)(lds_raw + o.fa), *const eacc = (long long *)(lds_raw + o.red) + MAX_OBS * 8;
+        const float4 *const xs = (const float4 *)(lds_raw + o.xs);
+        const float2 *const pp = (const float2 *)lds_raw;
         if (toy) {
             if (tid == 0 && a0 == 0 && a1 > 0) {
                 float fx, fy;
                 const float u = toy_force(xs[0].x, xs[0].y, fx, fy);
                 fa[0] = fix_f(fx);
-                fa[lmax] = fix_f(fy);
+                fa[1] = fix_f(fy);
                 if (energy) *eacc = fix_f(u);
             }
         } else {
-            // bonded terms on the last waves, then the pair loop, whose tasks (16 atoms each,
+            const unsigned short *const perm = (const unsigned short *)(lds_raw + o.perm), *const keyl = (const unsigned short *)(lds_raw + o.keyl);
+            float *const gn = (float *)(lds_raw + o.gn);
+            const int lane = fresh_v(tid) & 63, q = lane & 3;
+            // bonded units on the last waves, then the pair loop, whose tasks (16 atoms each,
             // longest lists first) the waves take from a shared counter as they come free
-            const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-            if (wv >= bw0)
-                bonded_units(bi, bp, u0, u1, PosLDS{xs}, a0, fa, lmax, energy ? eacc : nullptr, wv - bw0, nbw, tid & 63);
-            const int ntask = nslot >> 4;
-            const NbConsts nbk = nb_consts(S);
+            if (wv >= bw0) {
+                const ForceLDS F{fa, a0, 3, 1};
+                if (energy) {
+                    const long long e = bonded_units<true>(bi, bp, u0, u1, PosLDS{xs}, F, wv - bw0, nbw, lane);
+                    if (e != 0) lds_add(eacc, e);
+                } else {
+                    bonded_units<false>(bi, bp, u0, u1, PosLDS{xs}, F, wv - bw0, nbw, lane);
+                }
+            }
+            const int ntask = (nl + 15) >> 4, nnoise = G == 1 && noise_ahead ? (nl + 63) >> 6 : 0;
             for (;;) {
                 int t = 0;
-                if ((tid & 63) == 0) t = atomicAdd(&ptask, 1);
-                t = __builtin_amdgcn_readfirstlane(__shfl(t, 0, 64));
-                if (t >= ntask) break;
-                const int q = tid & 3;
-                const int l = perm[16 * t + ((tid & 63) >> 2)];
+                if (lane == 0) t = lds_inc((GPR_LDS int *)&ptask);
+                t = uni(t);
+                if (t >= ntask) {
+                    // after them, with no exchange to draw them in, the next step's Gaussians
+                    if (t >= ntask + nnoise) break;
+                    const int l = 64 * (t - ntask) + lane;
+                    if (l < nl) {
+                        const float3 z = step_noise(ik, a0 + l, r, s + 1);
+                        gn[l] = z.x; gn[lm + l] = z.y; gn[2 * lm + l] = z.z;
+                    }
+                    continue;
+                }
+                const int l = perm[16 * t + (lane >> 2)];
                 long long eatom = 0;
                 if (l != 0xFFFF) {
                     const int i = a0 + l;
-                    float4 f = nb_lane(nbk, r, i, q, xs, pp, energy, keyl[l]);
+                    const unsigned off = (unsigned)(i * P + q) * 8;
+                    float4 f = energy ? pair_sums<true>(lists, off, lstep, keyl[l], xs[i], pp[i], xs, pp, rc2, krf2, krf, crf)
+                                      : pair_sums<false>(lists, off, lstep, keyl[l], xs[i], pp[i], xs, pp, rc2, krf2, krf, crf);
                     f.x = quad_sum(f.x);
                     f.y = quad_sum(f.y);
                     f.z = quad_sum(f.z);
-                    if (energy) f.w = quad_sum(f.w);
-                    if (q == 0) {
-                        lds_add(&fa[l], fix_f(f.x));
-                        lds_add(&fa[lmax + l], fix_f(f.y));
-                        lds_add(&fa[2 * lmax + l], fix_f(f.z));
-                        if (energy) eatom = fix_f(f.w);
+                    // one lane of the atom per component, and one for the energy
+                    if (q < 3) lds_add(&fa[3 * l + q], fix_f(q == 0 ? f.x : (q == 1 ? f.y : f.z)));
+                    if (energy) {
+                        f.w = quad_sum(f.w);
+                        if (q == 3) eatom = fix_f(f.w);
                     }
                 }
                 if (energy) {
                     eatom = wave_sum_ll(eatom);
-                    if ((tid & 63) == 0 && eatom != 0) lds_add(eacc, eatom);
+                    if (lane == 0 && eatom != 0) lds_add(eacc, eatom);
                 }
             }
         }
@@ -1514,57 +1699,41 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
         // launch), else by the next step's integrator
         pend = !(samp || step + 1 == nsteps);
         if (!pend) {
-            for (int a = a0 + tid; a < a1; a += BT) {
-                const int l = a - a0;
+            float *const vs = (float *)(lds_raw + o.vs);
+            const float *const iml = (const float *)(lds_raw + o.iml);
+            for (int l = fresh_v(tid); l < nl; l = fresh_v(l + BT)) {
                 const float im = iml[l], h = ik.h;
-                const float Fx = unfix_f(fa[l]), Fy = unfix_f(fa[lmax + l]), Fz = unfix_f(fa[2 * lmax + l]);
+                const float Fx = unfix_f(fa[3 * l]), Fy = unfix_f(fa[3 * l + 1]), Fz = unfix_f(fa[3 * l + 2]);
                 vs[l] = kick(vs[l], Fx, h, im);
-                vs[lmax + l] = kick(vs[lmax + l], Fy, h, im);
-                vs[2 * lmax + l] = kick(vs[2 * lmax + l], Fz, h, im);
-                if (bad_force(Fx) || bad_force(Fy) || bad_force(Fz)) atomicOr(&errp[ERR_UNSTABLE], 1);
+                vs[lm + l] = kick(vs[lm + l], Fy, h, im);
+                vs[2 * lm + l] = kick(vs[2 * lm + l], Fz, h, im);
+                if (bad_force(Fx) || bad_force(Fy) || bad_force(Fz)) atomicOr((int *)&errp[ERR_UNSTABLE], 1);
             }
-        }
-        if (samp) {
+            if (samp) {
+                if (G > 1) ++gen;
+                alive = persist_sample(&S, (GPR_LDS unsigned char *)lds_raw, (GPR_LDS int *)&bbuf, lmax, a0, a1, r, g, G, G * gen, energy);
+            }
             __syncthreads();
-            if (G == 1) {
-                for (int k = tid; k < 3 * np; k += BT) gmut(vg)[k] = k % np < n ? vs[(k / np) * lmax + k % np] : 0.f;
-                __syncthreads();
-                observables_wg(S, xs, vg, unfix_d(*eacc), red, vals, tid, BT);
-                if (tid == 0) accumulate_obs(S, r, vals);
-            } else {
-                // own velocities and energy to the group 0 of the replica
-                for (int a = a0 + tid; a < a1; a += BT) {
-                    const int l = a - a0;
-                    st_coh(vg + a, vs[l]); st_coh(vg + np + a, vs[lmax + l]); st_coh(vg + 2 * np + a, vs[2 * lmax + l]);
-                }
-                if (tid == 0 && energy && *eacc != 0)
-                    __hip_atomic_fetch_add(S.esum + r, *eacc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                alive = group_barrier(sync, G * ++gen, S.err, &bbuf);
-                if (!alive) break;
-                if (g == 0) {
-                    __shared__ long long etot;
-                    if (tid == 0) {
-                        etot = __hip_atomic_load(S.esum + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_store(S.esum + r, 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    __syncthreads();
-                    observables_wg(S, xs, vg, unfix_d(etot), red, vals, tid, BT, true);
-                    if (tid == 0) accumulate_obs(S, r, vals);
-                }
-            }
         }
-        __syncthreads();
         PHASE_MARK(PH_TAIL);
         PHASE_COUNT(PH_NSTEP);
     }
     // write back this group's atoms
-    for (int a = a0 + tid; a < a1; a += BT) {
-        const int l = a - a0;
-        xg[a] = xs[a].x; xg[np + a] = xs[a].y; xg[2 * np + a] = xs[a].z;
-        for (int d = 0; d < 3; ++d) {
-            gmut(vg)[d * np + a] = vs[d * lmax + l];
-            Fg[d * np + a] = fa[d * lmax + l];
-            xbg[d * np + a] = xbl[d * lmax + l];
+    const PersistOff o = persist_off(n, np, lmax);
+    const float4 *const xs = (const float4 *)(lds_raw + o.xs);
+    {
+        const long long *fa = (const long long *)(lds_raw + o.fa);
+        const float *vs = (const float *)(lds_raw + o.vs), *xbl = (const float *)(lds_raw + o.xbl);
+        GPR_GLOBAL float *xg = gmut(S.x) + b, *vg = gmut(S.v) + b, *xbg = gmut(S.xb) + b;
+        GPR_GLOBAL long long *Fg = gmut(S.F) + b;
+        for (int l = tid; l < nl; l += BT) {
+            const int a = a0 + l;
+            xg[a] = xs[a].x; xg[np + a] = xs[a].y; xg[2 * np + a] = xs[a].z;
+            for (int d = 0; d < 3; ++d) {
+                vg[d * np + a] = vs[d * lmax + l];
+                Fg[d * np + a] = fa[3 * l + d];
+                xbg[d * np + a] = xbl[d * lmax + l];
+            }
         }
     }
     if (g == 0 && tid == 0 && nsteps > 0) {
@@ -1573,7 +1742,7 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
     }
     if (state_end && g == 0) {
         __syncthreads();
-        const int id = state_wg(S, xs, red, &sbuf, tid, BT);
+        const int id = state_wg(S, PosLDS{xs}, (long long *)(lds_raw + o.red), &hbuf, tid, BT);
         if (tid == 0) S.state[r] = id;
     }
     if (G > 1 && nsteps > 0) {
@@ -1619,7 +1788,7 @@ __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
     int t0 = it.t0;
     if (it.cyc && !cycle_start(it, s0, t0)) return;
     persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1], it.sp.bi,
-                    it.sp.bp, set + it.roff, g, s0, it.nsteps, t0, it.sample, it.state_end);
+                    it.sp.bp, it.noise_ahead, set + it.roff, g, s0, it.nsteps, t0, it.sample, it.state_end);
 }
 
 // ------------------------------------------------------------------ small systems
@@ -1698,7 +1867,8 @@ __device__ double small_observable(const Dev &S, const ObsDesc &o, const SmallLd
         for (int a = lane; a < n; a += 64) s += fix_d(0.5 * (double)S.mass[a] * vel2(a));
         return unfix_d(wave_sum_ll(s));
     }
-    case OB_DIH: return dihedral_d(xs_d(L.xs, o.atoms[0]), xs_d(L.xs, o.atoms[1]), xs_d(L.xs, o.atoms[2]), xs_d(L.xs, o.atoms[3]));
+    case OB_DIH: return dihedral_d(xs_d(PosLDS{L.xs}, o.atoms[0]), xs_d(PosLDS{L.xs}, o.atoms[1]), xs_d(PosLDS{L.xs}, o.atoms[2]),
+                                   xs_d(PosLDS{L.xs}, o.atoms[3]));
     case OB_COMD: {
         double ax, ay, az, bx, by, bz;
         com(o.ga_off, o.ga_n, o.ma, ax, ay, az);
@@ -1999,7 +2169,7 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
     if (sample && r >= 1 && tid < 2 * S.nobs) S.acc[(size_t)r * 2 * MAX_OBS + tid] = L.acc[tid];
     if (S.cutoff_on && tid == 0 && nsteps > 0) S.need_build[r] = 1;
     if (state_end) {
-        const int id = state_wg(S, L.xs, L.red, &sbuf, tid, BT);
+        const int id = state_wg(S, PosLDS{L.xs}, L.red, &sbuf, tid, BT);
         if (tid == 0) S.state[r] = id;
     }
 #ifdef GPR_PHASE_PROBE
@@ -2029,12 +2199,12 @@ __global__ void __launch_bounds__(1024) k_persist_small(PersistItem it)
 // arguments of a call arrive in vector registers; they are wave-uniform, and made so again,
 // so that the values and branches that depend on them stay scalar.
 __device__ __noinline__ void persist_replica_call(const Dev *dev, int G, int lmax, int a0, int a1, int u0, int u1,
-                                                  const uint2 *bi, const float4 *bp, int r, int g, long long s0, int nsteps,
-                                                  int t0, int sample, int state_end)
+                                                  const uint2 *bi, const float4 *bp, int noise_ahead, int r, int g,
+                                                  long long s0, int nsteps, int t0, int sample, int state_end)
 {
     const Dev *d = (const Dev *)uni64((long long)dev);
     persist_replica(*d, uni(G), uni(lmax), uni(a0), uni(a1), uni(u0), uni(u1), (const uint2 *)uni64((long long)bi),
-                    (const float4 *)uni64((long long)bp), uni(r), uni(g), uni64(s0), uni(nsteps), uni(t0), uni(sample),
+                    (const float4 *)uni64((long long)bp), uni(noise_ahead), uni(r), uni(g), uni64(s0), uni(nsteps), uni(t0), uni(sample),
                     uni(state_end));
 }
 
@@ -2048,7 +2218,7 @@ __global__ void __launch_bounds__(1024) k_persist_batch(PersistBatch pb)
     if (!persist_place(it, (int)blockIdx.x - it.boff, set, g)) return;
     for (int r = set; r < it.nrep; r += it.nsets) {
         persist_replica_call(it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1],
-                             it.sp.bi, it.sp.bp, r, g, it.s0, it.nsteps, it.t0, it.sample, it.state_end);
+                             it.sp.bi, it.sp.bp, it.noise_ahead, r, g, it.s0, it.nsteps, it.t0, it.sample, it.state_end);
         __syncthreads();
     }
 }
