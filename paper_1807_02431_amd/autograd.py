@@ -34,9 +34,14 @@ class EnergyModel:
         return tuple(torch.tensor(p, dtype=torch.float64, device=device) for p in self._params)
 
     def _sync_params(self, *tensors):
-        new = tuple(t.detach().to("cpu", torch.float64).numpy() for t in tensors)
-        if any(a.shape != b.shape for a, b in zip(new, self._params)):
+        if any(t.shape != p.shape for t, p in zip(tensors, self._params)):
             raise ValueError("parameter shapes must be (n,), (n,), (n,), (n_torsions,)")
+        if len({t.device for t in tensors}) == 1:
+            # one copy to the host, not one for each
+            flat = torch.cat([t.detach().to(torch.float64) for t in tensors]).cpu().numpy()
+            new = np.split(flat, np.cumsum([p.size for p in self._params[:-1]]))
+        else:
+            new = tuple(t.detach().to("cpu", torch.float64).numpy() for t in tensors)
         if not all(np.array_equal(a, b) for a, b in zip(new, self._params)):
             self.system.set_params(*new)
             self._params = tuple(a.copy() for a in new)

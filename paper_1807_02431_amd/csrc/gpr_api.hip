@@ -91,9 +91,11 @@ struct gpr_system {
     CycRec *cyc_dev = nullptr, *cyc_host = nullptr;
     Status *stc_dev = nullptr, *stc_host = nullptr;   // [cycles] statuses of a replay
     // scratch
-    Status *st_dev = nullptr, *st_host = nullptr;
-    long long *adv_fec = nullptr;   // page-locked [R]: first exit checks read back by gpr_advance
-    int *adv_err = nullptr;         // page-locked [4]: error flags read back by gpr_advance
+    Status *st_host = nullptr;      // page-locked: the status of the last check, written by k_check
+    long long *adv_fec = nullptr;   // page-locked [R]: first exit checks of an advance
+    char *rb = nullptr;             // page-locked [rb_bytes]: results on their way to the caller (k_read)
+    size_t rb_bytes = 0;
+    bool gacc_dirty = false;        // a backward pass did not get to clear gacc
     double *obs_out = nullptr;
     int *donor = nullptr, *surv = nullptr;
     long long *fec = nullptr;
@@ -474,11 +476,11 @@ static hipError_t write_params(gpr_system *S)
 // (force_build = 0) rely on k_integrate to clear the energies and maintain the list guard;
 // force-only calls (force_build = 1) rebuild the lists and clear the energies here.
 static gpr_status launch_forces(gpr_system *S, int r_off, int nrep, long long s, int energy, int apply_b, int force_build,
-                                bool timed = false)
+                                bool timed = false, bool clear_e = true)
 {
     const int BTB = 256, BTN = 1024;
     if (force_build) s = S->s - 1;             // a forced build counts as built in the previous step
-    if (energy && force_build) {
+    if (energy && force_build && clear_e) {
         HIPCHK(S, hipMemsetAsync(S->d.E + r_off, 0, sizeof(long long) * nrep, S->stream));
     }
     dim3 gb((S->n + BTB - 1) / BTB, nrep);
@@ -753,28 +755,52 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
     return GPR_OK;
 }
 
-// the error flags a check copied into its status
-static gpr_status status_errors(gpr_system *S, const Status &st)
+// the error flags of a check's status, or read back
+static gpr_status flag_errors(gpr_system *S, const int *err)
 {
-    if (st.err[ERR_UNSTABLE]) return fail(S, GPR_EUNSTABLE, "non-finite or overflowing state");
-    if (st.err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
-    if (st.err[ERR_BARRIER]) return fail(S, GPR_EDEVICE, "persistent-kernel barrier timed out");
+    if (err[ERR_UNSTABLE]) return fail(S, GPR_EUNSTABLE, "non-finite or overflowing state");
+    if (err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
+    if (err[ERR_BARRIER]) return fail(S, GPR_EDEVICE, "persistent-kernel barrier timed out");
+    return GPR_OK;
+}
+
+// Up to three pieces of device memory (multiples of four bytes) into the read-back buffer, one after
+// the other, at most rb_bytes; there once the stream has been waited for.
+struct Piece {
+    const void *src;
+    size_t bytes;
+};
+static gpr_status read_pieces(gpr_system *S, std::initializer_list<Piece> pieces)
+{
+    ReadList l{};
+    size_t words = 0;
+    int k = 0;
+    for (const Piece &p : pieces) {
+        l.src[k] = (const uint32_t *)p.src;
+        l.words[k++] = (unsigned)(p.bytes / 4);
+        words += p.bytes / 4;
+    }
+    if (words * 4 > S->rb_bytes) return fail(S, GPR_EDEVICE, "read-back buffer too small");
+    const unsigned blocks = (unsigned)std::min<size_t>(256, (words + 255) / 256);
+    hipLaunchKernelGGL(k_read, dim3(std::max(1u, blocks)), dim3(256), 0, S->stream, l, (uint32_t *)S->rb);
+    LAUNCHCHK(S);
     return GPR_OK;
 }
 
 // one launch: bookkeeping by block (0, 0), and with CHK_DEPHASE the clone-on-kill copies by
 // the blocks of each killed worker's row
-static gpr_status check(gpr_system *S, int mode, int nrep, long long check_index)
+// (CHK_ADVANCE: fresh at the first check of a call; wait false: the caller waits and looks for errors)
+static gpr_status check(gpr_system *S, int mode, int nrep, long long check_index, bool fresh = false, bool wait = true)
 {
     const dim3 grid = mode == CHK_DEPHASE ? dim3((3 * S->np + 255) / 256, nrep) : dim3(1, 1);
     hipLaunchKernelGGL(k_check, grid, dim3(256), sizeof(int) * nrep, S->stream, S->d_dev, mode, S->s, S->omega, nrep,
-                       S->nsamp, check_index, (long long)S->tcp, S->st_dev, S->donor, S->surv, S->fec,
-                       (CycRec *)nullptr, 0);
+                       S->nsamp, check_index, (long long)S->tcp, S->st_host, S->donor, S->surv, S->fec, fresh ? 1 : 0,
+                       mode == CHK_ADVANCE ? S->adv_fec : (long long *)nullptr, (CycRec *)nullptr, 0);
     LAUNCHCHK(S);
-    HIPCHK(S, hipMemcpyAsync(S->st_host, S->st_dev, sizeof(Status), hipMemcpyDeviceToHost, S->stream));
+    if (!wait) return GPR_OK;
     HIPCHK(S, hipStreamSynchronize(S->stream));
     HIPCHK(S, prof_collect(S));
-    return status_errors(S, *S->st_host);
+    return flag_errors(S, S->st_host->err);
 }
 
 static gpr_status copy_replica(gpr_system *S, int dst, int src)
@@ -823,7 +849,7 @@ extern "C" void gpr_system_destroy(gpr_system *S)
     for (hipEvent_t e : S->ev_b) (void)hipEventDestroy(e);
     if (S->st_host) (void)hipHostFree(S->st_host);
     if (S->adv_fec) (void)hipHostFree(S->adv_fec);
-    if (S->adv_err) (void)hipHostFree(S->adv_err);
+    if (S->rb) (void)hipHostFree(S->rb);
     delete S;
 }
 
@@ -1151,10 +1177,10 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
 
     // scratch for the per-check bookkeeping
-    HIPCHK(S, dalloc(S, &S->st_dev, 1));
     HIPCHK(S, hipHostMalloc((void **)&S->st_host, sizeof(Status), hipHostMallocDefault));
     HIPCHK(S, hipHostMalloc((void **)&S->adv_fec, sizeof(long long) * R, hipHostMallocDefault));
-    HIPCHK(S, hipHostMalloc((void **)&S->adv_err, sizeof(int) * 4, hipHostMallocDefault));
+    S->rb_bytes = std::max<size_t>((size_t)6 * np * sizeof(float), (size_t)R * MAX_OBS * 16 + MAX_OBS * 8);
+    HIPCHK(S, hipHostMalloc((void **)&S->rb, S->rb_bytes, hipHostMallocDefault));
     HIPCHK(S, dalloc(S, &S->donor, R));
     HIPCHK(S, dalloc(S, &S->surv, R));
     HIPCHK(S, dalloc(S, &S->fec, R));
@@ -1629,15 +1655,14 @@ extern "C" gpr_status gpr_energy_forces_dev(gpr_system *S, const float *x_dev, d
 {
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
     if (!x_dev) return fail(S, GPR_EINVAL, "NULL positions");
-    const int n = S->n, np = S->np, R = S->R;
-    HIPCHK(S, hipMemcpy2DAsync(S->d.x, sizeof(float) * np, x_dev, sizeof(float) * n, sizeof(float) * n, (size_t)3 * R,
-                               hipMemcpyDeviceToDevice, S->stream));
-    gpr_status rc = launch_forces(S, 0, R, -1, 1, 0, 1);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_unfix_out, dim3((n + 255) / 256, R), dim3(256), 0, S->stream, S->d_dev, energy_dev, forces_dev);
+    const int n = S->n, R = S->R;
+    hipLaunchKernelGGL(k_load_x, dim3((n + 255) / 256, R), dim3(256), 0, S->stream, S->d_dev, x_dev);
     LAUNCHCHK(S);
-    int err[4];
-    HIPCHK(S, hipMemcpyAsync(err, S->d.err, sizeof err, hipMemcpyDeviceToHost, S->stream));
+    gpr_status rc = launch_forces(S, 0, R, -1, 1, 0, 1, false, false);
+    if (rc) return rc;
+    int *err = (int *)S->rb;
+    hipLaunchKernelGGL(k_unfix_out, dim3((n + 255) / 256, R), dim3(256), 0, S->stream, S->d_dev, energy_dev, forces_dev, err);
+    LAUNCHCHK(S);
     HIPCHK(S, hipStreamSynchronize(S->stream));
     if (err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
     return GPR_OK;
@@ -1659,7 +1684,10 @@ extern "C" gpr_status gpr_energy_backward_dev(gpr_system *S, const double *w_dev
         LAUNCHCHK(S);
     }
     if (params) {
-        HIPCHK(S, hipMemsetAsync(S->d.gacc, 0, sizeof(long long) * ((size_t)3 * np + std::max(1, nt)), S->stream));
+        // gacc is clear: k_grad_finish leaves it so
+        if (S->gacc_dirty)
+            HIPCHK(S, hipMemsetAsync(S->d.gacc, 0, sizeof(long long) * ((size_t)3 * np + std::max(1, nt)), S->stream));
+        S->gacc_dirty = true;
         hipLaunchKernelGGL(k_grad_nb, dim3((n * P + 1023) / 1024, R), dim3(1024), S->lds_nb, S->stream, S->d_dev, w_dev);
         LAUNCHCHK(S);
         const int nterm = std::max(nt, n14);
@@ -1670,6 +1698,7 @@ extern "C" gpr_status gpr_energy_backward_dev(gpr_system *S, const double *w_dev
         hipLaunchKernelGGL(k_grad_finish, dim3((std::max(n, nt) + 255) / 256), dim3(256), 0, S->stream, S->d_dev, d_eps,
                            d_sigma, d_charge, d_torsion_k);
         LAUNCHCHK(S);
+        S->gacc_dirty = false;
     }
     HIPCHK(S, hipStreamSynchronize(S->stream));
     return GPR_OK;
@@ -1680,15 +1709,17 @@ extern "C" gpr_status gpr_get_state(const gpr_system *Sc, int32_t r, double *q, 
     gpr_system *S = const_cast<gpr_system *>(Sc);
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
     if (r < 0 || r >= S->R) return fail(S, GPR_EINVAL, "replica index");
-    std::vector<float> x(3 * S->np), vv(3 * S->np);
-    HIPCHK(S, hipMemcpyAsync(x.data(), S->d.x + (size_t)r * 3 * S->np, x.size() * 4, hipMemcpyDeviceToHost, S->stream));
-    HIPCHK(S, hipMemcpyAsync(vv.data(), S->d.v + (size_t)r * 3 * S->np, vv.size() * 4, hipMemcpyDeviceToHost, S->stream));
+    const size_t m = (size_t)3 * S->np;
+    const gpr_status rc = read_pieces(S, {{S->d.x + r * m, m * 4}, {S->d.v + r * m, m * 4}});
+    if (rc) return rc;
     HIPCHK(S, hipStreamSynchronize(S->stream));
-    for (int c = 0; c < 3; ++c)
-        for (int i = 0; i < S->n; ++i) {
-            if (q) q[c * S->n + i] = x[c * S->np + i];
-            if (v) v[c * S->n + i] = vv[c * S->np + i];
-        }
+    const float *x = (const float *)S->rb;
+    for (double *out : {q, v}) {
+        if (out)
+            for (int c = 0; c < 3; ++c)
+                for (int i = 0; i < S->n; ++i) out[c * S->n + i] = x[c * S->np + i];
+        x += m;
+    }
     return GPR_OK;
 }
 
@@ -1720,17 +1751,17 @@ extern "C" gpr_status gpr_get_accumulators(const gpr_system *Sc, int64_t *n, dou
 {
     gpr_system *S = const_cast<gpr_system *>(Sc);
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
-    std::vector<double> acc((size_t)S->R * MAX_OBS * 2), sh(MAX_OBS);
-    HIPCHK(S, hipMemcpyAsync(acc.data(), S->d.acc, acc.size() * 8, hipMemcpyDeviceToHost, S->stream));
-    HIPCHK(S, hipMemcpyAsync(sh.data(), S->d.shift, sh.size() * 8, hipMemcpyDeviceToHost, S->stream));
+    const gpr_status rc = read_pieces(S, {{S->d.shift, MAX_OBS * 8}, {S->d.acc, (size_t)S->R * MAX_OBS * 16}});
+    if (rc) return rc;
     HIPCHK(S, hipStreamSynchronize(S->stream));
-    if (n) *n = S->nsamp;
+    const double *sh = (const double *)S->rb, *acc = sh + MAX_OBS;
     for (int r = 0; r < S->R; ++r)
         for (int j = 0; j < S->nobs; ++j) {
             if (S1) S1[r * S->nobs + j] = acc[((size_t)r * MAX_OBS + j) * 2];
             if (S2) S2[r * S->nobs + j] = acc[((size_t)r * MAX_OBS + j) * 2 + 1];
         }
     if (shift) for (int j = 0; j < S->nobs; ++j) shift[j] = sh[j];
+    if (n) *n = S->nsamp;
     return GPR_OK;
 }
 
@@ -2022,7 +2053,8 @@ static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
         }
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(k_check, cgrid, dim3(256), sizeof(int) * nrep, cs, S->d_dev, dep ? CHK_DEPHASE : CHK_PARALLEL,
-                           0LL, 0, nrep, 0LL, 0LL, (long long)S->tcp, S->stc_dev, S->donor, S->surv, S->fec, S->cyc_dev, j);
+                           0LL, 0, nrep, 0LL, 0LL, (long long)S->tcp, S->stc_dev, S->donor, S->surv, S->fec, 0, (long long *)nullptr,
+                           S->cyc_dev, j);
         e = hipGetLastError();
     }
     hipGraph_t g = nullptr;
@@ -2070,7 +2102,7 @@ static gpr_status run_cycles(gpr_system *S, PhaseRun &p, bool &ran)
     const int ncyc = halt == NO_HALT ? C : halt + 1;
     for (int j = 0; j < ncyc; ++j) {
         const Status &st = S->stc_host[j];
-        rc = status_errors(S, st);
+        rc = flag_errors(S, st.err);
         if (rc) return rc;
         Chunk c{};
         c.nrep = S->R; c.k = per; c.t0 = dep ? S->dp_t : 0; c.sample = dep; c.at_check = true;
@@ -2210,36 +2242,36 @@ extern "C" gpr_status gpr_advance(gpr_system *S, int64_t nsteps, int64_t *first_
 {
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
     if (nsteps < 0) return fail(S, GPR_EINVAL, "nsteps < 0");
-    // first exit checks are recorded (and read back) only for a caller that asks for them
-    if (first_exit_check) HIPCHK(S, hipMemsetAsync(S->fec, 0, sizeof(long long) * S->R, S->stream));
     // the sampling (every t_GR) and check (every t_check_dephase) schedule runs on the steps
     // counted over all calls, so that short calls sample and check as one long call would
     long long t = S->adv_t;
     const long long end = S->adv_t + nsteps;
+    bool checked = false, at_check = false;
     while (t < end) {
         const long long k = std::min<long long>(S->tcd - t % S->tcd, end - t);
-        const bool at_check = (t + k) % S->tcd == 0;
+        at_check = (t + k) % S->tcd == 0;
         gpr_status rc = run_steps(S, S->R, k, t, true, at_check);
         if (rc) return rc;
         S->nsamp += count_samples(t, t + k, S->t_gr);
         t += k;
         S->adv_t = t;
         if (at_check) {
-            rc = check(S, CHK_ADVANCE, S->R, t / S->tcd);
+            rc = check(S, CHK_ADVANCE, S->R, t / S->tcd, !checked, t < end);
             if (rc) return rc;
+            checked = true;
         }
     }
-    // error flags (and first exit checks) through page-locked memory, one wait
-    if (first_exit_check)
-        HIPCHK(S, hipMemcpyAsync(S->adv_fec, S->fec, sizeof(long long) * S->R, hipMemcpyDeviceToHost, S->stream));
-    HIPCHK(S, hipMemcpyAsync(S->adv_err, S->d.err, sizeof(int) * 4, hipMemcpyDeviceToHost, S->stream));
+    // one wait for the steps and the results: the error flags come with the check that ends the call,
+    // the first exit checks with its last check
+    if (!at_check) {
+        const gpr_status rc = read_pieces(S, {{S->d.err, sizeof(int) * 4}});
+        if (rc) return rc;
+    }
     HIPCHK(S, hipStreamSynchronize(S->stream));
     HIPCHK(S, prof_collect(S));
-    const int *err = S->adv_err;
-    if (err[ERR_UNSTABLE]) return fail(S, GPR_EUNSTABLE, "non-finite or overflowing state");
-    if (err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
-    if (err[ERR_BARRIER]) return fail(S, GPR_EDEVICE, "persistent-kernel barrier timed out");
-    if (first_exit_check) for (int r = 0; r < S->R; ++r) first_exit_check[r] = S->adv_fec[r];
+    const gpr_status rc = flag_errors(S, at_check ? S->st_host->err : (const int *)S->rb);
+    if (rc) return rc;
+    if (first_exit_check) for (int r = 0; r < S->R; ++r) first_exit_check[r] = checked ? S->adv_fec[r] : 0;
     return GPR_OK;
 }
 
@@ -2362,8 +2394,7 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
     if (rc) return rc;
     std::vector<long long> t(nsys, 0);
     for (int k = 0; k < nsys; ++k) t[k] = systems[k]->adv_t;
-    for (int k = 0; k < nsys; ++k)
-        HIPCHK(systems[k], hipMemsetAsync(systems[k]->fec, 0, sizeof(long long) * systems[k]->R, stream));
+    std::vector<char> checked(nsys, 0);
     long long done = 0;
     while (done < nsteps) {
         long long kstep = nsteps - done;
@@ -2387,24 +2418,24 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
             t[k] += kstep;
             S->adv_t = t[k];
             if (t[k] % S->tcd == 0) {
-                rc = check(S, CHK_ADVANCE, S->R, t[k] / S->tcd);
+                rc = check(S, CHK_ADVANCE, S->R, t[k] / S->tcd, !checked[k]);
                 if (rc) return rc;
+                checked[k] = 1;
             }
         }
         done += kstep;
     }
     for (int k = 0; k < nsys; ++k) {
+        rc = read_pieces(systems[k], {{systems[k]->d.err, sizeof(int) * 4}});
+        if (rc) return rc;
+    }
+    HIPCHK(S0, hipStreamSynchronize(stream));
+    for (int k = 0; k < nsys; ++k) {
         gpr_system *S = systems[k];
-        std::vector<long long> f(S->R);
-        HIPCHK(S, hipMemcpyAsync(f.data(), S->fec, sizeof(long long) * S->R, hipMemcpyDeviceToHost, stream));
-        int err[4];
-        HIPCHK(S, hipMemcpyAsync(err, S->d.err, sizeof err, hipMemcpyDeviceToHost, stream));
-        HIPCHK(S, hipStreamSynchronize(stream));
-        if (err[ERR_UNSTABLE]) return fail(S, GPR_EUNSTABLE, "non-finite or overflowing state");
-        if (err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
-        if (err[ERR_BARRIER]) return fail(S, GPR_EDEVICE, "persistent-kernel barrier timed out");
+        rc = flag_errors(S, (const int *)S->rb);
+        if (rc) return rc;
         if (first_exit_check && first_exit_check[k])
-            for (int r = 0; r < S->R; ++r) first_exit_check[k][r] = f[r];
+            for (int r = 0; r < S->R; ++r) first_exit_check[k][r] = checked[k] ? S->adv_fec[r] : 0;
     }
     return GPR_OK;
 }

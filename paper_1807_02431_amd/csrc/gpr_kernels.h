@@ -138,11 +138,18 @@ __global__ void k_persist_batch(PersistBatch pb);
 __global__ void k_grad_nb(const Dev *__restrict__ Sp, const double *w);
 __global__ void k_grad_terms(const Dev *__restrict__ Sp, const double *w);
 __global__ void k_grad_finish(const Dev *__restrict__ Sp, double *d_eps, double *d_sigma, double *d_charge, double *d_tk);
-__global__ void k_unfix_out(const Dev *__restrict__ Sp, double *energy, float *forces);
+__global__ void k_unfix_out(const Dev *__restrict__ Sp, double *energy, float *forces, int *err);
 __global__ void k_weighted_dx(const Dev *__restrict__ Sp, const double *w, float *dx);
 __global__ void k_check(const Dev *__restrict__ Sp, int mode, long long s, int omega, int nrep, long long nsamp,
                         long long check_index, long long t_check, Status *st, int *donor, int *surv, long long *fec,
-                        CycRec *cyc, int cycle);
+                        int fec_fresh, long long *fec_out, CycRec *cyc, int cycle);
+// pieces of device memory of `words` 32-bit words each, one after the other (words 0: none)
+struct ReadList {
+    const uint32_t *src[3];
+    unsigned words[3];
+};
+__global__ void k_read(ReadList l, uint32_t *out);
+__global__ void k_load_x(const Dev *__restrict__ Sp, const float *x);
 __global__ void k_clone(const Dev *__restrict__ Sp, const int *donor, int acc_mode);
 __global__ void k_init_vel(const Dev *__restrict__ Sp, float kT);
 __global__ void k_noise_test(uint32_t k0, uint32_t k1, int replica, long long step, int stream, int n,

@@ -1145,8 +1145,12 @@ __global__ void __launch_bounds__(256) k_grad_finish(const Dev *__restrict__ Sp,
         if (d_eps) d_eps[a] = unfix_d(S.gacc[a]) * S.inv2eps[a];
         if (d_sigma) d_sigma[a] = unfix_d(S.gacc[S.np + a]);
         if (d_charge) d_charge[a] = unfix_d(S.gacc[2 * S.np + a]) * sqrt_f;
+        S.gacc[a] = S.gacc[S.np + a] = S.gacc[2 * S.np + a] = 0;      // for the next call
     }
-    if (a < S.tp.nt && d_tk) d_tk[S.tor_orig[a]] = unfix_d(S.gacc[3 * S.np + a]);
+    if (a < S.tp.nt) {
+        if (d_tk) d_tk[S.tor_orig[a]] = unfix_d(S.gacc[3 * S.np + a]);
+        S.gacc[3 * S.np + a] = 0;
+    }
 }
 
 // dx[r] = w[r] dU_r/dx = -w[r] F_r, from the fixed-point forces
@@ -1162,12 +1166,35 @@ __global__ void __launch_bounds__(256) k_weighted_dx(const Dev *__restrict__ Sp,
     }
 }
 
-// energies and forces of every replica out of the fixed-point accumulators
-__global__ void __launch_bounds__(256) k_unfix_out(const Dev *__restrict__ Sp, double *energy, float *forces)
+// Positions [R][3][n] into the replicas' padded arrays, their energies cleared for the force kernels
+__global__ void __launch_bounds__(256) k_load_x(const Dev *__restrict__ Sp, const float *x)
 {
     const Dev &S = *Sp;
     const int r = blockIdx.y;
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a == 0) S.E[r] = 0;
+    if (a < S.n)
+        for (int d = 0; d < 3; ++d) S.x[((size_t)r * 3 + d) * S.np + a] = x[((size_t)r * 3 + d) * S.n + a];
+}
+
+// Pieces of device memory into page-locked host memory: a read-back is one launch and one wait, where
+// a copy per piece costs some 15 us each (a 300-atom replica's state 37 -> 18 us, call and all).
+__global__ void __launch_bounds__(256) k_read(ReadList l, uint32_t *out)
+{
+    const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    for (int p = 0; p < 3; ++p) {
+        for (unsigned w = t; w < l.words[p]; w += step) out[w] = l.src[p][w];
+        out += l.words[p];
+    }
+}
+
+// energies and forces of every replica out of the fixed-point accumulators, and the error flags
+__global__ void __launch_bounds__(256) k_unfix_out(const Dev *__restrict__ Sp, double *energy, float *forces, int *err)
+{
+    const Dev &S = *Sp;
+    const int r = blockIdx.y;
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a < 4 && r == 0) err[a] = S.err[a];
     if (a == 0 && energy) energy[r] = unfix_d(S.E[r]);
     if (a < S.n && forces) {
         for (int d = 0; d < 3; ++d)
@@ -2382,7 +2409,8 @@ __device__ void vote_block(int R, Fec fec, long long t_check, long long *red, lo
 // donor's observable sums (cleared when every worker is re-copied from the reference).
 __global__ void __launch_bounds__(256) k_check(const Dev *__restrict__ Sp, int mode, long long s, int omega, int nrep,
                                                long long nsamp, long long check_index, long long t_check, Status *st,
-                                               int *donor, int *surv, long long *fec, CycRec *cyc, int cycle)
+                                               int *donor, int *surv, long long *fec, int fec_fresh, long long *fec_out,
+                                               CycRec *cyc, int cycle)
 {
     const Dev &S = *Sp;
     const int tid = threadIdx.x;
@@ -2451,7 +2479,13 @@ __global__ void __launch_bounds__(256) k_check(const Dev *__restrict__ Sp, int m
         const int dq = fv_donor(S.key0, S.key1, s, q, ex, sl, ns);
         if (mode == CHK_DEPHASE || mode == CHK_ADVANCE) donor[q] = dq;
         ne += q > 0 && ex(q);
-        if (mode == CHK_ADVANCE && fec[q] == 0 && ex(q)) fec[q] = check_index;
+        if (mode == CHK_ADVANCE) {
+            // the check of the first exit: from none at a call's first check (fec_fresh)
+            long long f = fec_fresh ? 0 : fec[q];
+            if (f == 0 && ex(q)) f = check_index;
+            fec[q] = f;
+            if (fec_out) fec_out[q] = f;
+        }
     }
     for (int o = 32; o > 0; o >>= 1) ne += __shfl_xor(ne, o, 64);
     if ((tid & 63) == 0 && ne) atomicAdd(&sh_ne, ne);
