@@ -276,14 +276,14 @@ static size_t small_lds(const gpr_system *S)
 {
     const Topo &T = S->d.tp;
     const size_t n = S->n, np = S->np, nterm = (size_t)T.nt + T.na + T.n14 + T.nb + T.nr;
-    return 16 * np + 16 * nterm + 48 * n + 64 + 24 * MAX_OBS + 8 * np + 8 * 64 * ((n + 15) / 16) + 8 * nterm + 32 * n;
+    return 16 * np + 16 * nterm + 48 * n + 64 + (24 + sizeof(ObsDesc)) * MAX_OBS + 8 * np + 8 * 64 * ((n + 15) / 16) + 8 * nterm + 32 * n;
 }
 static int small_units(const gpr_system *S)
 {
     const Topo &T = S->d.tp;
     auto blocks = [](int c) { return (c + 63) / 64; };
     return blocks(T.nt) + blocks(T.na) + blocks(T.n14) + blocks(T.nb) + blocks(T.nr) + blocks(S->n) +
-           (S->kind == GPR_KIND_TOY2D ? 0 : (S->n + 15) / 16);
+           (S->kind == GPR_KIND_TOY2D ? 1 : (S->n + 15) / 16);
 }
 // Launch shape of a persistent launch of one system's first nrep replicas.  Unless the caller (or
 // the autotuner) chose it:

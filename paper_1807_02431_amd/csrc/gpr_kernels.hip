@@ -16,11 +16,29 @@ namespace gpr {
 // ------------------------------------------------------------------ small helpers
 __device__ __forceinline__ float kick(float v, float F, float h, float im) { return v + (h * F) * im; }
 
+// Sum over the wave, in every lane: pairs, quads, eights and rows of 16 by DPP moves, the four rows by
+// scalar adds.  All lanes are active.  (Six shuffles through LDS took 0.3 us of a toy step.)
+template <int CTRL>
+__device__ __forceinline__ long long dpp_ll(long long v)
+{
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xF, 0xF, true);
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
 __device__ __forceinline__ long long wave_sum_ll(long long v)
 {
+    v += dpp_ll<0xB1>(v);                                   // quad_perm [1, 0, 3, 2]
+    v += dpp_ll<0x4E>(v);                                   // quad_perm [2, 3, 0, 1]
+    v += dpp_ll<0x141>(v);                                  // row_half_mirror
+    v += dpp_ll<0x140>(v);                                  // row_mirror
+    long long s = 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int row = 0; row < 4; ++row) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, 16 * row);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), 16 * row);
+        s += (long long)(((unsigned long long)hi << 32) | lo);
+    }
+    return s;
 }
 
 // the P = 4 lanes of one atom are consecutive: (s0 + s1) + (s2 + s3) in a fixed order
@@ -906,7 +924,9 @@ __global__ void __launch_bounds__(256) k_bonded(const Dev *__restrict__ Sp, long
 // Nonbonded forces of atoms [blockIdx.x * blockDim.x / P, ...) of replica r (P lanes per
 // atom), added to the bonded forces; then the closing B kick (apply_b).  The pair lists of
 // the block's atoms are rebuilt first when due (period, displacement guard, force_build).
-__global__ void __launch_bounds__(1024) k_nonbonded(const Dev *__restrict__ Sp, long long s, int r_off, int energy, int apply_b,
+// (At most 64 registers, so that two workgroups share a compute unit where their LDS fits, one staging
+// or waiting while the other computes: 85 -> 66 us for 64 replicas of 2,432 atoms with a rebuild.)
+__global__ void __launch_bounds__(1024, 8) k_nonbonded(const Dev *__restrict__ Sp, long long s, int r_off, int energy, int apply_b,
                                                    int force_build)
 {
     step_args(*Sp, s, energy);
@@ -1827,7 +1847,10 @@ __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
 //   sub-list order of the pair lists: lane 4 (i - i0) + q runs over j = q, q + 4, ... with the
 //   partners outside the list, the cutoff or the system adding an exact zero); the Gaussians of
 //   the next step for 64 atoms.
-// The arithmetic, its order and the fixed-point sums are the general body's, so are the bits.
+// The arithmetic, its order and the fixed-point sums are the general body's, so are the bits.  The
+// integrator takes a component per thread, which is a third of its chain (0.58 -> 0.42 of 1.6 us a
+// step at 22 atoms); the rest is one wave's torsions or pairs, about 0.9 us of dependent arithmetic
+// and LDS atomics whichever way they are split (four lanes a torsion came out the same).
 // Pairs are not listed (up to SMALL_MAX atoms running over all of them costs less than reading a
 // list), so the launch leaves a system with a cutoff marked for a list rebuild.
 struct SmallLds {
@@ -1839,6 +1862,7 @@ struct SmallLds {
     unsigned long long *am;     // [64 ceil(n / 16)] bit k: partner 4 k + q of the lane's atom counts
     float4 *tp;                 // [nterm] parameters of the bonded terms
     uint2 *ti;                  // [nterm] their atoms, 16 bits each
+    ObsDesc *ob;                // [MAX_OBS]
     float *vs, *im, *sd, *gn;   // [3][n], [n], [n], [3][n]: velocities, 1/m, noise amplitudes, Gaussians
 };
 
@@ -1851,7 +1875,8 @@ __device__ __forceinline__ SmallLds small_lds_layout(unsigned char *raw, int n, 
     L.red = L.fa + 6 * n;
     L.acc = (double *)(L.red + 8);
     L.shift = L.acc + 2 * MAX_OBS;
-    L.pp = (float2 *)(L.shift + MAX_OBS);
+    L.ob = (ObsDesc *)(L.shift + MAX_OBS);
+    L.pp = (float2 *)(L.ob + MAX_OBS);
     L.am = (unsigned long long *)(L.pp + np);
     L.ti = (uint2 *)(L.am + 64 * ((n + 15) >> 4));
     L.vs = (float *)(L.ti + nterm);
@@ -2016,13 +2041,17 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
         L.am[c] = m;
     }
     if (tid < 2 * MAX_OBS) L.acc[tid] = S.acc[(size_t)r * 2 * MAX_OBS + tid];
-    if (tid < MAX_OBS) L.shift[tid] = S.shift[tid];
+    if (tid < MAX_OBS) {
+        L.shift[tid] = S.shift[tid];
+        L.ob[tid] = S.obs[tid];
+    }
     if (tid < 2) eacc[tid] = 0;
     __syncthreads();
     PHASE_MARK(PH_PROLOGUE);
 
-    // units of a step, the longest first: torsions, pair tasks, angles, noise, 1-4, bonds, restraints
-    const int u0 = (nt + 63) >> 6, u1 = u0 + npt, u2 = u1 + ((na + 63) >> 6), u3 = u2 + ((n + 63) >> 6), u4 = u3 + ((n14 + 63) >> 6), u5 = u4 + ((nb + 63) >> 6), u6 = u5 + ((nr + 63) >> 6);
+    // units of a step, the longest first: torsions, pair tasks, angles, noise, 1-4, bonds, restraints,
+    // the toy potential
+    const int u0 = (nt + 63) >> 6, u1 = u0 + npt, u2 = u1 + ((na + 63) >> 6), u3 = u2 + ((n + 63) >> 6), u4 = u3 + ((n14 + 63) >> 6), u5 = u4 + ((nb + 63) >> 6), u6 = u5 + ((nr + 63) >> 6), u7 = u6 + toy;
     bool pend = false;                                      // the previous step's closing B is due
     int cur = 0;                                            // accumulators holding the last forces
     for (int step = 0; step < nsteps; ++step) {
@@ -2031,21 +2060,23 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
         // B A O A; the accumulators read here are cleared while the others are being summed
         long long *const f0 = L.fa + 3 * n * cur;
         bool bad = false;
-        for (int a = tid; a < n; a += BT) {
-            float3 x = make_float3(L.xs[a].x, L.xs[a].y, L.xs[a].z);
-            float3 v = make_float3(L.vs[a], L.vs[n + a], L.vs[2 * n + a]);
-            const float3 F = make_float3(unfix_f(f0[a]), unfix_f(f0[n + a]), unfix_f(f0[2 * n + a]));
-            const float im = L.im[a];
+        // (a component per thread: integrate_baoa_g's operations, none of which mixes them)
+        for (int k = tid; k < 3 * n; k += BT) {
+            const int d = (k >= n) + (k >= 2 * n), a = k - d * n;
+            float *const xp = (float *)(L.xs + a) + d;
+            float x = *xp, v = L.vs[k];
+            const float F = unfix_f(f0[k]), im = L.im[a], h = ik.h;
             if (pend) {
-                v.x = kick(v.x, F.x, ik.h, im);
-                v.y = kick(v.y, F.y, ik.h, im);
-                v.z = kick(v.z, F.z, ik.h, im);
-                bad |= bad_force(F.x) || bad_force(F.y) || bad_force(F.z);
+                v = kick(v, F, h, im);
+                bad |= bad_force(F);
             }
-            integrate_baoa_g(ik, x, v, F, im, L.sd[a], make_float3(L.gn[a], L.gn[n + a], L.gn[2 * n + a]));
-            L.xs[a].x = x.x; L.xs[a].y = x.y; L.xs[a].z = x.z;
-            L.vs[a] = v.x; L.vs[n + a] = v.y; L.vs[2 * n + a] = v.z;
-            bad |= !(finite3(x) && finite3(v));
+            v = kick(v, F, h, im);
+            x = x + h * v;
+            if (!(toy && d == 2)) v = ik.c1 * v + L.sd[a] * L.gn[k];
+            x = x + h * v;
+            *xp = x;
+            L.vs[k] = v;
+            bad |= !(isfinite(x) && isfinite(v));
         }
         if (bad) atomicOr(&errp[ERR_UNSTABLE], 1);
         cur ^= 1;
@@ -2059,7 +2090,7 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
         };
         const PosLDS pos{L.xs};
         long long e = 0;
-        for (int u = wv; u < u6; u += nwv) {
+        for (int u = wv; u < u7; u += nwv) {
             if (u >= u0 && u < u1) {
                 const int i = 16 * (u - u0) + (lane >> 2), q = lane & 3;
                 const float4 pi = L.xs[i];
@@ -2109,12 +2140,6 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
                     const float3 g = step_noise(ik, a, r, s0 + step + 1);
                     L.gn[a] = g.x; L.gn[n + a] = g.y; L.gn[2 * n + a] = g.z;
                     if (a == 0) eacc[cur ^ 1] = 0;
-                    if (toy) {
-                        float3 f = make_float3(0.f, 0.f, 0.f);
-                        e += fix_f(toy_force(L.xs[0].x, L.xs[0].y, f.x, f.y));
-                        fa[0] = fix_f(f.x);
-                        fa[n] = fix_f(f.y);
-                    }
                 }
             } else if (u < u4) {
                 const int t = 64 * (u - u3) + lane;
@@ -2137,7 +2162,7 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
                     add(w.x >> 16, neg3(fi));
                     e += fix_f(ut);
                 }
-            } else {
+            } else if (u < u6) {
                 const int t = 64 * (u - u5) + lane;
                 if (t < nr) {
                     const int i = L.ti[nt + na + n14 + nb + t].x;
@@ -2147,6 +2172,11 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
                     add(i, make_float3(-p.w * dx, -p.w * dy, -p.w * dz));
                     e += fix_f(0.5f * p.w * (dx * dx + dy * dy + dz * dz));
                 }
+            } else if (lane == 0) {
+                float3 f = make_float3(0.f, 0.f, 0.f);
+                e += fix_f(toy_force(L.xs[0].x, L.xs[0].y, f.x, f.y));
+                fa[0] = fix_f(f.x);
+                fa[n] = fix_f(f.y);
             }
         }
         if (energy) {
@@ -2158,20 +2188,17 @@ __device__ __forceinline__ void persist_small(const Dev &S, int r, long long s0,
         // the closing B: here when the step's velocities are read, else by the next integrator
         pend = !(samp || step + 1 == nsteps);
         if (!pend) {
-            for (int a = tid; a < n; a += BT) {
-                const float im = L.im[a];
-                const float Fx = unfix_f(fa[a]), Fy = unfix_f(fa[n + a]), Fz = unfix_f(fa[2 * n + a]);
-                L.vs[a] = kick(L.vs[a], Fx, ik.h, im);
-                L.vs[n + a] = kick(L.vs[n + a], Fy, ik.h, im);
-                L.vs[2 * n + a] = kick(L.vs[2 * n + a], Fz, ik.h, im);
-                if (bad_force(Fx) || bad_force(Fy) || bad_force(Fz)) atomicOr(&errp[ERR_UNSTABLE], 1);
+            for (int k = tid; k < 3 * n; k += BT) {
+                const float F = unfix_f(fa[k]);
+                L.vs[k] = kick(L.vs[k], F, ik.h, L.im[k - ((k >= n) + (k >= 2 * n)) * n]);
+                if (bad_force(F)) atomicOr(&errp[ERR_UNSTABLE], 1);
             }
         }
         if (samp) {
             // one wave per observable, its sums kept in LDS
             __syncthreads();
             for (int j = wv; j < S.nobs; j += nwv) {
-                const double val = small_observable(S, S.obs[j], L, unfix_d(eacc[cur]), lane);
+                const double val = small_observable(S, L.ob[j], L, unfix_d(eacc[cur]), lane);
                 if (lane == 0) {
                     const double xj = val - L.shift[j];
                     L.acc[2 * j] += xj;
