@@ -1092,7 +1092,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     HIPCHK(S, dalloc(S, &d.clock, 2));
     HIPCHK(S, dalloc(S, &d.err, 4));
     HIPCHK(S, dalloc(S, &d.sync, (size_t)R * 64));
-    HIPCHK(S, dalloc(S, &d.xchg, (size_t)R * 6 * np));
+    HIPCHK(S, dalloc(S, &d.xchg, (size_t)R * 4 * np));
     HIPCHK(S, dalloc(S, &d.esum, R));
     HIPCHK(S, dalloc(S, &d.acc, (size_t)R * MAX_OBS * 2));
     HIPCHK(S, dalloc(S, &d.shift, MAX_OBS));
