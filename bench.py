@@ -241,7 +241,7 @@ def differentiation_bench(spec, iters):
 
 
 def pair_kernel_bench(pl, spec, pairs, launches=100):
-    """The plain path's pair-force kernel (k_nonbonded, all replicas in one launch) timed launch
+    """The plain path's force kernel (k_forces: pairs and bonded terms, all replicas in one launch) timed launch
     by launch with HIP events over one-step calls; the median is a step without a pair-list
     rebuild (the lists are rebuilt on one step in ten).  Its algorithmic rate counts each
     in-cutoff unordered pair once at FLOP_PAIR."""
@@ -262,7 +262,7 @@ def pair_kernel_bench(pl, spec, pairs, launches=100):
     fast = [x for x in per if x <= cut]
     med = float(np.median(fast)) * 1e-3
     achieved = pairs * FLOP_PAIR * R / med / 1e12
-    return dict(kernel="k_nonbonded", launches=len(per), launches_without_rebuild=len(fast), median_us=med * 1e6,
+    return dict(kernel="k_forces", launches=len(per), launches_without_rebuild=len(fast), median_us=med * 1e6,
                 median_all_us=1e3 * float(np.median(per)), max_us=1e3 * max(per), min_us=1e3 * min(per),
                 achieved_tflops=achieved, frac=achieved / PEAK_FP32_TFLOPS,
                 note="plain path, one launch for all 64 replicas; median of the launches without a pair-list "

@@ -478,17 +478,15 @@ static hipError_t write_params(gpr_system *S)
 static gpr_status launch_forces(gpr_system *S, int r_off, int nrep, long long s, int energy, int apply_b, int force_build,
                                 bool timed = false, bool clear_e = true)
 {
-    const int BTB = 256, BTN = 1024;
+    const int BTN = 1024;
     if (force_build) s = S->s - 1;             // a forced build counts as built in the previous step
     if (energy && force_build && clear_e) {
         HIPCHK(S, hipMemsetAsync(S->d.E + r_off, 0, sizeof(long long) * nrep, S->stream));
     }
-    dim3 gb((S->n + BTB - 1) / BTB, nrep);
-    hipLaunchKernelGGL(k_bonded, gb, dim3(BTB), 3 * BTB * sizeof(long long), S->stream, S->d_dev, s, r_off, energy);
-    LAUNCHCHK(S);
     dim3 gn((S->n * P + BTN - 1) / BTN, nrep);
     if (timed) HIPCHK(S, prof_begin(S));
-    hipLaunchKernelGGL(k_nonbonded, gn, dim3(BTN), S->lds_nb, S->stream, S->d_dev, s, r_off, energy, apply_b, force_build);
+    hipLaunchKernelGGL(k_forces, gn, dim3(BTN), S->lds_nb, S->stream, S->d_dev, s, r_off, energy, apply_b,
+                       force_build);
     LAUNCHCHK(S);
     if (timed) HIPCHK(S, prof_end(S));
     return GPR_OK;
@@ -614,13 +612,10 @@ static gpr_status launch_persist(gpr_system *S, PersistBatch &pb, int nblocks, i
 // unless the step samples.
 static gpr_status launch_step_dc(gpr_system *S, int nrep, int code, int phase, int k, hipStream_t st)
 {
-    const int BTI = 256, BTB = 256, BTN = 1024;
+    const int BTI = 256, BTN = 1024;
     hipLaunchKernelGGL(k_integrate, dim3((S->n + BTI - 1) / BTI, nrep), dim3(BTI), 0, st, S->d_dev, (long long)k, 0, code);
     LAUNCHCHK(S);
-    hipLaunchKernelGGL(k_bonded, dim3((S->n + BTB - 1) / BTB, nrep), dim3(BTB), 3 * BTB * sizeof(long long), st, S->d_dev,
-                       (long long)k, 0, code);
-    LAUNCHCHK(S);
-    hipLaunchKernelGGL(k_nonbonded, dim3((S->n * P + BTN - 1) / BTN, nrep), dim3(BTN), S->lds_nb, st, S->d_dev,
+    hipLaunchKernelGGL(k_forces, dim3((S->n * P + BTN - 1) / BTN, nrep), dim3(BTN), S->lds_nb, st, S->d_dev,
                        (long long)k, 0, code, 1, 0);
     LAUNCHCHK(S);
     if (code == DCLK_SAMPLE && nrep > 1) {
@@ -1188,7 +1183,8 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
 
     // LDS budgets
     const int nblk = (n + BLK - 1) / BLK;
-    S->lds_nb = (size_t)np * 24 + (size_t)nblk * 16 + (size_t)16 * WBLK * 4;
+    // the replica, then the boxes and scratch of a rebuild, or the force sums of 256 atoms over them
+    S->lds_nb = (size_t)np * 24 + std::max((size_t)nblk * 16 + (size_t)16 * WBLK * 4, (size_t)256 * 3 * sizeof(long long));
     S->lds_stage = (size_t)np * 16;
     int dev = 0, maxlds = 0;
     HIPCHK(S, hipGetDevice(&dev));
@@ -1196,7 +1192,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     S->maxlds = maxlds;
     if ((int)S->lds_nb > maxlds || (int)S->lds_stage > maxlds)
         return fail(S, GPR_EINVAL, "system too large for the LDS-staged pair kernel");
-    HIPCHK(S, hipFuncSetAttribute((const void *)k_nonbonded, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_nb));
+    HIPCHK(S, hipFuncSetAttribute((const void *)k_forces, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_nb));
     HIPCHK(S, hipFuncSetAttribute((const void *)k_grad_nb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_nb));
     HIPCHK(S, hipFuncSetAttribute((const void *)k_obs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_stage));
     HIPCHK(S, hipFuncSetAttribute((const void *)k_state, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_stage));

@@ -1,12 +1,13 @@
 // gpr_kernels.hip -- gfx950 kernels of the Gen.ParRep hot path.
 //
 // Two stepping paths share every arithmetic routine, so they give bit-identical results:
-//   plain      : per step, k_integrate (B A O A of Eq. 1's BAOAB discretisation),
-//                k_bonded, k_nonbonded (pair forces, the closing B kick, pair-list rebuild
-//                when due); observables and state tests as separate launches;
-//   persistent : k_persist advances one replica per workgroup for a whole check period,
-//                with its positions and parameters resident in LDS and its velocities and
-//                forces in registers.
+//   plain      : per step, k_integrate (B A O A of Eq. 1's BAOAB discretisation) and k_forces (bonded
+//                and pair forces, the closing B kick, pair-list rebuild when due); observables and
+//                state tests as separate launches;
+//   persistent : k_persist (k_persist_batch: several systems) advances each replica by one to eight
+//                workgroups for a whole check period, its positions, parameters, velocities and
+//                forces in LDS; k_persist_small does so for small replicas, one workgroup each, with
+//                their bonded terms in LDS too and no pair lists.
 // Gen.ParRep bookkeeping (Sec. 2.4.1 branching and Gelman-Rubin, Sec. 2.4.2 exit vote)
 // runs in k_check / k_clone once per check.
 #include "gpr_kernels.h"
@@ -875,58 +876,16 @@ __global__ void __launch_bounds__(256) k_integrate(const Dev *__restrict__ Sp, l
     }
 }
 
-// Bonded forces of atom range [blockIdx.x * blockDim.x, +blockDim.x) of replica r:
-// fixed-point LDS accumulation, then a plain store that initialises F for the step.
-__global__ void __launch_bounds__(256) k_bonded(const Dev *__restrict__ Sp, long long s, int r_off, int energy)
-{
-    const Dev &S = *Sp;
-    step_args(S, s, energy);
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    long long *fa = (long long *)lds_raw;
-    __shared__ long long e_acc;
-    const int r = r_off + blockIdx.y;
-    const int len = blockDim.x;
-    const int a0 = blockIdx.x * len, a1 = min(S.n, a0 + len);
-    const int tid = threadIdx.x;
-    for (int k = tid; k < 3 * len; k += len) fa[k] = 0;
-    if (tid == 0) e_acc = 0;
-    __syncthreads();
-    const size_t b = (size_t)r * 3 * S.np;
-    if (S.kind == KIND_TOY) {
-        if (tid == 0 && a0 == 0) {
-            float fx, fy;
-            const float u = toy_force(S.x[b], S.x[b + S.np], fx, fy);
-            fa[0] = fix_f(fx);
-            fa[len] = fix_f(fy);
-            if (energy) e_acc = fix_f(u);
-        }
-    } else {
-        const int u0 = gconst(S.pl_first)[blockIdx.x], u1 = gconst(S.pl_first)[blockIdx.x + 1];
-        const PosGlob pos{gconst(S.x) + b, S.np};
-        const ForceLDS F{fa, a0, 1, len};
-        if (energy) {
-            const long long e = bonded_units<true>(S.pl_bi, S.pl_bp, u0, u1, pos, F, uni(tid >> 6), len >> 6, tid & 63);
-            if (e != 0) lds_add(&e_acc, e);
-        } else {
-            bonded_units<false>(S.pl_bi, S.pl_bp, u0, u1, pos, F, uni(tid >> 6), len >> 6, tid & 63);
-        }
-    }
-    __syncthreads();
-    const int a = a0 + tid;
-    if (a < a1) {
-        S.F[b + a] = fa[tid];
-        S.F[b + S.np + a] = fa[len + tid];
-        S.F[b + 2 * S.np + a] = fa[2 * len + tid];
-    }
-    if (energy && tid == 0 && e_acc != 0) atomicAdd((unsigned long long *)&S.E[r], (unsigned long long)e_acc);
-}
-
-// Nonbonded forces of atoms [blockIdx.x * blockDim.x / P, ...) of replica r (P lanes per
-// atom), added to the bonded forces; then the closing B kick (apply_b).  The pair lists of
-// the block's atoms are rebuilt first when due (period, displacement guard, force_build).
-// (At most 64 registers, so that two workgroups share a compute unit where their LDS fits, one staging
-// or waiting while the other computes: 85 -> 66 us for 64 replicas of 2,432 atoms with a rebuild.)
-__global__ void __launch_bounds__(1024, 8) k_nonbonded(const Dev *__restrict__ Sp, long long s, int r_off, int energy, int apply_b,
+// Forces of atoms [blockIdx.x * blockDim.x / P, ...) of replica r (256 atoms, P lanes each), then the
+// closing B kick (apply_b).  The block stages the replica, rebuilds its atoms' pair lists first when
+// due (period, displacement guard, force_build), and sums the bonded units of its atom range and
+// their pairs in LDS fixed point, over the boxes and scratch of the rebuild.  Bound by the search
+// when lists are rebuilt, else by the staging and the pairs.  Bonded terms in a kernel of their own
+// waited for scattered positions from memory: 7.0 + 21.4 -> 22.5 us a step (5,200 atoms x 12
+// replicas), 13.9 + 66.0 -> 70.6 us for 64 replicas of 2,432 atoms with a rebuild.  At most 64
+// registers, so that two workgroups share a compute unit where their LDS fits, one staging or
+// waiting while the other computes (89 us with one).
+__global__ void __launch_bounds__(1024, 8) k_forces(const Dev *__restrict__ Sp, long long s, int r_off, int energy, int apply_b,
                                                    int force_build)
 {
     step_args(*Sp, s, energy);
@@ -985,29 +944,43 @@ __global__ void __launch_bounds__(1024, 8) k_nonbonded(const Dev *__restrict__ S
         __syncthreads();
     }
     long long eatom = 0;
-    if (i < S.n) {
-        float4 f = nb_lane(nb_consts(S), r, i, q, xs, pp, energy != 0);
-        f.x = quad_sum(f.x);
-        f.y = quad_sum(f.y);
-        f.z = quad_sum(f.z);
-        if (energy) f.w = quad_sum(f.w);
-        if (q == 0) {
-            GPR_GLOBAL long long *Fp = gmut(S.F) + b;
-            GPR_GLOBAL float *V = gmut(S.v) + b;
-            const long long Fx = Fp[i] + fix_f(f.x);
-            const long long Fy = Fp[S.np + i] + fix_f(f.y);
-            const long long Fz = Fp[2 * S.np + i] + fix_f(f.z);
-            Fp[i] = Fx; Fp[S.np + i] = Fy; Fp[2 * S.np + i] = Fz;
-            const float fx = unfix_f(Fx), fy = unfix_f(Fy), fz = unfix_f(Fz);
-            if (bad_force(fx) || bad_force(fy) || bad_force(fz)) atomicOr(&S.err[ERR_UNSTABLE], 1);
-            if (apply_b) {
-                const float im = gld(gconst(S.prm) + i).w, h = S.h;
-                V[i] = kick(V[i], fx, h, im);
-                V[S.np + i] = kick(V[S.np + i], fy, h, im);
-                V[2 * S.np + i] = kick(V[2 * S.np + i], fz, h, im);
-            }
-            if (energy) eatom = fix_f(f.w);
+    const int a0 = blockIdx.x * (nthr / P), l = tid / P, na = nthr / P;
+    long long *const fa = (long long *)box;                // [na][3]
+    for (int k = tid; k < 3 * na; k += nthr) fa[k] = 0;
+    __syncthreads();
+    if (S.kind == KIND_TOY) {
+        if (tid == 0 && a0 == 0) {
+            float fx, fy;
+            const float u = toy_force(xs[0].x, xs[0].y, fx, fy);
+            fa[0] = fix_f(fx);
+            fa[1] = fix_f(fy);
+            eatom = fix_f(u);
         }
+    } else {
+        // every wave its share of the bonded units, then its pairs
+        const int wv = uni(tid >> 6), nwv = nthr >> 6, u0 = gconst(S.pl_first)[blockIdx.x], u1 = gconst(S.pl_first)[blockIdx.x + 1];
+        const ForceLDS F{fa, a0, 3, 1};
+        if (energy) eatom = bonded_units<true>(S.pl_bi, S.pl_bp, u0, u1, PosLDS{xs}, F, wv, nwv, tid & 63);
+        else bonded_units<false>(S.pl_bi, S.pl_bp, u0, u1, PosLDS{xs}, F, wv, nwv, tid & 63);
+        if (i < S.n) {
+            float4 f = nb_lane(nb_consts(S), r, i, q, xs, pp, energy != 0);
+            f.x = quad_sum(f.x);
+            f.y = quad_sum(f.y);
+            f.z = quad_sum(f.z);
+            if (energy) f.w = quad_sum(f.w);
+            if (q < 3) lds_add(&fa[3 * l + q], fix_f(q == 0 ? f.x : (q == 1 ? f.y : f.z)));
+            else if (energy) eatom += fix_f(f.w);
+        }
+    }
+    __syncthreads();
+    for (int k = tid; k < 3 * na; k += nthr) {
+        const int d = k / na, c = k - d * na, a = a0 + c;
+        if (a >= S.n) continue;
+        const long long Fi = fa[3 * c + d];
+        const float f = unfix_f(Fi);
+        gmut(S.F)[b + d * S.np + a] = Fi;
+        if (bad_force(f)) atomicOr(&S.err[ERR_UNSTABLE], 1);
+        if (apply_b) gmut(S.v)[b + d * S.np + a] = kick(gmut(S.v)[b + d * S.np + a], f, S.h, gld(gconst(S.prm) + a).w);
     }
     if (energy) {
         eatom = wave_sum_ll(eatom);
