@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <climits>
 #include <new>
 #include <string>
 #include <vector>
@@ -543,10 +544,15 @@ static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt,
     }
     int nsets = std::min(nrep, cap_blocks / G);
     if (nsets < 1) return fail(S, GPR_EINVAL, "a replica's workgroups do not fit on the device at once");
+    // a multiple of eight sets, for their placement: more (the rest idle) where they fit, else fewer
+    // where that adds no round (a second round of launches doubles the time: 12 replicas of 1,200
+    // atoms used to run as 8 and then 4)
     it.xcd = 0;
     if (G > 1 && nsets >= 8) {
-        nsets -= nsets % 8;
-        it.xcd = 1;
+        const int up = (nsets + 7) / 8 * 8, down = nsets / 8 * 8;
+        auto rounds = [&](int sets) { return (nrep + sets - 1) / sets; };
+        if (up * G <= cap_blocks) { nsets = up; it.xcd = 1; }
+        else if (rounds(down) == rounds(nsets)) { nsets = down; it.xcd = 1; }
     }
     it.nsets = nsets;
     nblocks = nsets * G;
@@ -2287,11 +2293,12 @@ static gpr_status batch_check(gpr_system *const *systems, int32_t nsys)
     return GPR_OK;
 }
 
-// block size and LDS of a shared launch (the largest of the systems') and the workgroups the
-// device holds at once with them; w[k]: work estimate of one step of all of system k's replicas
+// block size of a shared launch (the largest of the systems'), LDS (with their own splits, then
+// of the layout), the workgroups the device holds at once and the most LDS that keeps that number;
+// w[k]: work estimate of one step of one of system k's replicas
 struct BatchShape {
     int bt = 64;
-    size_t lds = 0;
+    size_t lds0 = 0, lds = 0, lds_most = 0;
     int capacity = 0;
     std::vector<double> w;
 };
@@ -2302,7 +2309,7 @@ static gpr_status batch_shape(gpr_system *const *systems, int32_t nsys, BatchSha
     for (int k = 0; k < nsys; ++k) {
         gpr_system *S = systems[k];
         sh.bt = std::max(sh.bt, S->bt_persist);
-        sh.lds = std::max(sh.lds, persist_lds(S->n, S->np, S->split));
+        sh.lds0 = std::max(sh.lds0, persist_lds(S->n, S->np, S->split));
         double per = 0.0;
         for (double x : S->work) per += x;
         sh.w[k] = per;
@@ -2310,46 +2317,71 @@ static gpr_status batch_shape(gpr_system *const *systems, int32_t nsys, BatchSha
     int dev = 0, cus = 0, per_cu = 0;
     HIPCHK(systems[0], hipGetDevice(&dev));
     HIPCHK(systems[0], hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHK(systems[0], hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_persist_batch, sh.bt, sh.lds));
+    HIPCHK(systems[0], hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_persist_batch, sh.bt, sh.lds0));
     sh.capacity = per_cu * cus;
+    sh.lds_most = per_cu == 1 ? (size_t)systems[0]->maxlds_persist : sh.lds0;
     return GPR_OK;
 }
 
-// Items of a shared launch for the systems with nrep[k] > 0 replicas stepped: sets per system
-// one each to begin with; then, one set at a time, more for the system whose replicas would
-// take longest, estimated as (replicas per set) x (time of one replica-step on one workgroup)
-// / G, that time modelled as 5 us of fixed latency plus 2.8e-4 us per unit of the per-atom
-// work estimate (both from measured step times).  slot[k]: the item of system k (-1: none).
+// Items of a shared launch for the systems with nrep[k] > 0 replicas stepped: workgroups per replica
+// and sets for each, so that the longest takes the least time by the estimate (rounds of replicas
+// per set) x (us of one replica's step on G workgroups).  That is 4 + 1.7 (G > 1) + (1.55e-4 + 1e-5 G)
+// w / G, within 8 % of steps measured from 160 to 4,600 atoms on 1 to 8 workgroups.  The splits are
+// the system's own where the caller or the autotuner chose it.  (One set at a time for the longest,
+// with each system's own split: 45.8 us a step for the mix of 22, 300, 1,200 and 2,432 atoms with 48
+// replicas each; this way 38.)  slot[k]: the item of system k (-1: none).
 static gpr_status batch_layout(gpr_system *const *systems, int32_t nsys, const std::vector<int> &nrep,
-                               const BatchShape &sh, PersistBatch &pb, std::vector<int> &slot, int &nblocks)
+                               BatchShape &sh, PersistBatch &pb, std::vector<int> &slot, int &nblocks)
 {
     gpr_system *S0 = systems[0];
-    std::vector<int> sets(nsys, 0);
-    int used = 0;
-    for (int k = 0; k < nsys; ++k)
-        if (nrep[k] > 0) { sets[k] = 1; used += systems[k]->groups; }
-    if (used > sh.capacity) return fail(S0, GPR_EINVAL, "the systems' workgroups do not fit on the device at once");
-    auto est = [&](int k, int ns) {
-        const double t1 = 5.0 + 2.8e-4 * sh.w[k];
-        return (double)((nrep[k] + ns - 1) / ns) * t1 / systems[k]->groups;
+    struct Choice {
+        const Split *sp = nullptr;
+        int sets = 0;
     };
-    for (;;) {
-        int pick = -1;
+    std::vector<Choice> pick(nsys);
+    // the fewest workgroups with which every system takes at most T
+    auto need = [&](double T) {
+        long used = 0;
         for (int k = 0; k < nsys; ++k) {
-            if (nrep[k] <= 0 || sets[k] >= nrep[k] || used + systems[k]->groups > sh.capacity) continue;
-            if (pick < 0 || est(k, sets[k]) > est(pick, sets[pick])) pick = k;
+            if (nrep[k] <= 0) continue;
+            const gpr_system *S = systems[k];
+            pick[k] = Choice{};
+            for (int j = 0; j < 4; ++j) {
+                const int G = 1 << j;
+                const Split *sp = G == S->groups ? &S->split : &S->splits[j];
+                if (G != S->groups && (S->groups_from != 0 || !S->split_ok[j] || S->n < 64 * G)) continue;
+                if (persist_lds(S->n, S->np, *sp) > sh.lds_most) continue;
+                const double t = 4.0 + (G > 1 ? 1.7 : 0.0) + (1.55e-4 + 1e-5 * G) * sh.w[k] / G;
+                const long rounds = (long)(T / t);
+                if (rounds < 1) continue;
+                const int sets = (int)((nrep[k] + rounds - 1) / rounds);
+                if (!pick[k].sp || (long)sets * G < (long)pick[k].sets * pick[k].sp->G) pick[k] = {sp, sets};
+            }
+            if (!pick[k].sp) return LONG_MAX;
+            used += (long)pick[k].sets * pick[k].sp->G;
         }
-        if (pick < 0) break;
-        sets[pick] += 1;
-        used += systems[pick]->groups;
+        return used;
+    };
+    double lo = 0.0, hi = 1.0;
+    while (hi < 1e12 && need(hi) > sh.capacity) hi *= 2.0;
+    if (need(hi) > sh.capacity) return fail(S0, GPR_EINVAL, "the systems' workgroups do not fit on the device at once");
+    for (int it = 0; it < 40 && hi - lo > 1e-3 * hi; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        (need(mid) > sh.capacity ? lo : hi) = mid;
     }
+    (void)need(hi);
     std::vector<PersistItem> items(nsys);
     std::vector<int> nb(nsys, 0);
+    sh.lds = 0;
     for (int k = 0; k < nsys; ++k) {
         if (nrep[k] <= 0) continue;
-        gpr_status rc = persist_item(systems[k], systems[k]->split, nrep[k], sh.bt, sh.lds, sets[k] * systems[k]->groups,
-                                     items[k], nb[k]);
+        gpr_system *S = systems[k];
+        const Split &sp = *pick[k].sp;
+        gpr_status rc = persist_item(S, sp, nrep[k], sh.bt, sh.lds_most, pick[k].sets * sp.G, items[k], nb[k]);
         if (rc) return rc;
+        const size_t with = (size_t)persist_off(S->n, S->np, sp.lmax).end;
+        items[k].noise_ahead = with <= sh.lds_most && S->kind != GPR_KIND_TOY2D;   // (drawn beside the pair tasks)
+        sh.lds = std::max(sh.lds, items[k].noise_ahead ? with : persist_lds(S->n, S->np, sp));
     }
     slot.assign(nsys, -1);
     pb = PersistBatch{};
