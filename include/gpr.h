@@ -136,8 +136,9 @@ typedef struct gpr_system_desc {
     double  skin;                /* pair-list skin (nm), cutoff > 0 */
     int32_t nlist_period;        /* pair lists are at most this many steps old (persistent path: per replica;
                                     plain path: on the steps s with s+1 a multiple of it, for all replicas);
-                                    rebuilt earlier when an atom has moved more than skin/2 since the last
-                                    build.  Results do not depend on when lists are rebuilt. */
+                                    rebuilt earlier when an atom has moved further than its list margin since
+                                    the last build: half the skin for atoms of less than four times the lightest's
+                                    mass, less for heavier ones.  Results do not depend on when lists are rebuilt. */
 
     int32_t n_bonds;     const int32_t *bond_atoms;     const double *bond_r0;      const double *bond_k;
     int32_t n_angles;    const int32_t *angle_atoms;    const double *angle_theta0; const double *angle_k;
@@ -402,7 +403,7 @@ gpr_status gpr_batch_run(gpr_system *const *systems, int32_t nsys, gpr_batch_op 
 gpr_status gpr_set_cycles(gpr_system *sys, int32_t cycles);
 
 /* Timing of the dominant stepping kernel (the persistent kernel on the persistent path,
- * the pair-force kernel on the plain path) with HIP events recorded on the system's
+ * the force kernel on the plain path) with HIP events recorded on the system's
  * stream around each launch.  gpr_profile enables (1) or disables (0) recording and
  * clears the totals; gpr_profile_read waits for the stream and returns the summed
  * duration in ms and the number of launches timed since the last clear. */
@@ -412,7 +413,7 @@ gpr_status gpr_profile_read(gpr_system *sys, double *ms, int64_t *launches);
 /* Phase timers of the persistent kernel, for measurement: only the library's timer build
  * (libgpr_hip_probe.so, the same sources built with GPR_PHASE_PROBE) records them; the
  * product build returns GPR_EINVAL.  out ([R][8][11] doubles, host, caller-owned) receives per
- * replica r and workgroup g of its replica (rows g >= G stay 0): the microseconds spent since
+ * replica r and workgroup g < 8 of its replica (rows g >= G stay 0): the microseconds spent since
  * the last read in the launch prologue (staging), the integrator (B A O A and the position
  * stores), the exchange (the other groups' positions), the pair-list rebuild, the forces
  * (bonded and pair terms), the step's tail (closing B, samples) and the epilogue (write back);

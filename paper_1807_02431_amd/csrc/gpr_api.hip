@@ -40,8 +40,8 @@ struct gpr_system {
     int bt_persist = 0;
     int groups = 1;            // workgroups per replica on the persistent path
     Split split{};             // their atom ranges
-    Split splits[4]{};         // the atom ranges with 1, 2, 4 and 8 workgroups per replica
-    bool split_ok[4]{};        // whether a workgroup of that split fits on a compute unit
+    Split splits[NSPLIT]{};    // the atom ranges with 1, 2, 4, ... MAX_G workgroups per replica
+    bool split_ok[NSPLIT]{};        // whether a workgroup of that split fits on a compute unit
     // whose choice the launch shape is: 0 the library's, for the replicas of each launch
     // (run_shape), 1 the autotuner's, for launches of all replicas, 2 the caller's, for every launch
     int bt_from = 0, groups_from = 0;
@@ -55,7 +55,7 @@ struct gpr_system {
         uint2 *bi = nullptr;
         float4 *bp = nullptr;
     };
-    Units units_plain, units_split[4];
+    Units units_plain, units_split[NSPLIT];
     // force-field parameters as the caller gave them (gpr_set_params rewrites the device copies)
     std::vector<double> mass_h, eps_h, sig_h, q_h, tor_k_h, tor_phi0_h;
     std::vector<int> tor_n_h, tor_order, p14_order;   // sorted term -> caller's index
@@ -259,7 +259,12 @@ static Split make_split(const std::vector<double> &work, int n, int np, int G)
     return sp;
 }
 
-static int split_index(int G) { return G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3; }
+static int split_index(int G)
+{
+    int k = 0;
+    while ((1 << k) < G) ++k;
+    return k;
+}
 
 static size_t persist_lds(int n, int np, const Split &sp) { return (size_t)persist_off(n, np, sp.lmax).gn; }
 
@@ -290,8 +295,9 @@ static int small_units(const gpr_system *S)
 // the autotuner) chose it:
 //   workgroups per replica: those of a launch of all replicas, doubled while all workgroups of the
 //   launch still get a compute unit of their own and a group keeps 64 atoms (measured, us per step:
-//   one replica of 2,432 atoms 20.7 with 4 groups, 14.9 with 8; 8 replicas of 1,200 atoms 15.3 and
-//   12.1; 24 replicas of 300 atoms 10.6, 9.3, 8.3 and 8.6 with 1, 2, 4 and 8, where 8 leave 38 atoms);
+//   one replica of 2,432 atoms 12.1 with 8 groups, 8.9 with 16, 8.3 with 32; of 4,600 atoms 19.3,
+//   13.3 and 10.0; 8 replicas of 1,200 atoms 9.4 with 8, 8.2 with 16; 24 replicas of 300 atoms 10.6,
+//   9.3, 8.3 and 8.6 with 1, 2, 4 and 8 when that line was drawn, where 8 leave 38 atoms);
 //   threads of k_persist_small: a wave per unit of a step's work, fewer where the replicas outnumber
 //   the compute units, so that they run side by side (16 waves fit on one at its register count;
 //   1,024 replicas of 22 atoms: 3.6 us per step with 4 waves each, 4.3 with 2, 4.9 with 7).
@@ -317,7 +323,7 @@ static RunShape run_shape(const gpr_system *S, int nrep)
         return sh;
     }
     if (!chosen(S->groups_from))
-        for (int k = 1; k < 4; ++k) {
+        for (int k = 1; k < NSPLIT; ++k) {
             const int G = 1 << k;
             if (G > sh.sp->G && S->split_ok[k] && S->n >= 64 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
         }
@@ -570,7 +576,7 @@ static gpr_status check_layout(gpr_system *S, const PersistBatch &pb, int nblock
     for (int k = 0; k < pb.nitems; ++k) {
         const PersistItem &it = pb.it[k];
         const Split &sp = it.sp;
-        if (it.boff != next || it.nsets < 1 || it.nrep < 1 || sp.G < 1 || sp.G > 8 || !it.dev)
+        if (it.boff != next || it.nsets < 1 || it.nrep < 1 || sp.G < 1 || sp.G > MAX_G || !it.dev)
             return fail(S, GPR_EDEVICE, "persistent launch layout: item placement");
         if (!single && k > 0 && pb.it[k - 1].boff >= it.boff) return fail(S, GPR_EDEVICE, "persistent launch layout: item order");
         const int n = sp.bnd[sp.G];
@@ -1247,7 +1253,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
             all_at_once = ok && (G == 1 || (long)R * G <= (long)per_cu * cus);
             return e;
         };
-        for (int k = 0; k < 4; ++k) S->splits[k] = make_split(S->work, n, np, 1 << k);
+        for (int k = 0; k < NSPLIT; ++k) S->splits[k] = make_split(S->work, n, np, 1 << k);
         int G = 1;
         bool ok = false, all = false;
         for (; G <= 8; G *= 2) {
@@ -1267,7 +1273,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         }
         S->groups = G;
         S->split = S->splits[split_index(G)];
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NSPLIT; ++k) {
             bool all2 = false;
             HIPCHK(S, usable(1 << k, S->split_ok[k], all2));
         }

@@ -43,11 +43,12 @@ constexpr int PHASE_MAX_R = 4096, PHASE_MAX_G = 8;
 hipError_t phase_take(unsigned long long *out, int R, hipStream_t st);
 
 // atom ranges of the workgroups of one replica on the persistent path
+constexpr int MAX_G = 32, NSPLIT = 6;
 struct Split {
-    int G;          // workgroups per replica (1, 2, 4 or 8)
+    int G;          // workgroups per replica (1, 2, 4, ... MAX_G)
     int lmax;       // LDS length of the per-group arrays: the largest range, rounded up to 16
-    int bnd[9];     // group g owns atoms [bnd[g], bnd[g + 1]); every bnd[g] < n is a multiple of 16
-    int bu[9];      // its bonded units are [bu[g], bu[g + 1]) of the records bi, bp
+    int bnd[MAX_G + 1];   // group g owns atoms [bnd[g], bnd[g + 1]); every bnd[g] < n is a multiple of 16
+    int bu[MAX_G + 1];   // its bonded units are [bu[g], bu[g + 1]) of the records bi, bp
     const uint2 *bi;
     const float4 *bp;
 };

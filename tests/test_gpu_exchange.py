@@ -24,3 +24,19 @@ def test_exchange_matches_one_group(kind, n, bt, groups, chunks):
         a.advance(k)
     b.advance(sum(chunks))
     _same(a, b)
+
+
+@pytest.mark.parametrize("n,R", [(1024, 2), (1100, 5), (2047, 3), (2100, 8), (4600, 2)])
+def test_many_groups_for_few_replicas(n, R):
+    """Launches of few replicas take up to 32 workgroups each by themselves: the same walker, states and
+    samples as on the caller's shape."""
+    import paper_1807_02431_amd as gpr
+    spec = dict(_spec("rl", n), n_replicas=R, t_check_dephase=20)
+    print("many groups", n, R, flush=True)
+    a = gpr.System(spec, path=gpr.PATH_PERSISTENT)
+    b = gpr.System(spec, path=gpr.PATH_PERSISTENT)
+    b.set_launch(1024, 8)
+    for _ in range(2):
+        assert a.decorrelate(40, max_steps=40) == b.decorrelate(40, max_steps=40)
+        assert np.array_equal(a.advance(25), b.advance(25))
+    _same(a, b)
