@@ -294,10 +294,10 @@ static int small_units(const gpr_system *S)
 // Launch shape of a persistent launch of one system's first nrep replicas.  Unless the caller (or
 // the autotuner) chose it:
 //   workgroups per replica: those of a launch of all replicas, doubled while all workgroups of the
-//   launch still get a compute unit of their own and a group keeps 64 atoms (measured, us per step:
+//   launch still get a compute unit of their own and a group keeps 32 atoms (measured, us per step:
 //   one replica of 2,432 atoms 12.1 with 8 groups, 8.9 with 16, 8.3 with 32; of 4,600 atoms 19.3,
-//   13.3 and 10.0; 8 replicas of 1,200 atoms 9.4 with 8, 8.2 with 16; 24 replicas of 300 atoms 10.6,
-//   9.3, 8.3 and 8.6 with 1, 2, 4 and 8 when that line was drawn, where 8 leave 38 atoms);
+//   13.3 and 10.0; 24 replicas of 300 atoms 7.3, 6.4 and 5.8 with 2, 4 and 8; with no fewer than 64,
+//   32 and 16 atoms to a group, two replicas of 161 atoms 6.7, 5.7, 5.7 and of 1,000 8.3, 7.8, 7.6);
 //   threads of k_persist_small: a wave per unit of a step's work, fewer where the replicas outnumber
 //   the compute units, so that they run side by side (16 waves fit on one at its register count;
 //   1,024 replicas of 22 atoms: 3.6 us per step with 4 waves each, 4.3 with 2, 4.9 with 7).
@@ -325,7 +325,7 @@ static RunShape run_shape(const gpr_system *S, int nrep)
     if (!chosen(S->groups_from))
         for (int k = 1; k < NSPLIT; ++k) {
             const int G = 1 << k;
-            if (G > sh.sp->G && S->split_ok[k] && S->n >= 64 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
+            if (G > sh.sp->G && S->split_ok[k] && S->n >= 32 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
         }
     sh.noise_ahead = noise_fits(S->n, S->np, *sh.sp, sh.bt, S->maxlds_persist);
     sh.lds = sh.noise_ahead ? (size_t)persist_off(S->n, S->np, sh.sp->lmax).end : persist_lds(S->n, S->np, *sh.sp);
