@@ -212,8 +212,8 @@ const char *gpr_last_error(const gpr_system *sys);
 /* Sets the HIP stream (hipStream_t passed as void*) on which all later calls run. */
 gpr_status gpr_set_stream(gpr_system *sys, void *hip_stream);
 
-/* Stepping path: GPR_PATH_PLAIN launches separate kernels every step (list build every
- * nlist_period, BAOAB, bonded, nonbonded); GPR_PATH_PERSISTENT advances whole check
+/* Stepping path: GPR_PATH_PLAIN launches separate kernels every step (BAOAB; forces,
+ * with the list build when due); GPR_PATH_PERSISTENT advances whole check
  * periods in one launch with the replica state held on chip.  Results are bit-identical.
  * EINVAL for the persistent path when no split of a replica over 1, 2, 4 or 8 workgroups fits
  * the device. */
@@ -222,7 +222,8 @@ gpr_status gpr_set_stream(gpr_system *sys, void *hip_stream);
 gpr_status gpr_set_path(gpr_system *sys, int32_t path);
 /* Launch shape of the persistent path: threads per workgroup (multiple of 64, <= 1024) and
  * workgroups per replica (1, 2, 4 or 8; a replica's atoms are split between its workgroups,
- * which exchange positions every step).  0 keeps the current value.  When the replicas times
+ * which exchange positions every step; launches of few replicas take up to 32 by themselves).
+ * 0 keeps the current value.  When the replicas times
  * the workgroups per replica exceed what the device holds at once, sets of workgroups take the
  * replicas in turn.  EINVAL, with nothing changed, if one workgroup's share of a replica does
  * not fit in LDS (large systems need several workgroups per replica) or a workgroup of that

@@ -311,7 +311,9 @@ __device__ __constant__ const PickTable pick_table = make_pick();
 // permutes whose selectors the lanes hold (entry `lane` of the table) and read from each other.
 // Excluded partners within 32 atoms (and the atom itself) are dropped only in tiles that may hold
 // some; farther ones are merged out against the atom's ascending list far_j.
-// Bound by VALU issue: about 27 instructions per tile and 17 tiles a task on the 2,432-atom system.
+// Bound by VALU issue: about 27 instructions per tile, 16 tiles a task on the 2,432-atom system; of a
+// rebuild's 30 us there (four groups) the tasks take 22: the scattered stores of finished groups 7,
+// the tiles 6, culling and a task's set-up 5, the exclusions 4.
 // UNR tiles are read at a time (more registers, fewer exposed LDS latencies).
 template <int UNR, bool PAD>
 __device__ __forceinline__ int search_task(const GPR_CONST Dev &S, int r, int iw, int iend, const GPR_LDS gv_f4 *xs,
