@@ -536,7 +536,7 @@ def main():
         nb_ms, nb_n = pl.profile_read()
         pl.profile(False)
         plain = dict(replica_steps_per_s=R * args.steps / t_pl, atom_steps_per_s=R * n * args.steps / t_pl,
-                     ms_per_step=1e3 * t_pl / args.steps, launches_per_step=3,
+                     ms_per_step=1e3 * t_pl / args.steps, launches_per_step=2,
                      median_ms_per_step=1e3 * float(np.median(reps_pl)) / args.steps,
                      pair_kernel_us=1e3 * nb_ms / max(nb_n, 1))
         print("# plain path: pair-force kernel launch by launch", file=sys.stderr, flush=True)
