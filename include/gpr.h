@@ -135,7 +135,8 @@ typedef struct gpr_system_desc {
     double  eps_rf;              /* reaction-field dielectric (cutoff > 0) */
     double  skin;                /* pair-list skin (nm), cutoff > 0 */
     int32_t nlist_period;        /* pair lists are at most this many steps old (persistent path: per replica;
-                                    plain path: on the steps s with s+1 a multiple of it, for all replicas);
+                                    plain path: on the steps s with s+1 a multiple of it, for all replicas,
+                                    and for all of a launch that the device holds at once when one of them must);
                                     rebuilt earlier when an atom has moved further than its list margin since
                                     the last build: half the skin for atoms of less than four times the lightest's
                                     mass, less for heavier ones.  Results do not depend on when lists are rebuilt. */

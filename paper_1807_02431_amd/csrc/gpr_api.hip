@@ -1181,6 +1181,11 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         d.pl_bp = S->units_plain.bp;
         HIPCHK(S, upload(S, (int **)&d.pl_first, S->units_plain.first));
     }
+    {
+        int dev = 0;
+        HIPCHK(S, hipGetDevice(&dev));
+        HIPCHK(S, hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev));
+    }
     HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
 
     // scratch for the per-check bookkeeping

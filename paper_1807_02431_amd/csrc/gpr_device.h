@@ -104,6 +104,7 @@ struct Dev {
     unsigned short *nbc;
     int Kg;                                // capacity of one sub-list, in groups of four
     int *guard;                            // [2][R] displacement guard flags by step parity
+    int cus;                               // compute units (k_forces: launches that fit them at once rebuild jointly)
     int *need_build;                       // [R]
     int *list_pad;                         // [R] 1: the replica's lists are the persistent search's (sub-lists
                                            // of an atom padded to one count), 0: the plain search's

@@ -883,7 +883,7 @@ __global__ void __launch_bounds__(256) k_integrate(const Dev *__restrict__ Sp, l
 // due (period, displacement guard, force_build), and sums the bonded units of its atom range and
 // their pairs in LDS fixed point, over the boxes and scratch of the rebuild.  Bound by the search
 // when lists are rebuilt, else by the staging and the pairs.  Bonded terms in a kernel of their own
-// waited for scattered positions from memory: 7.0 + 21.4 -> 22.5 us a step (5,200 atoms x 12
+// waited for scattered positions from memory: 7.0 + 21.4 -> 22.5 us a step (19.1 with joint rebuilds; 5,200 atoms x 12
 // replicas), 13.9 + 66.0 -> 70.6 us for 64 replicas of 2,432 atoms with a rebuild.  At most 64
 // registers, so that two workgroups share a compute unit where their LDS fits, one staging or
 // waiting while the other computes (89 us with one).
@@ -913,7 +913,14 @@ __global__ void __launch_bounds__(1024, 8) k_forces(const Dev *__restrict__ Sp, 
         long long lb = 0;
         if (S.cutoff_on) {
             lb = S.last_build[(s & 1) * S.R + r];
-            rebuild = (s + 1) % S.period == 0 || S.guard[(s & 1) * S.R + r] != 0;
+            const int *flags = S.guard + (s & 1) * S.R;
+            rebuild = (s + 1) % S.period == 0 || flags[r] != 0;
+            // A launch that fits the device at once lasts as long as its slowest block, so one replica
+            // that rebuilds costs as much as all: then they all do, and their next guards fall due
+            // together (12 replicas of 5,200 atoms: long launches on 20 % of the steps, not 36 %)
+            if ((int)(gridDim.x * gridDim.y) <= S.cus)
+                for (int q = tid & 63; q < (int)gridDim.y; q += 64) rebuild |= flags[r_off + q] != 0;
+            rebuild = __any(rebuild);
         }
         if (blockIdx.x == 0 && tid == 0) {
             S.guard[((s + 1) & 1) * S.R + r] = 0;

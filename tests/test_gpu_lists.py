@@ -91,3 +91,22 @@ def test_forces_do_not_depend_on_the_skin(n):
         # in units of 2^-24: r^2 3 and its root 2, up to the 14th power, the sum of sigmas 2, to the 12th,
         # and some 15 others, so 100 a pair; n for the sum
         assert np.abs(out[0][1][0] - ref).max() <= (100 + n) * 2.0 ** -24 * scale
+
+
+@pytest.mark.parametrize("R", [255, 256, 257, 300])
+def test_plain_launches_that_fit_the_device_rebuild_jointly(R):
+    """Around the number of workgroups up to which a plain launch rebuilds all of its lists as soon as one
+    replica has to: the states of the persistent path, with replicas that move very differently."""
+    import paper_1807_02431_amd as gpr
+    spec = dict(_spec("rl", 161), n_replicas=R, nlist_period=40)
+    print("joint rebuilds", R, flush=True)
+    a = gpr.System(spec, path=gpr.PATH_PLAIN)
+    b = gpr.System(spec, path=gpr.PATH_PERSISTENT)
+    for s in (a, b):
+        q, v = s.get_state(R - 1)
+        s.set_state(R - 1, q, 3.0 * v)         # the fastest comes last
+    for k in (1, 25, 40):
+        assert np.array_equal(a.advance(k), b.advance(k))
+    for r in (0, 1, R // 2, R - 2, R - 1):
+        for x, y in zip(a.get_state(r), b.get_state(r)):
+            assert np.array_equal(x, y), r
