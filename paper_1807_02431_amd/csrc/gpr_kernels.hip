@@ -1001,7 +1001,7 @@ __global__ void __launch_bounds__(1024, 8) k_forces(const Dev *__restrict__ Sp, 
 
 // observables of replicas r_off + blockIdx.x: accumulate (mode 0, workers), set the shift
 // c_j from replica 0 (mode 1), or write the values to out[r][MAX_OBS] (mode 2)
-__global__ void __launch_bounds__(256) k_obs(const Dev *__restrict__ Sp, int r_off, int mode, double *out, int k)
+__global__ void __launch_bounds__(1024) k_obs(const Dev *__restrict__ Sp, int r_off, int mode, double *out, int k)
 {
     const Dev &S = *Sp;
     if (mode == 3 && (S.clock[1] + k + 1) % S.t_gr != 0) return;    // step k of a device-clock cycle: no sample
