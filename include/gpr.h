@@ -282,7 +282,8 @@ gpr_status gpr_energy_forces_dev(gpr_system *sys, const float *x_dev, double *en
  * parameter gradient sum_r w[r] dU_r/dtheta into d_epsilon, d_sigma, d_charge (double
  * [n_atoms]) and d_torsion_k (double [n_torsions], caller's torsion order); device buffers, each
  * may be NULL.  Parameter sums are taken in 2^-32 fixed point, so they do not depend on the order
- * of the terms.  EINVAL for a toy system (when a parameter output is requested) or when an
+ * of the terms.  EDEVICE if pair lists that are rebuilt here (after steps or copies that kept none)
+ * overflow their capacity.  EINVAL for a toy system (when a parameter output is requested) or when an
  * epsilon is 0 and d_epsilon is requested (sqrt(eps_i eps_j) has no derivative there). */
 gpr_status gpr_energy_backward_dev(gpr_system *sys, const double *w_dev, float *d_x, double *d_epsilon,
                                    double *d_sigma, double *d_charge, double *d_torsion_k);

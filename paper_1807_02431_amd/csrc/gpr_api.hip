@@ -97,6 +97,8 @@ struct gpr_system {
     char *rb = nullptr;             // page-locked [rb_bytes]: results on their way to the caller (k_read)
     size_t rb_bytes = 0;
     bool gacc_dirty = false;        // a backward pass did not get to clear gacc
+    bool lists_old = false;         // some replica's pair lists may not be those of its positions (k_persist_small
+                                    // keeps none, copies take none along): stepping rebuilds them, k_grad_nb reads them
     double *obs_out = nullptr;
     int *donor = nullptr, *surv = nullptr;
     long long *fec = nullptr;
@@ -500,6 +502,7 @@ static gpr_status launch_forces(gpr_system *S, int r_off, int nrep, long long s,
                        force_build);
     LAUNCHCHK(S);
     if (timed) HIPCHK(S, prof_end(S));
+    if (force_build && r_off == 0 && nrep == S->R) S->lists_old = false;
     return GPR_OK;
 }
 
@@ -739,6 +742,7 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
             done += chunk;
         }
         S->s += nsteps;
+        if (sh.small) S->lists_old = true;
         return GPR_OK;
     }
     // whole cycles replayed from a captured graph, the steps left over launched from the host
@@ -808,6 +812,7 @@ static gpr_status check(gpr_system *S, int mode, int nrep, long long check_index
                        S->nsamp, check_index, (long long)S->tcp, S->st_host, S->donor, S->surv, S->fec, fresh ? 1 : 0,
                        mode == CHK_ADVANCE ? S->adv_fec : (long long *)nullptr, (CycRec *)nullptr, 0);
     LAUNCHCHK(S);
+    if (mode == CHK_DEPHASE) S->lists_old = true;          // (a killed worker has its donor's positions)
     if (!wait) return GPR_OK;
     HIPCHK(S, hipStreamSynchronize(S->stream));
     HIPCHK(S, prof_collect(S));
@@ -821,6 +826,7 @@ static gpr_status copy_replica(gpr_system *S, int dst, int src)
     HIPCHK(S, hipMemcpyAsync(S->donor, dn.data(), sizeof(int) * S->R, hipMemcpyHostToDevice, S->stream));
     hipLaunchKernelGGL(k_clone, dim3((3 * S->np + 255) / 256, S->R), dim3(256), 0, S->stream, S->d_dev, S->donor, 0);
     LAUNCHCHK(S);
+    S->lists_old = true;
     return GPR_OK;
 }
 
@@ -831,6 +837,7 @@ static gpr_status broadcast_reference(gpr_system *S)
     HIPCHK(S, hipMemcpyAsync(S->donor, dn.data(), sizeof(int) * S->R, hipMemcpyHostToDevice, S->stream));
     hipLaunchKernelGGL(k_clone, dim3((3 * S->np + 255) / 256, S->R), dim3(256), 0, S->stream, S->d_dev, S->donor, 1);
     LAUNCHCHK(S);
+    S->lists_old = true;
     return GPR_OK;
 }
 
@@ -1464,6 +1471,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
         if (!e) e = hipMemcpyAsync(save ? sF : d.F, save ? d.F : sF, sizeof(long long) * m, k, S->stream);
         if (!e) e = hipMemcpyAsync(save ? slb : d.last_build, save ? d.last_build : slb, sizeof(long long) * 2 * R, k, S->stream);
         if (!e && !save) {
+            S->lists_old = true;
             std::vector<int> ones(R, 1);
             e = hipMemcpyAsync(d.need_build, ones.data(), sizeof(int) * R, hipMemcpyHostToDevice, S->stream);
             if (!e) e = hipStreamSynchronize(S->stream);
@@ -1700,6 +1708,14 @@ extern "C" gpr_status gpr_energy_backward_dev(gpr_system *S, const double *w_dev
         hipLaunchKernelGGL(k_weighted_dx, dim3((n + 255) / 256, R), dim3(256), 0, S->stream, S->d_dev, w_dev, d_x);
         LAUNCHCHK(S);
     }
+    const bool relist = params && S->lists_old;
+    if (relist) {
+        // the lists of the present positions (the forces come out as they are)
+        gpr_status rc = launch_forces(S, 0, R, -1, 0, 0, 1);
+        if (rc) return rc;
+        rc = read_pieces(S, {{S->d.err, sizeof(int) * 4}});
+        if (rc) return rc;
+    }
     if (params) {
         // gacc is clear: k_grad_finish leaves it so
         if (S->gacc_dirty)
@@ -1718,6 +1734,7 @@ extern "C" gpr_status gpr_energy_backward_dev(gpr_system *S, const double *w_dev
         S->gacc_dirty = false;
     }
     HIPCHK(S, hipStreamSynchronize(S->stream));
+    if (relist && ((const int *)S->rb)[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
     return GPR_OK;
 }
 
@@ -2110,6 +2127,7 @@ static gpr_status run_cycles(gpr_system *S, PhaseRun &p, bool &ran)
     h.s_start = S->s; h.t_start = dep ? S->dp_t : 0; h.M_start = S->par_M; h.nsamp = S->nsamp;
     h.nsteps = (int)per; h.halt_cycle = NO_HALT; h.omega = S->omega; h.pad = 0;
     HIPCHK(S, hipMemcpyAsync(S->cyc_dev, S->cyc_host, sizeof(CycRec), hipMemcpyHostToDevice, S->stream));
+    S->lists_old = true;
     HIPCHK(S, hipGraphLaunch(ex, S->stream));
     HIPCHK(S, hipMemcpyAsync(S->stc_host, S->stc_dev, sizeof(Status) * C, hipMemcpyDeviceToHost, S->stream));
     HIPCHK(S, hipMemcpyAsync(S->cyc_host, S->cyc_dev, sizeof(CycRec), hipMemcpyDeviceToHost, S->stream));
@@ -2213,6 +2231,7 @@ extern "C" gpr_status gpr_dephase_fixed(gpr_system *S, int64_t t_phase, int64_t 
             if (st[r] != S->omega) {
                 rc = move_replica(S, d.x + b, d.v + b, d.F + b, S->snap_x, S->snap_v, S->snap_F);
                 if (rc) return rc;
+                S->lists_old = true;
                 HIPCHK(S, hipMemcpyAsync(d.need_build + r, &one, sizeof(int), hipMemcpyHostToDevice, S->stream));
                 S->resid[r] = 0;
                 S->n_branch += 1;
@@ -2226,6 +2245,7 @@ extern "C" gpr_status gpr_dephase_fixed(gpr_system *S, int64_t t_phase, int64_t 
             }
         }
         if (all) {
+            S->lists_old = true;
             for (int r = 0; r < R; ++r) {
                 const size_t b = (size_t)r * m;
                 rc = move_replica(S, d.x + b, d.v + b, d.F + b, S->samp_x + b, S->samp_v + b, S->samp_F + b);
