@@ -224,7 +224,8 @@ gpr_status gpr_set_path(gpr_system *sys, int32_t path);
 /* Launch shape of the persistent path: threads per workgroup (multiple of 64, <= 1024) and
  * workgroups per replica (1, 2, 4 or 8; a replica's atoms are split between its workgroups,
  * which exchange positions every step; launches of few replicas take up to 32 by themselves).
- * 0 keeps the current value.  When the replicas times
+ * 0 keeps the current value.  A replica of fewer than 16 atoms for each workgroup runs on fewer: every
+ * workgroup owns atoms.  When the replicas times
  * the workgroups per replica exceed what the device holds at once, sets of workgroups take the
  * replicas in turn.  EINVAL, with nothing changed, if one workgroup's share of a replica does
  * not fit in LDS (large systems need several workgroups per replica) or a workgroup of that

@@ -40,7 +40,7 @@ struct gpr_system {
     int bt_persist = 0;
     int groups = 1;            // workgroups per replica on the persistent path
     Split split{};             // their atom ranges
-    Split splits[NSPLIT]{};    // the atom ranges with 1, 2, 4, ... MAX_G workgroups per replica
+    Split splits[NSPLIT]{};    // the atom ranges with 1, 2, 4, ... MAX_G workgroups per replica (fewer for tiny ones)
     bool split_ok[NSPLIT]{};        // whether a workgroup of that split fits on a compute unit
     // whose choice the launch shape is: 0 the library's, for the replicas of each launch
     // (run_shape), 1 the autotuner's, for launches of all replicas, 2 the caller's, for every launch
@@ -233,31 +233,10 @@ static hipError_t prof_collect(gpr_system *S)
     return hipSuccess;
 }
 
-// Atom ranges of the G workgroups of a replica (k_persist): contiguous, starting at multiples
-// of 16 (so that every wave of the pair loop covers 16 atoms of one group), with boundaries
-// placed where the running sum of the per-atom work estimate crosses g/G of the total.
 static Split make_split(const std::vector<double> &work, int n, int np, int G)
 {
     Split sp{};
-    sp.G = G;
-    sp.bnd[0] = 0;
-    sp.bnd[G] = n;
-    if (G == 1) {
-        sp.lmax = np;
-        return sp;
-    }
-    std::vector<double> cum(n + 1, 0.0);
-    for (int i = 0; i < n; ++i) cum[i + 1] = cum[i] + work[i];
-    for (int g = 1; g < G; ++g) {
-        const double target = cum[n] * g / G;
-        int a = (int)(std::lower_bound(cum.begin(), cum.end(), target) - cum.begin());
-        const int lo = a / 16 * 16, hi = std::min(n, lo + 16);
-        a = (target - cum[lo] <= cum[hi] - target) ? lo : hi;
-        sp.bnd[g] = std::min(n, std::max(a, sp.bnd[g - 1]));
-    }
-    int lmax = 16;
-    for (int g = 0; g < G; ++g) lmax = std::max(lmax, sp.bnd[g + 1] - sp.bnd[g]);
-    sp.lmax = (lmax + 15) / 16 * 16;
+    static_cast<AtomRanges &>(sp) = atom_ranges(work, n, np, G);
     return sp;
 }
 
@@ -329,7 +308,8 @@ static RunShape run_shape(const gpr_system *S, int nrep)
             const int G = 1 << k;
             if (G > sh.sp->G && S->split_ok[k] && S->n >= 32 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
         }
-    sh.noise_ahead = noise_fits(S->n, S->np, *sh.sp, sh.bt, S->maxlds_persist);
+    // (one group draws them beside its pair tasks, which the toy system has none of)
+    sh.noise_ahead = S->kind != GPR_KIND_TOY2D && noise_fits(S->n, S->np, *sh.sp, sh.bt, S->maxlds_persist);
     sh.lds = sh.noise_ahead ? (size_t)persist_off(S->n, S->np, sh.sp->lmax).end : persist_lds(S->n, S->np, *sh.sp);
     return sh;
 }
@@ -574,8 +554,9 @@ static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt,
 
 // The layout of a persistent launch checked on the host before it runs, with the device's own
 // placement function: items cover the grid in order without overlap, every workgroup is group
-// g < G of a set < nsets, every (set, g) occurs once, the groups' atom ranges are ordered,
-// within the system and no longer than the LDS arrays (lmax), and the block size is whole waves.
+// g < G of a set < nsets, every (set, g) occurs once, the groups' atom ranges are ordered, not empty
+// (the position exchange relies on it), within the system and no longer than the LDS arrays (lmax),
+// and the block size is whole waves.
 static gpr_status check_layout(gpr_system *S, const PersistBatch &pb, int nblocks, int bt, bool single)
 {
     if (pb.nitems < 1 || pb.nitems > MAX_BATCH || bt < 64 || bt > 1024 || bt % 64) return fail(S, GPR_EDEVICE, "bad persistent launch shape");
@@ -589,7 +570,7 @@ static gpr_status check_layout(gpr_system *S, const PersistBatch &pb, int nblock
         const int n = sp.bnd[sp.G];
         if (sp.bnd[0] != 0) return fail(S, GPR_EDEVICE, "persistent launch layout: atom ranges");
         for (int g = 0; g < sp.G; ++g)
-            if (sp.bnd[g] > sp.bnd[g + 1] || sp.bnd[g + 1] > n || sp.bnd[g + 1] - sp.bnd[g] > sp.lmax)
+            if (sp.bnd[g] >= sp.bnd[g + 1] || sp.bnd[g + 1] > n || sp.bnd[g + 1] - sp.bnd[g] > sp.lmax)
                 return fail(S, GPR_EDEVICE, "persistent launch layout: atom ranges");
         std::vector<unsigned char> seen((size_t)it.nsets * sp.G, 0);
         for (int local = 0; local < it.nsets * sp.G; ++local) {
@@ -2382,9 +2363,9 @@ static gpr_status batch_layout(gpr_system *const *systems, int32_t nsys, const s
             const gpr_system *S = systems[k];
             pick[k] = Choice{};
             for (int j = 0; j < 4; ++j) {
-                const int G = 1 << j;
-                const Split *sp = G == S->groups ? &S->split : &S->splits[j];
-                if (G != S->groups && (S->groups_from != 0 || !S->split_ok[j] || S->n < 64 * G)) continue;
+                const Split *sp = (1 << j) == S->groups ? &S->split : &S->splits[j];
+                const int G = sp->G;
+                if ((1 << j) != S->groups && (S->groups_from != 0 || !S->split_ok[j] || S->n < 64 << j)) continue;
                 if (persist_lds(S->n, S->np, *sp) > sh.lds_most) continue;
                 const double t = 4.0 + (G > 1 ? 1.7 : 0.0) + (1.55e-4 + 1e-5 * G) * sh.w[k] / G;
                 const long rounds = (long)(T / t);

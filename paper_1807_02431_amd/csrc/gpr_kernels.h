@@ -1,6 +1,7 @@
 // gpr_kernels.h -- kernel entry points of the Gen.ParRep hot path (launched by gpr_api.hip).
 #pragma once
 #include "gpr_device.h"
+#include "gpr_layout.h"
 
 namespace gpr {
 
@@ -42,13 +43,10 @@ constexpr int PHASE_MAX_R = 4096, PHASE_MAX_G = 8;
 // them, on the stream; hipErrorNotSupported in a build without the timers.
 hipError_t phase_take(unsigned long long *out, int R, hipStream_t st);
 
-// atom ranges of the workgroups of one replica on the persistent path
-constexpr int MAX_G = 32, NSPLIT = 6;
-struct Split {
-    int G;          // workgroups per replica (1, 2, 4, ... MAX_G)
-    int lmax;       // LDS length of the per-group arrays: the largest range, rounded up to 16
-    int bnd[MAX_G + 1];   // group g owns atoms [bnd[g], bnd[g + 1]); every bnd[g] < n is a multiple of 16
-    int bu[MAX_G + 1];   // its bonded units are [bu[g], bu[g + 1]) of the records bi, bp
+// a replica over workgroups on the persistent path
+constexpr int NSPLIT = 6;
+struct Split : AtomRanges {
+    int bu[MAX_G + 1];   // group g's bonded units are [bu[g], bu[g + 1]) of the records bi, bp
     const uint2 *bi;
     const float4 *bp;
 };

@@ -1458,7 +1458,7 @@ __device__ __forceinline__ void persist_replica(const Dev &S, int G, int lmax, i
     // displacement margin).  A word is there when its tag is (the word it replaces has the tag of two
     // steps before, or none), so the groups need no barrier: a reader polls the words themselves.
     // A group writes step s + 1 over step s - 1 once it has every other group's step s, which each
-    // of them wrote after reading step s - 1.
+    // of them wrote after reading step s - 1 (so every group owns atoms: the host lays out no other).
     GPR_GLOBAL unsigned long long *const xchg = gmut(((const GPR_CONST Dev *)&S)->xchg) + (size_t)r * 4 * np;
     int gen = 0;
 
