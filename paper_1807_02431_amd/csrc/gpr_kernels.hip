@@ -1422,11 +1422,10 @@ __device__ __noinline__ bool persist_sample(const Dev *Sv, GPR_LDS unsigned char
         __hip_atomic_fetch_add(S.esum + r, *eacc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!group_barrier(S.sync + (size_t)r * 64, target, S.err, (int *)bufl)) return false;
     if (g == 0) {
-        if (tid == 0) {
-            // the sum of the groups' energies, by way of the accumulator
-            *eacc = __hip_atomic_load(S.esum + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(S.esum + r, 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        // the sum of the groups' energies, by way of the accumulator.  The sum is cleared by the exchange that
+        // reads it: its value is there, and so the clearing done, before this group's waves pass the
+        // barrier and publish the next step's positions, which the other groups need to add to it again
+        if (tid == 0) *eacc = __hip_atomic_exchange(S.esum + r, 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         observables_wg(S, xs, vg, unfix_d(*eacc), red, vals, tid, BT, true);
         if (tid == 0) accumulate_obs(S, r, vals);
