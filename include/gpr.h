@@ -116,7 +116,7 @@ typedef struct gpr_system_desc {
     int32_t kind;
     int32_t n_atoms;             /* >= 1; the pair kernels hold a replica's positions and LJ
                                     parameters in LDS (24 bytes per atom), so creation fails with
-                                    EINVAL past about 6,500 atoms on a 160 KiB-LDS device; the
+                                    EINVAL past 6,136 atoms on a 160 KiB-LDS device; the
                                     persistent path, which also keeps its own atoms' velocities
                                     and forces in LDS, takes up to about 4,600 atoms (8 workgroups
                                     per replica; gpr_set_path reports EINVAL beyond) */

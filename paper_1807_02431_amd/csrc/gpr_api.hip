@@ -1199,8 +1199,17 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     HIPCHK(S, hipGetDevice(&dev));
     HIPCHK(S, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     S->maxlds = maxlds;
-    if ((int)S->lds_nb > maxlds || (int)S->lds_stage > maxlds)
-        return fail(S, GPR_EINVAL, "system too large for the LDS-staged pair kernel");
+    {
+        // with the static LDS of the kernels that take them
+        struct { const void *fn; size_t lds; } use[] = {{(const void *)k_forces, S->lds_nb}, {(const void *)k_grad_nb, S->lds_nb},
+                                                        {(const void *)k_obs, S->lds_stage}, {(const void *)k_state, S->lds_stage}};
+        for (const auto &u : use) {
+            hipFuncAttributes fa{};
+            HIPCHK(S, hipFuncGetAttributes(&fa, u.fn));
+            if (u.lds + fa.sharedSizeBytes > (size_t)maxlds)
+                return fail(S, GPR_EINVAL, "system too large for the LDS-staged pair kernel");
+        }
+    }
     HIPCHK(S, hipFuncSetAttribute((const void *)k_forces, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_nb));
     HIPCHK(S, hipFuncSetAttribute((const void *)k_grad_nb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_nb));
     HIPCHK(S, hipFuncSetAttribute((const void *)k_obs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S->lds_stage));

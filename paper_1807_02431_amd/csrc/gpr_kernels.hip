@@ -898,10 +898,11 @@ __global__ void __launch_bounds__(1024, 8) k_forces(const Dev *__restrict__ Sp, 
     float4 *box = xs + S.np;                               // boxes of the atom blocks
     int *wscr = (int *)(box + (S.n + BLK - 1) / BLK);      // [16][WBLK] build scratch per wave
     __shared__ long long e_acc;
+    __shared__ int far_out;                                // (a word of its own: __syncthreads_or takes 256 bytes)
     const int r = r_off + blockIdx.y;
     const int tid = threadIdx.x, nthr = blockDim.x;
     stage_replica(S, r, xs, pp, tid, nthr);
-    if (tid == 0) e_acc = 0;
+    if (tid == 0) { e_acc = 0; far_out = 0; }
     for (int t = tid; t < (S.n + BLK - 1) / BLK; t += nthr) box[t].w = __uint_as_float((unsigned)gconst(S.cls)[t] << 24);
     // rebuild when forced, when flagged (displacement guard or a new configuration), or on the
     // steps s with s + 1 a multiple of period, the same steps for every replica: one launch
@@ -941,7 +942,9 @@ __global__ void __launch_bounds__(1024, 8) k_forces(const Dev *__restrict__ Sp, 
         const GPR_LDS gv_f4 *xl = (const GPR_LDS gv_f4 *)xs;
         GPR_LDS gv_f2 *pl = (GPR_LDS gv_f2 *)pp;
         const float3 c = search_centre(xl, S.n);
-        const bool wide = __syncthreads_or(block_boxes(C, xl, pl, (GPR_LDS gv_f4 *)box, c, tid, nthr)) != 0;
+        if (block_boxes(C, xl, pl, (GPR_LDS gv_f4 *)box, c, tid, nthr)) far_out = 1;
+        __syncthreads();
+        const bool wide = uni(far_out) != 0;
         const int wv = uni(tid >> 6);
         search_task<2, false>(C, r, blockIdx.x * (nthr / P) + 16 * wv, S.n, xl, pl, (const GPR_LDS gv_f4 *)box,
                               (GPR_LDS int *)wscr + wv * WBLK, c, wide, !S.cutoff_on);
