@@ -229,7 +229,14 @@ gpr_status gpr_set_path(gpr_system *sys, int32_t path);
  * the workgroups per replica exceed what the device holds at once, sets of workgroups take the
  * replicas in turn.  EINVAL, with nothing changed, if one workgroup's share of a replica does
  * not fit in LDS (large systems need several workgroups per replica) or a workgroup of that
- * size cannot run.  Results do not depend on the shape. */
+ * size cannot run.  Results do not depend on the shape.
+ * Workgroups of one replica wait for each other, so all of them must find room on the device
+ * together.  Launches of the handles of one process are kept within it, on whatever threads and
+ * streams they are: beside others' launches one takes fewer workgroups per replica, or waits for theirs
+ * to end where one workgroup does not fit or this call chose the shape.  Launches of other processes
+ * are not seen: where several processes share a device, one workgroup per replica (this call with
+ * groups_per_replica 1) waits for nothing; otherwise a wait that does not end within seconds is
+ * reported as EDEVICE. */
 gpr_status gpr_set_launch(gpr_system *sys, int32_t block_threads, int32_t groups_per_replica);
 
 /* Plain path as replays of a HIP graph: with cycle_steps > 0 the plain path's launches of

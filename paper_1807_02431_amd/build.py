@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgpr_hip.so")
 PROBE_LIB = os.path.join(HERE, "libgpr_hip_probe.so")
 SOURCES = ["gpr_kernels.hip", "gpr_api.hip"]
-HEADERS = ["gpr_device.h", "gpr_kernels.h", "gpr_layout.h"]
+HEADERS = ["gpr_device.h", "gpr_kernels.h", "gpr_layout.h", "gpr_room.h"]
 ARCH = os.environ.get("GPR_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

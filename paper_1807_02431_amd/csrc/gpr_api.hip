@@ -18,6 +18,7 @@
 
 #include "gpr.h"
 #include "gpr_kernels.h"
+#include "gpr_room.h"
 
 using namespace gpr;
 
@@ -29,6 +30,9 @@ enum { PH_IDLE = 0, PH_DECORR = 1, PH_DEPHASE = 2, PH_CONVERGED = 3, PH_PARALLEL
 
 thread_local std::string g_thread_err;
 
+constexpr int MAX_DEV = 64;
+Room g_room[MAX_DEV];                  // by device
+
 } // namespace
 
 struct gpr_system {
@@ -36,6 +40,9 @@ struct gpr_system {
     Dev *d_dev = nullptr;     // device copy of d, passed to every kernel
     std::vector<void *> bufs;
     hipStream_t stream = nullptr;
+    int dev = 0;               // the device it was created on
+    int held = 0;              // room taken on it by launches not yet waited for
+    Room::Key held_by{};
     int path = GPR_PATH_PLAIN;
     int bt_persist = 0;
     int groups = 1;            // workgroups per replica on the persistent path
@@ -87,7 +94,7 @@ struct gpr_system {
     std::vector<Graph> graphs;
     // persistent convergence and parallel steps as replays of captured check cycles (0: off)
     int cycles = 0;
-    struct CGraph { int op; hipGraphExec_t exec; };
+    struct CGraph { int op; hipGraphExec_t exec; int units; };    // units: room a replay needs
     std::vector<CGraph> cgraphs;
     CycRec *cyc_dev = nullptr, *cyc_host = nullptr;
     Status *stc_dev = nullptr, *stc_host = nullptr;   // [cycles] statuses of a replay
@@ -289,29 +296,34 @@ struct RunShape {
     bool noise_ahead;          // k_persist: the next step's Gaussians in LDS
     size_t lds;
 };
+static RunShape shape_on(const gpr_system *S, int bt, const Split *sp)
+{
+    RunShape sh{bt, sp, false, false, 0};
+    // (one group draws them beside its pair tasks, which the toy system has none of)
+    sh.noise_ahead = S->kind != GPR_KIND_TOY2D && noise_fits(S->n, S->np, *sp, bt, S->maxlds_persist);
+    sh.lds = sh.noise_ahead ? (size_t)persist_off(S->n, S->np, sp->lmax).end : persist_lds(S->n, S->np, *sp);
+    return sh;
+}
+static bool chosen(const gpr_system *S, int from, int nrep) { return from == 2 || (from == 1 && nrep == S->R); }
 static RunShape run_shape(const gpr_system *S, int nrep)
 {
-    auto chosen = [&](int from) { return from == 2 || (from == 1 && nrep == S->R); };
     const int cus = std::max(1, S->max_coresident);
     RunShape sh{S->bt_persist, &S->split, false, false, 0};
     if (S->small_ok && S->groups == 1) {
         sh.small = true;
-        if (!chosen(S->bt_from)) {
+        if (!chosen(S, S->bt_from, nrep)) {
             const int waves = std::min(16, std::max(small_units(S), S->nobs));
             sh.bt = 64 * std::max(1, std::min(waves, 16 / ((nrep + cus - 1) / cus)));
         }
         sh.lds = small_lds(S);
         return sh;
     }
-    if (!chosen(S->groups_from))
+    if (!chosen(S, S->groups_from, nrep))
         for (int k = 1; k < NSPLIT; ++k) {
             const int G = 1 << k;
             if (G > sh.sp->G && S->split_ok[k] && S->n >= 32 * G && (long)nrep * G <= cus) sh.sp = &S->splits[k];
         }
-    // (one group draws them beside its pair tasks, which the toy system has none of)
-    sh.noise_ahead = S->kind != GPR_KIND_TOY2D && noise_fits(S->n, S->np, *sh.sp, sh.bt, S->maxlds_persist);
-    sh.lds = sh.noise_ahead ? (size_t)persist_off(S->n, S->np, sh.sp->lmax).end : persist_lds(S->n, S->np, *sh.sp);
-    return sh;
+    return shape_on(S, sh.bt, sh.sp);
 }
 
 // ------------------------------------------------------------------ bonded units
@@ -507,9 +519,9 @@ static gpr_status persist_capacity(gpr_system *S, int bt, size_t lds, int &cap)
 // groups of a replica wait for each other, so they must be resident together: the replicas are
 // shared by at most capacity / G sets (cap_blocks < 0: the whole device), so that the grid is
 // no larger than what the device holds at once, and every workgroup gets a CU as soon as the
-// device is free of other work.  (A launch cannot start its workgroups while other kernels
-// hold the CUs they need only until those kernels end; should a group still wait longer than
-// the barrier's bounded spin, the call reports GPR_EDEVICE, never hangs.)  No cooperative
+// device is free of other work.  (Other kernels hold the CUs it needs only until they end, and
+// launches that wait for workgroups of their own take room first, see admit; should a group still wait
+// longer than the bounded spin, the call reports GPR_EDEVICE, never hangs.)  No cooperative
 // launch: it adds tens of microseconds to each launch and is refused while another process
 // holds the device's cooperative resources.
 static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt, size_t lds, int cap_blocks,
@@ -549,6 +561,65 @@ static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt,
     }
     it.nsets = nsets;
     nblocks = nsets * G;
+    return GPR_OK;
+}
+
+// The room that launches held is free again: the stream has been waited for.
+static void give_back(gpr_system *S)
+{
+    if (S->held) g_room[S->dev].give(S->held_by);
+    S->held = 0;
+}
+static hipError_t finish(gpr_system *S)
+{
+    const hipError_t e = hipStreamSynchronize(S->stream);
+    give_back(S);
+    return e;
+}
+struct FinishAtEnd {                   // of a call, where it ends without having waited
+    gpr_system *S;
+    ~FinishAtEnd() { if (S->held) (void)finish(S); }
+};
+static Room::Key room_key(const gpr_system *S)
+{
+    return {S->stream, S->stream == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()};
+}
+static int room_cap(const gpr_system *S) { return std::max(8, S->max_coresident / 8 * 8); }
+// Workgroups go to the eight XCDs in turn, so what counts is a launch's share of each.
+static int room_units(int nblocks) { return (nblocks + 7) / 8 * 8; }
+static bool hold(gpr_system *S, int units, bool wait)
+{
+    if (S->held >= units) return true;                     // of this call's earlier launches on the stream
+    if (S->held) (void)finish(S);
+    const Room::Key key = room_key(S);
+    if (wait) g_room[S->dev].take(key, units, room_cap(S));
+    else if (!g_room[S->dev].try_take(key, units, room_cap(S))) return false;
+    S->held = units;
+    S->held_by = key;
+    return true;
+}
+
+// The shape and item of a launch that there is room for beside the launches of other streams that wait for
+// their own workgroups too.  While others have room or wait for it, a launch takes no more workgroups per
+// replica than one of all replicas does; where that has no room, fewer, down to one, which needs
+// none; and it waits for room only where one does not fit or the caller chose the shape.
+static gpr_status admit(gpr_system *S, int nrep, RunShape &sh, PersistItem &it, int &nblocks)
+{
+    const bool fixed = chosen(S, S->groups_from, nrep);
+    if (sh.sp->G > S->split.G && S->held == 0 && g_room[S->dev].others(room_key(S))) sh = shape_on(S, sh.bt, &S->split);
+    for (;;) {
+        const gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, it, nblocks);
+        if (rc) return rc;
+        if (sh.sp->G == 1 || hold(S, room_units(nblocks), fixed)) return GPR_OK;
+        int k = split_index(sh.sp->G) - 1;
+        while (k >= 0 && !S->split_ok[k]) --k;
+        if (k < 0) break;
+        sh = shape_on(S, sh.bt, &S->splits[k]);
+    }
+    sh = shape_on(S, sh.bt, &S->split);
+    const gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, it, nblocks);
+    if (rc) return rc;
+    (void)hold(S, room_units(nblocks), true);
     return GPR_OK;
 }
 
@@ -696,8 +767,8 @@ static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long
         PersistBatch pb{};
         pb.nitems = 1;
         int nblocks = 0;
-        const RunShape sh = run_shape(S, nrep);
-        gpr_status rc = persist_item(S, *sh.sp, nrep, sh.bt, sh.lds, -1, pb.it[0], nblocks);
+        RunShape sh = run_shape(S, nrep);
+        gpr_status rc = admit(S, nrep, sh, pb.it[0], nblocks);
         if (rc) return rc;
         pb.it[0].noise_ahead = sh.noise_ahead ? 1 : 0;
         // more replicas than sets that fit at once: rounds of launches, each set taking one
@@ -795,7 +866,7 @@ static gpr_status check(gpr_system *S, int mode, int nrep, long long check_index
     LAUNCHCHK(S);
     if (mode == CHK_DEPHASE) S->lists_old = true;          // (a killed worker has its donor's positions)
     if (!wait) return GPR_OK;
-    HIPCHK(S, hipStreamSynchronize(S->stream));
+    HIPCHK(S, finish(S));
     HIPCHK(S, prof_collect(S));
     return flag_errors(S, S->st_host->err);
 }
@@ -1176,6 +1247,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     {
         int dev = 0;
         HIPCHK(S, hipGetDevice(&dev));
+        S->dev = dev < MAX_DEV ? dev : MAX_DEV - 1;
         HIPCHK(S, hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev));
     }
     HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
@@ -1469,6 +1541,7 @@ extern "C" gpr_status gpr_autotune(gpr_system *S, int32_t nsteps, int32_t *block
         return e;
     };
     HIPCHK(S, copy_all(true));
+    FinishAtEnd at_end{S};
     const long long s_saved = S->s;
     const int path_saved = S->path, bt_saved = S->bt_persist, g_saved = S->groups;
     const int btf_saved = S->bt_from, gf_saved = S->groups_from;
@@ -2012,6 +2085,7 @@ static gpr_status run_cycles(gpr_system *S, PhaseRun &p, bool &ran);
 
 static gpr_status run_phase(gpr_system *S, PhaseRun &p)
 {
+    FinishAtEnd at_end{S};
     gpr_status rc = phase_begin(S, p);
     if (rc) return rc;
     for (;;) {
@@ -2043,10 +2117,10 @@ static void drop_cycle_graphs(gpr_system *S)
 // launch(es) of one check period with the state test at the end, then the check with its
 // clone-on-kill copies.  Steps, check indices and Omega come from the cycle record, which the
 // host writes before each replay.
-static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
+static gpr_status cycle_graph(gpr_system *S, int op, gpr_system::CGraph *out)
 {
     for (auto &g : S->cgraphs)
-        if (g.op == op) { *out = g.exec; return GPR_OK; }
+        if (g.op == op) { *out = g; return GPR_OK; }
     const int nrep = S->R;
     const bool dep = op == GPR_OP_DEPHASE;
     const int nsteps = dep ? S->tcd : S->tcp;
@@ -2091,8 +2165,8 @@ static gpr_status cycle_graph(gpr_system *S, int op, hipGraphExec_t *out)
     if (e != hipSuccess || e2 != hipSuccess || e3 != hipSuccess)
         return fail(S, GPR_EDEVICE, std::string("check-cycle capture: ") +
                                         hipGetErrorString(e != hipSuccess ? e : e2 != hipSuccess ? e2 : e3));
-    S->cgraphs.push_back({op, ex});
-    *out = ex;
+    S->cgraphs.push_back({op, ex, sh.sp->G > 1 && !sh.small ? room_units(nblocks) : 0});
+    *out = S->cgraphs.back();
     return GPR_OK;
 }
 
@@ -2110,18 +2184,19 @@ static gpr_status run_cycles(gpr_system *S, PhaseRun &p, bool &ran)
     const long long per = dep ? S->tcd : S->tcp;
     if (dep ? (S->dp_t % S->tcd != 0 || p.budget - p.taken < C * per) : (S->par_t != 0 || p.budget - p.taken < C))
         return GPR_OK;
-    hipGraphExec_t ex = nullptr;
-    gpr_status rc = cycle_graph(S, p.op, &ex);
+    gpr_system::CGraph g{};
+    gpr_status rc = cycle_graph(S, p.op, &g);
     if (rc) return rc;
+    if (g.units) (void)hold(S, g.units, true);
     CycRec &h = *S->cyc_host;
     h.s_start = S->s; h.t_start = dep ? S->dp_t : 0; h.M_start = S->par_M; h.nsamp = S->nsamp;
     h.nsteps = (int)per; h.halt_cycle = NO_HALT; h.omega = S->omega; h.pad = 0;
     HIPCHK(S, hipMemcpyAsync(S->cyc_dev, S->cyc_host, sizeof(CycRec), hipMemcpyHostToDevice, S->stream));
     S->lists_old = true;
-    HIPCHK(S, hipGraphLaunch(ex, S->stream));
+    HIPCHK(S, hipGraphLaunch(g.exec, S->stream));
     HIPCHK(S, hipMemcpyAsync(S->stc_host, S->stc_dev, sizeof(Status) * C, hipMemcpyDeviceToHost, S->stream));
     HIPCHK(S, hipMemcpyAsync(S->cyc_host, S->cyc_dev, sizeof(CycRec), hipMemcpyDeviceToHost, S->stream));
-    HIPCHK(S, hipStreamSynchronize(S->stream));
+    HIPCHK(S, finish(S));
     ran = true;
     const int halt = S->cyc_host->halt_cycle;
     const int ncyc = halt == NO_HALT ? C : halt + 1;
@@ -2174,6 +2249,7 @@ static gpr_status move_replica(gpr_system *S, float *dx, float *dv, long long *d
 extern "C" gpr_status gpr_dephase_fixed(gpr_system *S, int64_t t_phase, int64_t max_steps, gpr_dephase_out *o)
 {
     if (!S || !o) return fail(S, GPR_EINVAL, "NULL argument");
+    FinishAtEnd at_end{S};
     const int R = S->R;
     const size_t m = (size_t)3 * S->np;
     Dev &d = S->d;
@@ -2210,7 +2286,7 @@ extern "C" gpr_status gpr_dephase_fixed(gpr_system *S, int64_t t_phase, int64_t 
         HIPCHK(S, hipMemcpyAsync(st.data(), d.state, sizeof(int) * R, hipMemcpyDeviceToHost, S->stream));
         int err[4];
         HIPCHK(S, hipMemcpyAsync(err, d.err, sizeof err, hipMemcpyDeviceToHost, S->stream));
-        HIPCHK(S, hipStreamSynchronize(S->stream));
+        HIPCHK(S, finish(S));
         if (err[ERR_UNSTABLE]) return fail(S, GPR_EUNSTABLE, "non-finite or overflowing state");
         if (err[ERR_BARRIER]) return fail(S, GPR_EDEVICE, "persistent kernel barrier timed out");
         if (err[ERR_LIST]) return fail(S, GPR_EDEVICE, "pair-list capacity exceeded");
@@ -2271,6 +2347,7 @@ extern "C" gpr_status gpr_advance(gpr_system *S, int64_t nsteps, int64_t *first_
     if (nsteps < 0) return fail(S, GPR_EINVAL, "nsteps < 0");
     // the sampling (every t_GR) and check (every t_check_dephase) schedule runs on the steps
     // counted over all calls, so that short calls sample and check as one long call would
+    FinishAtEnd at_end{S};
     long long t = S->adv_t;
     const long long end = S->adv_t + nsteps;
     bool checked = false, at_check = false;
@@ -2294,7 +2371,7 @@ extern "C" gpr_status gpr_advance(gpr_system *S, int64_t nsteps, int64_t *first_
         const gpr_status rc = read_pieces(S, {{S->d.err, sizeof(int) * 4}});
         if (rc) return rc;
     }
-    HIPCHK(S, hipStreamSynchronize(S->stream));
+    HIPCHK(S, finish(S));
     HIPCHK(S, prof_collect(S));
     const gpr_status rc = flag_errors(S, at_check ? S->st_host->err : (const int *)S->rb);
     if (rc) return rc;
@@ -2325,6 +2402,7 @@ struct BatchShape {
     int bt = 64;
     size_t lds0 = 0, lds = 0, lds_most = 0;
     int capacity = 0;
+    int units = 0;             // room that the workgroups that wait for one another need (0: none do)
     std::vector<double> w;
 };
 
@@ -2422,6 +2500,10 @@ static gpr_status batch_layout(gpr_system *const *systems, int32_t nsys, const s
     pb.nitems = j;
     if (boff > sh.capacity) return fail(S0, GPR_EINVAL, "the systems' workgroups do not fit on the device at once");
     nblocks = boff;
+    int waiting = 0;
+    for (int k = 0; k < nsys; ++k)
+        if (nrep[k] > 0 && items[k].sp.G > 1) waiting += room_units(nb[k]);
+    sh.units = waiting;
     return GPR_OK;
 }
 
@@ -2445,6 +2527,7 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
     int nblocks = 0;
     rc = batch_layout(systems, nsys, nrep, sh, pb, slot, nblocks);
     if (rc) return rc;
+    FinishAtEnd at_end{S0};
     std::vector<long long> t(nsys, 0);
     for (int k = 0; k < nsys; ++k) t[k] = systems[k]->adv_t;
     std::vector<char> checked(nsys, 0);
@@ -2462,6 +2545,7 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
             it.sample = 1;
             it.state_end = (t[k] + kstep) % S->tcd == 0 ? 1 : 0;
         }
+        if (sh.units) (void)hold(S0, sh.units, true);
         rc = launch_persist(S0, pb, nblocks, sh.bt, sh.lds, stream);
         if (rc) return rc;
         for (int k = 0; k < nsys; ++k) {
@@ -2474,6 +2558,7 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
                 rc = check(S, CHK_ADVANCE, S->R, t[k] / S->tcd, !checked[k]);
                 if (rc) return rc;
                 checked[k] = 1;
+                give_back(S0);                             // (the check has waited for the launch)
             }
         }
         done += kstep;
@@ -2482,7 +2567,7 @@ extern "C" gpr_status gpr_batch_advance(gpr_system *const *systems, int32_t nsys
         rc = read_pieces(systems[k], {{systems[k]->d.err, sizeof(int) * 4}});
         if (rc) return rc;
     }
-    HIPCHK(S0, hipStreamSynchronize(stream));
+    HIPCHK(S0, finish(S0));
     for (int k = 0; k < nsys; ++k) {
         gpr_system *S = systems[k];
         rc = flag_errors(S, (const int *)S->rb);
@@ -2505,6 +2590,7 @@ extern "C" gpr_status gpr_batch_run(gpr_system *const *systems, int32_t nsys, gp
     BatchShape sh;
     rc = batch_shape(systems, nsys, sh);
     if (rc) return rc;
+    FinishAtEnd at_end{S0};
     std::vector<PhaseRun> p(nsys);
     for (int k = 0; k < nsys; ++k) {
         p[k].op = ops[k].op;
@@ -2512,7 +2598,7 @@ extern "C" gpr_status gpr_batch_run(gpr_system *const *systems, int32_t nsys, gp
         p[k].budget = ops[k].max_steps;
         ops[k].status = GPR_BUDGET;
     }
-    auto finish = [&](int k) {
+    auto hand_over = [&](int k) {
         ops[k].status = p[k].rc;
         if (p[k].rc == GPR_OK) {
             if (p[k].op == GPR_OP_DECORRELATE) ops[k].event = p[k].ev;
@@ -2557,6 +2643,7 @@ extern "C" gpr_status gpr_batch_run(gpr_system *const *systems, int32_t nsys, gp
             it.sample = c[k].sample ? 1 : 0;
             it.state_end = c[k].at_check ? 1 : 0;
         }
+        if (sh.units) (void)hold(S0, sh.units, true);
         rc = launch_persist(S0, pb, nblocks, sh.bt, sh.lds, stream);
         if (rc) return rc;
         for (int k = 0; k < nsys; ++k) {
@@ -2564,9 +2651,10 @@ extern "C" gpr_status gpr_batch_run(gpr_system *const *systems, int32_t nsys, gp
             systems[k]->s += kstep;
             rc = phase_advance(systems[k], p[k], c[k]);
             if (rc) { ops[k].status = rc; return rc; }
+            if (c[k].at_check) give_back(S0);              // (the check has waited for the launch)
         }
     }
-    for (int k = 0; k < nsys; ++k) finish(k);
+    for (int k = 0; k < nsys; ++k) hand_over(k);
     return GPR_OK;
 }
 
