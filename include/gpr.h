@@ -234,9 +234,9 @@ gpr_status gpr_set_path(gpr_system *sys, int32_t path);
  * together.  Launches of the handles of one process are kept within it, on whatever threads and
  * streams they are: beside others' launches one takes fewer workgroups per replica, or waits for theirs
  * to end where one workgroup does not fit or this call chose the shape.  Launches of other processes
- * are not seen: where several processes share a device, one workgroup per replica (this call with
- * groups_per_replica 1) waits for nothing; otherwise a wait that does not end within seconds is
- * reported as EDEVICE. */
+ * are not seen; beside them a launch's workgroups take their places in the order in which they start, so that
+ * those that run make whole replicas, which end and make room.  A wait that does not end within
+ * seconds all the same is reported as EDEVICE; one workgroup per replica waits for nothing. */
 gpr_status gpr_set_launch(gpr_system *sys, int32_t block_threads, int32_t groups_per_replica);
 
 /* Plain path as replays of a HIP graph: with cycle_steps > 0 the plain path's launches of

@@ -1162,6 +1162,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     HIPCHK(S, dalloc(S, &d.clock, 2));
     HIPCHK(S, dalloc(S, &d.err, 4));
     HIPCHK(S, dalloc(S, &d.sync, (size_t)R * 64));
+    HIPCHK(S, dalloc(S, &d.ticket, (size_t)9 * 32));
     HIPCHK(S, dalloc(S, &d.xchg, (size_t)R * 4 * np));
     HIPCHK(S, dalloc(S, &d.esum, R));
     HIPCHK(S, dalloc(S, &d.acc, (size_t)R * MAX_OBS * 2));
@@ -2496,6 +2497,7 @@ static gpr_status batch_layout(gpr_system *const *systems, int32_t nsys, const s
             boff += nb[k];
             slot[k] = j;
             pb.it[j++] = items[k];
+            if (pass == 1) pb.mapped = boff;
         }
     pb.nitems = j;
     if (boff > sh.capacity) return fail(S0, GPR_EINVAL, "the systems' workgroups do not fit on the device at once");

@@ -112,6 +112,7 @@ struct Dev {
     long long *clock;                      // [2]: global step s and steps t of the current call (device-clocked plain steps)
     int *err;                              // [4] error flags
     int *sync;                             // [R][64] per-replica barrier counter and leave count (groups > 1)
+    int *ticket;                           // [9][32] places of a launch's workgroups, as they start (groups > 1)
     unsigned long long *xchg;              // [R][2][2][np] position exchange between a replica's groups (by step parity)
     long long *esum;                       // [R] energy partial sums of a replica's groups
     double *acc;                           // [R][MAX_OBS][2]

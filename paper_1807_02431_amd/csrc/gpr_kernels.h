@@ -105,6 +105,7 @@ constexpr int SMALL_MAX = 256;
 constexpr int MAX_BATCH = 8;
 struct PersistBatch {
     int nitems;
+    int mapped;         // workgroups of the items with xcd set, which come first
     PersistItem it[MAX_BATCH];
 };
 

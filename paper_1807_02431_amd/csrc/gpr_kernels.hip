@@ -1816,15 +1816,39 @@ __device__ __forceinline__ bool cycle_start(const PersistItem &it, long long &s0
     return true;
 }
 
+// A workgroup's place in a launch whose workgroups wait for one another: in the order in which they
+// start, not by blockIdx.  Of the first `mapped` workgroups, those with equal blockIdx mod 8 keep that
+// residue (they are of one XCD) and the order counts among them; the order of the others counts among
+// all of those.  So when a launch gets only part of the device, beside another process's, the workgroups that do run
+// make whole replicas but for one in each of these rows; the whole ones end and make room, where
+// workgroups placed by blockIdx could all be waiting for others that have none.  (The last to ask
+// clears the counter for the next launch.)
+__device__ __forceinline__ int start_place(int *ticket, int mapped)
+{
+    __shared__ int place;
+    if (threadIdx.x == 0) {
+        const int b = (int)blockIdx.x, c = b < mapped ? b % 8 : 8;
+        int *const ctr = ticket + 32 * c;
+        const int total = c < 8 ? mapped / 8 : (int)gridDim.x - mapped;
+        const int t = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == total - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        place = c < 8 ? 8 * t + c : mapped + t;
+    }
+    __syncthreads();
+    return uni(place);
+}
+
 // One system, one replica per set: replicas roff, roff + 1, ... (a system with more replicas
 // than sets that fit at once takes several launches, each with the body inlined).
 __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
 {
     int set, g;
-    if (!persist_place(it, (int)blockIdx.x, set, g) || set + it.roff >= it.nrep) return;
     long long s0 = it.s0;
     int t0 = it.t0;
     if (it.cyc && !cycle_start(it, s0, t0)) return;
+    // (with one workgroup per replica too, though it waits for none: a choice here cost the step loop registers, 6 to 11 % of a step)
+    const int local = start_place(it.dev->ticket, it.xcd ? (int)gridDim.x : 0);
+    if (!persist_place(it, local, set, g) || set + it.roff >= it.nrep) return;
     persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1], it.sp.bi,
                     it.sp.bp, it.noise_ahead, set + it.roff, g, s0, it.nsteps, t0, it.sample, it.state_end);
 }
@@ -2257,10 +2281,11 @@ __device__ __noinline__ void persist_replica_call(const Dev *dev, int G, int lma
 __global__ void __launch_bounds__(1024) k_persist_batch(PersistBatch pb)
 {
     int k = 0;
-    while (k + 1 < pb.nitems && (int)blockIdx.x >= pb.it[k + 1].boff) ++k;
+    const int b = start_place(pb.it[0].dev->ticket, pb.mapped);
+    while (k + 1 < pb.nitems && b >= pb.it[k + 1].boff) ++k;
     const PersistItem &it = pb.it[k];
     int set, g;
-    if (!persist_place(it, (int)blockIdx.x - it.boff, set, g)) return;
+    if (!persist_place(it, b - it.boff, set, g)) return;
     for (int r = set; r < it.nrep; r += it.nsets) {
         persist_replica_call(it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1],
                              it.sp.bi, it.sp.bp, it.noise_ahead, r, g, it.s0, it.nsteps, it.t0, it.sample, it.state_end);
