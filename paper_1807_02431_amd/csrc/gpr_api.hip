@@ -25,7 +25,6 @@ using namespace gpr;
 namespace {
 
 constexpr double COULOMB_F = 138.935458;
-constexpr double margin_heavy = 1.35;
 enum { PH_IDLE = 0, PH_DECORR = 1, PH_DEPHASE = 2, PH_CONVERGED = 3, PH_PARALLEL = 4, PH_DEPHASE_FIXED = 5 };
 
 thread_local std::string g_thread_err;
@@ -1092,14 +1091,10 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
 
     // nonbonded constants and pair-list capacity
     d.cutoff_on = (D->kind == GPR_KIND_MOLECULAR && D->cutoff > 0) ? 1 : 0;
-    // list margins by mass: the light atoms (less than four times the lightest's mass) get half the
-    // skin, the others that times 1.35 sqrt(lightest mass / lightest heavy mass)
-    double mmin = D->mass[0], mheavy = INFINITY;
-    for (int i = 0; i < n; ++i) mmin = std::min(mmin, D->mass[i]);
-    for (int i = 0; i < n; ++i)
-        if (D->mass[i] >= 4.0 * mmin) mheavy = std::min(mheavy, D->mass[i]);
-    const double heavy = std::isfinite(mheavy) ? std::min(1.0, margin_heavy * std::sqrt(mmin / mheavy)) : 1.0;
-    d.im_light = std::isfinite(mheavy) ? (float)(0.5 / mmin) : 0.f;     // between 1/4 and 1 of the lightest's 1/m
+    // list margins by mass
+    const MarginRule margins = margin_rule(D->mass, n);
+    const double heavy = margins.heavy;
+    d.im_light = margins.im_light;
     {
         std::vector<unsigned char> cls((n + BLK - 1) / BLK, 0);
         for (int i = 0; i < n; ++i)

@@ -2,6 +2,7 @@
 // can compile it by itself.
 #pragma once
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace gpr {
@@ -46,6 +47,24 @@ inline AtomRanges atom_ranges(const std::vector<double> &work, int n, int np, in
     for (int g = 0; g < G; ++g) lmax = std::max(lmax, a.bnd[g + 1] - a.bnd[g]);
     a.lmax = (lmax + 15) / 16 * 16;
     return a;
+}
+
+// Pair-list margins by mass: an atom of less than four times the lightest's mass (light: 1/m above
+// im_light) may move half the skin between builds, any other one `heavy` times that, in proportion to
+// how much slower the lightest of them is, times 1.35 (measured on masses of 1 and 12 to 16: with 1.7, 2.2 and
+// 3.0, 20-step launches take 2 % less, 1,000-step launches 1 to 3 % more and plain steps 4 to 6 % more).
+struct MarginRule {
+    float im_light;       // 0: every atom is light
+    double heavy;
+};
+inline MarginRule margin_rule(const double *mass, int n)
+{
+    double mmin = mass[0], mheavy = INFINITY;
+    for (int i = 0; i < n; ++i) mmin = std::min(mmin, mass[i]);
+    for (int i = 0; i < n; ++i)
+        if (mass[i] >= 4.0 * mmin) mheavy = std::min(mheavy, mass[i]);
+    if (!std::isfinite(mheavy)) return {0.f, 1.0};
+    return {(float)(1.0 / mheavy), std::min(1.0, 1.35 * std::sqrt(mmin / mheavy))};
 }
 
 } // namespace gpr
