@@ -289,6 +289,13 @@ constexpr PickTable make_pick()
 }
 __device__ __constant__ const PickTable pick_table = make_pick();
 
+// The list entries (8 j) of block b's atoms j of residue q mod 4: the first in the low half, the second in
+// the high half.  Unsigned: from block 512 on the product passes 2^31, and the halves are meant to wrap.
+__host__ __device__ constexpr unsigned block_entries(unsigned b, unsigned q) { return b * (8u * BLK * 0x10001u) + 0x200000u + q * 0x80008u; }
+static_assert(block_entries(0, 3) == 0x00380018u && block_entries(511, 0) == 0x7FE07FC0u && block_entries(512, 1) == 0x80288008u &&
+                  block_entries(767, 3) == 0xBFF8BFD8u && block_entries(1023, 3) == 0xFFF8FFD8u,
+              "entries of the last blocks of any accepted size");
+
 // Pair lists of the atoms [iw, iw + 16) below iend, by one wave; all 64 lanes call it together with
 // the same arguments.  Lane 16 q + k owns sub-list (i, q) of atom i = iw + k: partners j = q (mod P),
 // j != i, not excluded, r^2 < list2 of the two atoms' classes, in ascending order; entry e is the
@@ -446,8 +453,7 @@ __device__ __forceinline__ int search_task(const GPR_CONST Dev &S, int r, int iw
                     }
                 }
                 const int e4 = (int)((p << 4) | (cnt4 & 12u));
-                const unsigned X = (unsigned)(b0 * (8 * BLK * 0x10001) + 0x200000) + (unsigned)q * 0x80008u;
-                const unsigned Y = (unsigned)(b1 * (8 * BLK * 0x10001) + 0x200000) + (unsigned)q * 0x80008u;
+                const unsigned X = block_entries((unsigned)b0, (unsigned)q), Y = block_entries((unsigned)b1, (unsigned)q);
                 const unsigned llo = plo | __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.x));
                 const unsigned lhi = phi | __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.y));
                 const unsigned olo = __builtin_amdgcn_perm(Y, X, (unsigned)__builtin_amdgcn_ds_bpermute(e4, (int)sel.z));
