@@ -52,16 +52,11 @@ struct gpr_system {
     // (run_shape), 1 the autotuner's, for launches of all replicas, 2 the caller's, for every launch
     int bt_from = 0, groups_from = 0;
     std::vector<double> work;  // per-atom work estimate that places the ranges
-    // bonded terms in the sorted order (kinds as in the bonded units), and the units laid out so far
-    std::vector<int4> term_idx[5];
-    std::vector<float4> term_prm[5];
-    struct Units {
-        std::vector<int> src;  // per record: 5 * (sorted term) + kind, or -1
-        std::vector<int> first;// first unit of each range, and the end
-        uint2 *bi = nullptr;
-        float4 *bp = nullptr;
-    };
-    Units units_plain, units_split[NSPLIT];
+    // bonded units of the plain path's ranges and of every split, one after the other
+    uint2 *unit_bi = nullptr;
+    float4 *unit_bp = nullptr;
+    int *unit_src = nullptr;   // per record: 5 * (sorted term) + kind, or -1
+    int n_records = 0;
     // force-field parameters as the caller gave them (gpr_set_params rewrites the device copies)
     std::vector<double> mass_h, eps_h, sig_h, q_h, tor_k_h, tor_phi0_h;
     std::vector<int> tor_n_h, tor_order, p14_order;   // sorted term -> caller's index
@@ -329,25 +324,28 @@ static RunShape run_shape(const gpr_system *S, int nrep)
 // The terms touching each of the atom ranges [bnd[k], bnd[k + 1]) in units of 64 terms of one kind
 // (the records of gpr_device.h): first the terms inside the range, the longest kinds first, then
 // those that reach outside it; a term's energy counts in the range that holds its smallest atom.
-static void write_units(const gpr_system *S, const std::vector<int> &bnd, gpr_system::Units &U, std::vector<uint2> &bi)
+// term[kind]: the terms' atoms (-1: none) in the sorted order.  The records go to the ends of bi and src; returns the
+// first unit of each range, counted from there, and the end.
+static std::vector<int> write_units(const std::vector<int4> *term, int n, const int *bnd, int nr, std::vector<uint2> &bi, std::vector<int> &src)
 {
-    const int nr = (int)bnd.size() - 1;
-    auto range_of = [&](int a) { return (int)(std::upper_bound(bnd.begin() + 1, bnd.end(), a) - bnd.begin()) - 1; };
+    std::vector<unsigned char> range(n);
+    for (int r = 0; r < nr; ++r) std::fill(range.begin() + bnd[r], range.begin() + bnd[r + 1], (unsigned char)r);
     // terms of (range, kind, inside or edge)
     std::vector<std::vector<int>> in((size_t)nr * 10);
     for (int k = 0; k < 5; ++k)
-        for (int t = 0; t < (int)S->term_idx[k].size(); ++t) {
-            const int4 q = S->term_idx[k][t];
+        for (int t = 0; t < (int)term[k].size(); ++t) {
+            const int4 q = term[k][t];
             const int at[4] = {q.x, q.y, q.z, q.w};
             int rg[4], m = 0;
             for (int a : at) {
                 if (a < 0) continue;
-                const int r = range_of(a);
+                const int r = range[a];
                 if (std::find(rg, rg + m, r) == rg + m) rg[m++] = r;
             }
             for (int j = 0; j < m; ++j) in[(size_t)rg[j] * 10 + k + (m > 1 ? BONDED_EDGE : 0)].push_back(t);
         }
-    U.first.assign(1, 0);
+    std::vector<int> first(1, 0);
+    const size_t base = src.size();
     for (int r = 0; r < nr; ++r) {
         for (int kk : {2, 7, 1, 6, 4, 9, 0, 5, 3, 8}) {
             const std::vector<int> &l = in[(size_t)r * 10 + kk];
@@ -357,7 +355,7 @@ static void write_units(const gpr_system *S, const std::vector<int> &bnd, gpr_sy
                 const unsigned kind0 = (unsigned)(kk & 3) << 14, kind1 = (unsigned)(kk >> 2) << 14;
                 unsigned f[4] = {kind0, kind1, 0u, 0u};
                 if (c < l.size()) {
-                    const int4 q = S->term_idx[k][l[c]];
+                    const int4 q = term[k][l[c]];
                     const int at[4] = {q.x, q.y, q.z, q.w};
                     int mn = q.x;
                     for (int j = 0; j < 4; ++j) {
@@ -368,56 +366,55 @@ static void write_units(const gpr_system *S, const std::vector<int> &bnd, gpr_sy
                     f[2] |= (mn >= bnd[r] && mn < bnd[r + 1] ? 0x4000u : 0u) | 0x8000u;
                 }
                 bi.push_back(make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16)));
-                U.src.push_back(c < l.size() ? 5 * l[c] + k : -1);
+                src.push_back(c < l.size() ? 5 * l[c] + k : -1);
             }
         }
-        U.first.push_back((int)(U.src.size() / 64));
+        first.push_back((int)((src.size() - base) / 64));
     }
+    return first;
 }
 
-// the records' parameters, from the terms' current ones (nothing for units not laid out)
-static hipError_t write_unit_params(gpr_system *S, const gpr_system::Units &U)
+// The records' parameters, from the terms' current ones
+static hipError_t write_unit_params(gpr_system *S)
 {
-    if (!U.bp || U.src.empty()) return hipSuccess;
-    std::vector<float4> p(U.src.size(), make_float4(0.f, 0.f, 0.f, 0.f));
-    for (size_t c = 0; c < p.size(); ++c)
-        if (U.src[c] >= 0) p[c] = S->term_prm[U.src[c] % 5][U.src[c] / 5];
-    const hipError_t e = hipMemcpyAsync(U.bp, p.data(), sizeof(float4) * p.size(), hipMemcpyHostToDevice, S->stream);
-    return e == hipSuccess ? hipStreamSynchronize(S->stream) : e;
+    if (S->n_records == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_unit_params, dim3((S->n_records + 255) / 256), dim3(256), 0, S->stream, S->d.tp, S->unit_src, S->n_records, S->unit_bp);
+    return hipGetLastError();
 }
 
-static hipError_t make_units(gpr_system *S, const std::vector<int> &bnd, gpr_system::Units &U)
+// The units of the plain path's blocks of 256 atoms and of every split that a launch may take (the
+// caller's 1 to 8 workgroups per replica, more where run_shape takes them), in one allocation, so that no
+// launch lays out any.
+static gpr_status lay_units(gpr_system *S, const std::vector<int4> *term)
 {
-    if (U.bi) return hipSuccess;
+    const int n = S->n;
     std::vector<uint2> bi;
-    write_units(S, bnd, U, bi);
-    hipError_t e = dalloc(S, &U.bp, bi.size());
-    if (e == hipSuccess) e = upload(S, &U.bi, bi);
-    if (e == hipSuccess) e = write_unit_params(S, U);
-    return e;
-}
-
-// The split with its bonded units.  Those of the shapes that launches take by themselves are laid out
-// when the path or the shape is set (0.1 ms each), others when a launch first needs them (never under
-// capture: captured launches take them before the capture begins).
-static gpr_status split_units(gpr_system *S, Split &sp)
-{
-    gpr_system::Units &U = S->units_split[split_index(sp.G)];
-    HIPCHK(S, make_units(S, std::vector<int>(sp.bnd, sp.bnd + sp.G + 1), U));
-    for (int g = 0; g <= sp.G; ++g) sp.bu[g] = U.first[g];
-    sp.bi = U.bi;
-    sp.bp = U.bp;
-    return GPR_OK;
-}
-static gpr_status shape_units(gpr_system *S)
-{
-    for (const int nrep : {S->R, 1}) {
-        const RunShape sh = run_shape(S, nrep);
-        if (sh.small) continue;
-        Split sp = *sh.sp;
-        const gpr_status rc = split_units(S, sp);
-        if (rc) return rc;
+    std::vector<int> src, bnd, at(NSPLIT, -1);
+    for (int a = 0; a < n; a += 256) bnd.push_back(a);
+    bnd.push_back(n);
+    const std::vector<int> plain = write_units(term, n, bnd.data(), (int)bnd.size() - 1, bi, src);
+    for (int k = 0; k < NSPLIT; ++k) {
+        Split &sp = S->splits[k];
+        if (sp.G < 1 << k) {                                // (fewer groups: the units of that split)
+            sp = S->splits[split_index(sp.G)];
+            at[k] = at[split_index(sp.G)];
+            continue;
+        }
+        if (!S->persist_ok || !S->split_ok[k] || (k > 3 && n < 32 << k)) continue;
+        at[k] = (int)src.size();
+        const std::vector<int> first = write_units(term, n, sp.bnd, sp.G, bi, src);
+        std::copy(first.begin(), first.end(), sp.bu);
     }
+    HIPCHK(S, upload(S, &S->unit_bi, bi));
+    HIPCHK(S, upload(S, &S->unit_src, src));
+    HIPCHK(S, dalloc(S, &S->unit_bp, src.size()));
+    S->n_records = (int)src.size();
+    HIPCHK(S, write_unit_params(S));
+    for (int k = 0; k < NSPLIT; ++k)
+        if (at[k] >= 0) { S->splits[k].bi = S->unit_bi + at[k]; S->splits[k].bp = S->unit_bp + at[k]; }
+    S->d.pl_bi = S->unit_bi;
+    S->d.pl_bp = S->unit_bp;
+    HIPCHK(S, upload(S, (int **)&S->d.pl_first, plain));
     return GPR_OK;
 }
 
@@ -450,7 +447,6 @@ static hipError_t write_params(gpr_system *S)
                                (float)S->tor_n_h[t]);
         }
         e = hipMemcpyAsync((void *)T.t_p, p.data(), sizeof(float4) * T.nt, hipMemcpyHostToDevice, S->stream);
-        S->term_prm[2] = p;
     }
     if (e == hipSuccess && mol && T.n14) {
         std::vector<float4> p(T.n14);
@@ -462,11 +458,8 @@ static hipError_t write_params(gpr_system *S)
                                (float)(COULOMB_F * S->q_h[ij.x] * S->q_h[ij.y] * S->scale14), 0.f);
         }
         e = hipMemcpyAsync((void *)T.p_p, p.data(), sizeof(float4) * T.n14, hipMemcpyHostToDevice, S->stream);
-        S->term_prm[4] = p;
     }
-    if (e == hipSuccess) e = write_unit_params(S, S->units_plain);
-    for (auto &u : S->units_split)
-        if (e == hipSuccess) e = write_unit_params(S, u);
+    if (e == hipSuccess) e = write_unit_params(S);
     if (e == hipSuccess) e = hipStreamSynchronize(S->stream);
     return e;
 }
@@ -530,10 +523,7 @@ static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt,
     it = PersistItem{};
     it.dev = S->d_dev;
     it.sp = sp;
-    {
-        const gpr_status rc = split_units(S, it.sp);
-        if (rc) return rc;
-    }
+    if (!sp.bi) return fail(S, GPR_EDEVICE, "no bonded units for this split");
     it.nrep = nrep;
     it.boff = 0;
     if (G == 1 && cap_blocks < 0) {
@@ -1013,7 +1003,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     // bonded topology, each type sorted by smallest atom
     Topo &T = d.tp;
     std::vector<int> order;
-    auto wide = [](const float2 &v) { return make_float4(v.x, v.y, 0.f, 0.f); };
+    std::vector<int4> term[5];         // by kind, as in the bonded units
     if (D->kind == GPR_KIND_MOLECULAR) {
         {
             sort_terms(D->bond_atoms, D->n_bonds, 2, order);
@@ -1024,7 +1014,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                 p[k] = make_float2((float)D->bond_r0[t], (float)D->bond_k[t]);
             }
             T.nb = D->n_bonds;
-            for (int k = 0; k < T.nb; ++k) { S->term_idx[0].push_back(make_int4(ij[k].x, ij[k].y, -1, -1)); S->term_prm[0].push_back(wide(p[k])); }
+            for (int k = 0; k < T.nb; ++k) term[0].push_back(make_int4(ij[k].x, ij[k].y, -1, -1));
             HIPCHK(S, upload(S, (int2 **)&T.b_ij, ij)); HIPCHK(S, upload(S, (float2 **)&T.b_p, p));
         }
         {
@@ -1036,7 +1026,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                 p[k] = make_float2((float)D->angle_theta0[t], (float)D->angle_k[t]);
             }
             T.na = D->n_angles;
-            for (int k = 0; k < T.na; ++k) { S->term_idx[1].push_back(make_int4(ijk[k].x, ijk[k].y, ijk[k].z, -1)); S->term_prm[1].push_back(wide(p[k])); }
+            for (int k = 0; k < T.na; ++k) term[1].push_back(make_int4(ijk[k].x, ijk[k].y, ijk[k].z, -1));
             HIPCHK(S, upload(S, (int4 **)&T.a_ijk, ijk)); HIPCHK(S, upload(S, (float2 **)&T.a_p, p));
         }
         {
@@ -1050,8 +1040,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)std::sin(D->torsion_phi0[t]), (float)D->torsion_n[t]);
             }
             T.nt = D->n_torsions;
-            S->term_idx[2] = q;
-            S->term_prm[2] = p;
+            term[2] = q;
             S->tor_order = order;
             HIPCHK(S, upload(S, (int4 **)&T.t_ijkl, q)); HIPCHK(S, upload(S, (float4 **)&T.t_p, p));
         }
@@ -1065,8 +1054,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)D->restraint_ref[3 * t + 2], (float)D->restraint_k[t]);
             }
             T.nr = D->n_restraints;
-            for (int k = 0; k < T.nr; ++k) S->term_idx[3].push_back(make_int4(ia[k], -1, -1, -1));
-            S->term_prm[3] = p;
+            for (int k = 0; k < T.nr; ++k) term[3].push_back(make_int4(ia[k], -1, -1, -1));
             HIPCHK(S, upload(S, (int **)&T.r_i, ia)); HIPCHK(S, upload(S, (float4 **)&T.r_p, p));
         }
         {
@@ -1082,8 +1070,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
                                    (float)(COULOMB_F * D->charge[i] * D->charge[j] * D->scale14), 0.f);
             }
             T.n14 = D->n_pairs14;
-            for (int k = 0; k < T.n14; ++k) S->term_idx[4].push_back(make_int4(ij[k].x, ij[k].y, -1, -1));
-            S->term_prm[4] = p;
+            for (int k = 0; k < T.n14; ++k) term[4].push_back(make_int4(ij[k].x, ij[k].y, -1, -1));
             S->p14_order = order;
             HIPCHK(S, upload(S, (int2 **)&T.p_ij, ij)); HIPCHK(S, upload(S, (float4 **)&T.p_p, p));
         }
@@ -1231,22 +1218,11 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     }
     HIPCHK(S, write_params(S));
     {
-        // bonded units of the plain path's blocks of 256 atoms
-        std::vector<int> bnd;
-        for (int a = 0; a < n; a += 256) bnd.push_back(a);
-        bnd.push_back(n);
-        HIPCHK(S, make_units(S, bnd, S->units_plain));
-        d.pl_bi = S->units_plain.bi;
-        d.pl_bp = S->units_plain.bp;
-        HIPCHK(S, upload(S, (int **)&d.pl_first, S->units_plain.first));
-    }
-    {
         int dev = 0;
         HIPCHK(S, hipGetDevice(&dev));
         S->dev = dev < MAX_DEV ? dev : MAX_DEV - 1;
         HIPCHK(S, hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev));
     }
-    HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
 
     // scratch for the per-check bookkeeping
     HIPCHK(S, hipHostMalloc((void **)&S->st_host, sizeof(Status), hipHostMallocDefault));
@@ -1345,13 +1321,16 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
         } else {
             G = 1;
         }
-        S->groups = G;
-        S->split = S->splits[split_index(G)];
         for (int k = 0; k < NSPLIT; ++k) {
             bool all2 = false;
             HIPCHK(S, usable(1 << k, S->split_ok[k], all2));
         }
+        const gpr_status rc = lay_units(S, term);
+        if (rc) return rc;
+        S->groups = G;
+        S->split = S->splits[split_index(G)];
     }
+    HIPCHK(S, upload(S, &S->d_dev, std::vector<Dev>(1, d)));
 
     // initial velocities, copies into every replica, forces, Omega and the observable shift
     if (!D->vel) {
@@ -1451,10 +1430,6 @@ extern "C" gpr_status gpr_set_path(gpr_system *S, int32_t path)
     if (!S) return fail(nullptr, GPR_EINVAL, "NULL system");
     if (path != GPR_PATH_PLAIN && path != GPR_PATH_PERSISTENT) return fail(S, GPR_EINVAL, "bad path");
     if (path == GPR_PATH_PERSISTENT && !S->persist_ok) return fail(S, GPR_EINVAL, "system too large for the persistent path");
-    if (path == GPR_PATH_PERSISTENT) {
-        const gpr_status rc = shape_units(S);
-        if (rc) return rc;
-    }
     S->path = path;
     return GPR_OK;
 }
@@ -1485,7 +1460,7 @@ extern "C" gpr_status gpr_set_launch(gpr_system *S, int32_t block_threads, int32
         S->groups = groups_per_replica;
         S->split = S->splits[split_index(groups_per_replica)];
     }
-    return S->path == GPR_PATH_PERSISTENT ? shape_units(S) : GPR_OK;
+    return GPR_OK;
 }
 
 // Launch-shape autotuner of the persistent path: every (threads per workgroup, workgroups per

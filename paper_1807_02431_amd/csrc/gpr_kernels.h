@@ -134,6 +134,7 @@ __host__ __device__ inline bool persist_place(const PersistItem &it, int local, 
 __global__ void k_persist(PersistItem it);
 __global__ void k_persist_small(PersistItem it);
 __global__ void k_persist_batch(PersistBatch pb);
+__global__ void k_unit_params(Topo T, const int *src, int n, float4 *bp);
 __global__ void k_grad_nb(const Dev *__restrict__ Sp, const double *w);
 __global__ void k_grad_terms(const Dev *__restrict__ Sp, const double *w);
 __global__ void k_grad_finish(const Dev *__restrict__ Sp, double *d_eps, double *d_sigma, double *d_charge, double *d_tk);

@@ -1045,6 +1045,22 @@ __global__ void __launch_bounds__(256) k_state(const Dev *__restrict__ Sp, int r
     if (threadIdx.x == 0) S.state[r] = id;
 }
 
+// parameters of the n records of the bonded units, from those of the terms (src: 5 (sorted term) + kind, or -1)
+__global__ void __launch_bounds__(256) k_unit_params(Topo T, const int *src, int n, float4 *bp)
+{
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const int t = src[c] / 5, kind = src[c] < 0 ? -1 : src[c] % 5;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (kind == 0 || kind == 1) {
+        const float2 q = kind == 0 ? T.b_p[t] : T.a_p[t];
+        p = make_float4(q.x, q.y, 0.f, 0.f);
+    } else if (kind >= 0) {
+        p = kind == 2 ? T.t_p[t] : kind == 3 ? T.r_p[t] : T.p_p[t];
+    }
+    bp[c] = p;
+}
+
 // ================================================================== force-field parameter gradient
 // dU_r/dtheta for theta = (eps_i, sigma_i, q_i, torsion k_t), weighted by w[r] and summed over
 // the replicas in 2^-32 fixed point (gacc).  With eps_ij = sqrt(eps_i eps_j), sigma_ij =
