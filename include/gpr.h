@@ -424,8 +424,9 @@ gpr_status gpr_profile_read(gpr_system *sys, double *ms, int64_t *launches);
 /* Phase timers of the persistent kernel, for measurement: only the library's timer build
  * (libgpr_hip_probe.so, the same sources built with GPR_PHASE_PROBE) records them; the
  * product build returns GPR_EINVAL.  out ([R][8][11] doubles, host, caller-owned) receives per
- * replica r and workgroup g < 8 of its replica (rows g >= G stay 0): the microseconds spent since
- * the last read in the launch prologue (staging), the integrator (B A O A and the position
+ * replica r and workgroup g < 8 of its replica (rows g >= G stay 0; launches of few replicas may
+ * take 16 or 32, of which the others are left out: gpr_set_launch(sys, 0, 8) has all timed): the
+ * microseconds spent since the last read in the launch prologue (staging), the integrator (B A O A and the position
  * stores), the exchange (the other groups' positions), the pair-list rebuild, the forces
  * (bonded and pair terms), the step's tail (closing B, samples) and the epilogue (write back);
  * the number of steps and of pair-list rebuilds; then the start and the end of the group's

@@ -184,7 +184,6 @@ long long count_samples(long long t_old, long long t_new, int t_gr) { return t_n
 
 static void drop_cycle_graphs(gpr_system *S);
 
-// event pair around the next timed launch (created on first use, reused afterwards)
 // one more pair of timing events (created ahead by gpr_profile, so that a timed call does not
 // create them; more only when a call launches the kernel more often than that)
 static hipError_t prof_add_pair(gpr_system *S)
@@ -202,6 +201,7 @@ static hipError_t prof_add_pair(gpr_system *S)
     return hipSuccess;
 }
 
+// event pair around the next timed launch
 static hipError_t prof_begin(gpr_system *S)
 {
     if (!S->prof) return hipSuccess;
@@ -490,8 +490,6 @@ static gpr_status launch_forces(gpr_system *S, int r_off, int nrep, long long s,
     return GPR_OK;
 }
 
-// advances replicas [0, nrep) by nsteps from local step counter t0; sample: accumulate the
-// observables of workers every t_gr; state_end: state ids at the end
 // Workgroups of the persistent kernel that the device holds at once for (bt, lds): the
 // occupancy query, kept per system and launch shape.
 static gpr_status persist_capacity(gpr_system *S, int bt, size_t lds, int &cap)
@@ -743,6 +741,8 @@ static gpr_status plain_steps(gpr_system *S, int nrep, long long nsteps, long lo
     return GPR_OK;
 }
 
+// advances replicas [0, nrep) by nsteps from local step counter t0; sample: accumulate the
+// observables of workers every t_gr; state_end: state ids at the end
 static gpr_status run_steps(gpr_system *S, int nrep, long long nsteps, long long t0, bool sample, bool state_end)
 {
     if (nsteps <= 0) {
@@ -1285,7 +1285,7 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     }
     {
         // persistent split: the fewest workgroups per replica (1, 2, 4 or 8) whose LDS fits, then
-        // more while each keeps >= 256 atoms; with more than one, every workgroup of the grid
+        // more while each keeps >= 256 atoms (launches of few replicas take more, see run_shape); with more than one, every workgroup of the grid
         // must be resident at once (the grid is sized to what the device holds)
         int cus = 0;
         HIPCHK(S, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -2084,10 +2084,9 @@ static void drop_cycle_graphs(gpr_system *S)
 
 // The captured run of S->cycles check cycles of the convergence step (op GPR_OP_DEPHASE) or
 // the parallel step on the persistent path, captured on a stream of its own the first time
-// it is needed.  Per cycle: the replicas' barrier counters cleared by a kernel, the persistent
-// launch(es) of one check period with the state test at the end, then the check with its
-// clone-on-kill copies.  Steps, check indices and Omega come from the cycle record, which the
-// host writes before each replay.
+// it is needed.  Per cycle: the persistent launch(es) of one check period with the state test at
+// the end, then the check with its clone-on-kill copies.  Steps, check indices and Omega come from
+// the cycle record, which the host writes before each replay.
 static gpr_status cycle_graph(gpr_system *S, int op, gpr_system::CGraph *out)
 {
     for (auto &g : S->cgraphs)

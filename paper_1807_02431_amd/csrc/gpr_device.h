@@ -27,7 +27,6 @@ namespace gpr {
 
 constexpr int P = 4;            // lanes per atom in the pair loop (sub-lists by j mod P)
 constexpr int MAX_OBS = 8;
-constexpr int CHMAX = 4;        // atoms per thread in the integrator mapping
 constexpr int BLK = 8;          // consecutive atoms per bounding box in the pair search (two per MFMA tile)
 constexpr int WBLK = 64;        // LDS ints per wave: the queue of near blocks in the pair search
 constexpr double FIX = 4294967296.0;          // 2^32
@@ -35,7 +34,7 @@ constexpr double FIX_INV = 2.3283064365386963e-10;  // 2^-32
 constexpr float FMAX_FIX = 2.5e5f;             // |F| beyond this (kJ/mol/nm) counts as unstable
 constexpr float FSAT = 524287.0f;              // 2^19 - 1: fixed-point conversions saturate here
 constexpr float FAR = 1.0e15f;                 // coordinate of the dummy atom
-constexpr int SPIN_MAX = 1 << 22;              // bound on a barrier wait (then ERR_BARRIER)
+constexpr int SPIN_MAX = 1 << 22;              // bound on a wait for other workgroups (then ERR_BARRIER)
 // energy codes of the plain-path kernels: 0 / 1 given by the host; DCLK_* take the step s and
 // the sampling decision from the device clock (so that a captured cycle of steps replays)
 constexpr int DCLK_SAMPLE = 2;                 // workers' observables sampled every t_GR steps
@@ -171,14 +170,11 @@ typedef unsigned gv_u2 __attribute__((ext_vector_type(2)));
 typedef unsigned gv_u4 __attribute__((ext_vector_type(4)));
 typedef float gv_f2 __attribute__((ext_vector_type(2)));
 typedef float gv_f4 __attribute__((ext_vector_type(4)));
-typedef float gv_f3 __attribute__((ext_vector_type(3)));   // 16-byte size and alignment, 12-byte loads
 __device__ __forceinline__ int2 gld(const GPR_GLOBAL int2 *p) { const gv_i2 v = *(const GPR_GLOBAL gv_i2 *)p; return make_int2(v.x, v.y); }
 __device__ __forceinline__ int4 gld(const GPR_GLOBAL int4 *p) { const gv_i4 v = *(const GPR_GLOBAL gv_i4 *)p; return make_int4(v.x, v.y, v.z, v.w); }
 __device__ __forceinline__ uint2 gld(const GPR_GLOBAL uint2 *p) { const gv_u2 v = *(const GPR_GLOBAL gv_u2 *)p; return make_uint2(v.x, v.y); }
 __device__ __forceinline__ float2 gld(const GPR_GLOBAL float2 *p) { const gv_f2 v = *(const GPR_GLOBAL gv_f2 *)p; return make_float2(v.x, v.y); }
 __device__ __forceinline__ float4 gld(const GPR_GLOBAL float4 *p) { const gv_f4 v = *(const GPR_GLOBAL gv_f4 *)p; return make_float4(v.x, v.y, v.z, v.w); }
-__device__ __forceinline__ void gst(GPR_GLOBAL uint2 *p, uint2 v) { gv_u2 w; w.x = v.x; w.y = v.y; *(GPR_GLOBAL gv_u2 *)p = w; }
-__device__ __forceinline__ void gst(GPR_GLOBAL unsigned long long *p, unsigned long long v) { *p = v; }
 
 // ------------------------------------------------------------------ Philox4x32-10
 // Salmon, Moraes, Dror, Shaw (SC'11): ten rounds; each multiplies words 0 and 2 by fixed

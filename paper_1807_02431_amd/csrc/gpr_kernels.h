@@ -38,7 +38,7 @@ constexpr int NO_HALT = 0x7FFFFFFF;
 // summed over launches), then the clock at the start and at the end of its last launch.
 enum { PH_PROLOGUE = 0, PH_INTEGRATE, PH_EXCHANGE, PH_REBUILD, PH_FORCES, PH_TAIL, PH_EPILOGUE, PH_NSTEP, PH_NREBUILD,
        PH_START, PH_END, NPHASE };
-constexpr int PHASE_MAX_R = 4096, PHASE_MAX_G = 8;
+constexpr int PHASE_MAX_R = 4096, PHASE_MAX_G = 8;    // (gpr_phase_read's rows; further workgroups of a replica are left out)
 // Host side: copies the slots of replicas [0, R) ([R][PHASE_MAX_G][NPHASE]) to out and clears
 // them, on the stream; hipErrorNotSupported in a build without the timers.
 hipError_t phase_take(unsigned long long *out, int R, hipStream_t st);

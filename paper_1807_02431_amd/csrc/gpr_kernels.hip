@@ -4,7 +4,7 @@
 //   plain      : per step, k_integrate (B A O A of Eq. 1's BAOAB discretisation) and k_forces (bonded
 //                and pair forces, the closing B kick, pair-list rebuild when due); observables and
 //                state tests as separate launches;
-//   persistent : k_persist (k_persist_batch: several systems) advances each replica by one to eight
+//   persistent : k_persist (k_persist_batch: several systems) advances each replica by one to 32
 //                workgroups for a whole check period, its positions, parameters, velocities and
 //                forces in LDS; k_persist_small does so for small replicas, one workgroup each, with
 //                their bonded terms in LDS too and no pair lists.

@@ -321,7 +321,7 @@ class System:
         return ms.value, n.value
 
     def phase_read(self):
-        """gpr_phase_read (timer build only): [R, 8, 11] per replica and workgroup, the
+        """gpr_phase_read (timer build only): [R, 8, 11] per replica and workgroup (its first 8), the
         microseconds in each of PHASES and the counts of steps and of pair-list rebuilds since
         the last read, then the start and end of the last launch (µs after its earliest start)."""
         out = np.zeros((self.R, 8, 11))
