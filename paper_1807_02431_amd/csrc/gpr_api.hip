@@ -93,9 +93,9 @@ struct gpr_system {
     CycRec *cyc_dev = nullptr, *cyc_host = nullptr;
     Status *stc_dev = nullptr, *stc_host = nullptr;   // [cycles] statuses of a replay
     // scratch
-    Status *st_host = nullptr;      // page-locked: the status of the last check, written by k_check
-    long long *adv_fec = nullptr;   // page-locked [R]: first exit checks of an advance
-    char *rb = nullptr;             // page-locked [rb_bytes]: results on their way to the caller (k_read)
+    Status *st_host = nullptr;      // page-locked, the three in one allocation: the status of the last check, written by k_check
+    long long *adv_fec = nullptr;   // [R]: first exit checks of an advance
+    char *rb = nullptr;             // [rb_bytes]: results on their way to the caller (k_read)
     size_t rb_bytes = 0;
     bool gacc_dirty = false;        // a backward pass did not get to clear gacc
     bool lists_old = false;         // some replica's pair lists may not be those of its positions (k_persist_small
@@ -141,20 +141,20 @@ gpr_status fail(gpr_system *s, gpr_status code, const std::string &msg)
     } while (0)
 
 template <class T>
-hipError_t dalloc(gpr_system *s, T **p, size_t count)
+hipError_t dalloc(gpr_system *s, T **p, size_t count, bool clear = true)
 {
     void *q = nullptr;
     hipError_t e = hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T));
     if (e != hipSuccess) return e;
     s->bufs.push_back(q);
     *p = (T *)q;
-    return hipMemset(q, 0, std::max<size_t>(count, 1) * sizeof(T));
+    return clear ? hipMemset(q, 0, std::max<size_t>(count, 1) * sizeof(T)) : hipSuccess;
 }
 
 template <class T>
 hipError_t upload(gpr_system *s, T **p, const std::vector<T> &h)
 {
-    hipError_t e = dalloc(s, p, h.size());
+    hipError_t e = dalloc(s, p, h.size(), h.empty());
     if (e != hipSuccess || h.empty()) return e;
     return hipMemcpy(*p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
 }
@@ -638,7 +638,11 @@ static gpr_status check_layout(gpr_system *S, const PersistBatch &pb, int nblock
                 return fail(S, GPR_EDEVICE, "persistent launch layout: workgroup placement");
         }
         next = it.boff + it.nsets * sp.G;
+        // the workgroups of mapped items come first, in whole rows of eight
+        if (!single && it.xcd && (next > pb.mapped || next % 8)) return fail(S, GPR_EDEVICE, "persistent launch layout: mapped items");
+        if (!single && !it.xcd && it.boff < pb.mapped) return fail(S, GPR_EDEVICE, "persistent launch layout: mapped items");
     }
+    if (single && pb.it[0].xcd && nblocks % 8) return fail(S, GPR_EDEVICE, "persistent launch layout: mapped items");
     if (next != nblocks) return fail(S, GPR_EDEVICE, "persistent launch layout: grid size");
     return GPR_OK;
 }
@@ -907,8 +911,6 @@ extern "C" void gpr_system_destroy(gpr_system *S)
     for (hipEvent_t e : S->ev_a) (void)hipEventDestroy(e);
     for (hipEvent_t e : S->ev_b) (void)hipEventDestroy(e);
     if (S->st_host) (void)hipHostFree(S->st_host);
-    if (S->adv_fec) (void)hipHostFree(S->adv_fec);
-    if (S->rb) (void)hipHostFree(S->rb);
     delete S;
 }
 
@@ -1225,10 +1227,15 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     }
 
     // scratch for the per-check bookkeeping
-    HIPCHK(S, hipHostMalloc((void **)&S->st_host, sizeof(Status), hipHostMallocDefault));
-    HIPCHK(S, hipHostMalloc((void **)&S->adv_fec, sizeof(long long) * R, hipHostMallocDefault));
     S->rb_bytes = std::max<size_t>((size_t)6 * np * sizeof(float), (size_t)R * MAX_OBS * 16 + MAX_OBS * 8);
-    HIPCHK(S, hipHostMalloc((void **)&S->rb, S->rb_bytes, hipHostMallocDefault));
+    {
+        const size_t at_fec = (sizeof(Status) + 255) / 256 * 256, at_rb = at_fec + (sizeof(long long) * R + 255) / 256 * 256;
+        char *host = nullptr;
+        HIPCHK(S, hipHostMalloc((void **)&host, at_rb + S->rb_bytes, hipHostMallocDefault));
+        S->st_host = (Status *)host;
+        S->adv_fec = (long long *)(host + at_fec);
+        S->rb = host + at_rb;
+    }
     HIPCHK(S, dalloc(S, &S->donor, R));
     HIPCHK(S, dalloc(S, &S->surv, R));
     HIPCHK(S, dalloc(S, &S->fec, R));
@@ -1285,8 +1292,9 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
     }
     {
         // persistent split: the fewest workgroups per replica (1, 2, 4 or 8) whose LDS fits, then
-        // more while each keeps >= 256 atoms (launches of few replicas take more, see run_shape); with more than one, every workgroup of the grid
-        // must be resident at once (the grid is sized to what the device holds)
+        // more while each keeps >= 256 atoms (launches of few replicas take more, see run_shape);
+        // with more than one, every workgroup of the grid must be resident at once (the grid is
+        // sized to what the device holds)
         int cus = 0;
         HIPCHK(S, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         S->max_coresident = cus;
@@ -1304,27 +1312,15 @@ static gpr_status create_impl(const gpr_system_desc *D, gpr_system *S)
             return e;
         };
         for (int k = 0; k < NSPLIT; ++k) S->splits[k] = make_split(S->work, n, np, 1 << k);
+        bool all[NSPLIT] = {};
+        for (int k = 0; k < NSPLIT; ++k) HIPCHK(S, usable(1 << k, S->split_ok[k], all[k]));
         int G = 1;
-        bool ok = false, all = false;
-        for (; G <= 8; G *= 2) {
-            HIPCHK(S, usable(G, ok, all));
-            if (ok) break;
-        }
-        S->persist_ok = ok ? 1 : 0;
-        if (ok) {
-            while (G < 8 && (n + 2 * G - 1) / (2 * G) >= 256) {
-                bool ok2 = false, all2 = false;
-                HIPCHK(S, usable(2 * G, ok2, all2));
-                if (!ok2 || !all2) break;
-                G *= 2;
-            }
-        } else {
+        while (G <= 8 && !S->split_ok[split_index(G)]) G *= 2;
+        S->persist_ok = G <= 8 ? 1 : 0;
+        if (S->persist_ok)
+            while (G < 8 && (n + 2 * G - 1) / (2 * G) >= 256 && all[split_index(2 * G)]) G *= 2;
+        else
             G = 1;
-        }
-        for (int k = 0; k < NSPLIT; ++k) {
-            bool all2 = false;
-            HIPCHK(S, usable(1 << k, S->split_ok[k], all2));
-        }
         const gpr_status rc = lay_units(S, term);
         if (rc) return rc;
         S->groups = G;
