@@ -250,7 +250,8 @@ gpr_status gpr_set_graph(gpr_system *sys, int32_t cycle_steps);
 /* Autotuner of the persistent path's launch shape: every (threads per workgroup in {256, 512,
  * 768, 1024}, workgroups per replica in {1, 2, 4, 8}) that fits the device is timed over nsteps
  * steps from the same saved state, and the fastest becomes the launch shape (written to
- * *block_threads and *groups when not NULL).  The state is restored afterwards (every pair list
+ * *block_threads and *groups when not NULL), unless what launches take by themselves, timed too, is
+ * faster still: that stays then.  The state is restored afterwards (every pair list
  * is rebuilt at the next step), so later results are those of a run without the call.  Device
  * scratch for one copy of the replicas' state is allocated and freed within the call.  EINVAL
  * if nsteps < 1 or the persistent path does not fit. */
