@@ -93,7 +93,8 @@ struct gpr_system {
     CycRec *cyc_dev = nullptr, *cyc_host = nullptr;
     Status *stc_dev = nullptr, *stc_host = nullptr;   // [cycles] statuses of a replay
     // scratch
-    Status *st_host = nullptr;      // page-locked, the three in one allocation: the status of the last check, written by k_check
+    // page-locked, the three in one allocation:
+    Status *st_host = nullptr;      // the status of the last check, written by k_check
     long long *adv_fec = nullptr;   // [R]: first exit checks of an advance
     char *rb = nullptr;             // [rb_bytes]: results on their way to the caller (k_read)
     size_t rb_bytes = 0;
@@ -324,8 +325,8 @@ static RunShape run_shape(const gpr_system *S, int nrep)
 // The terms touching each of the atom ranges [bnd[k], bnd[k + 1]) in units of 64 terms of one kind
 // (the records of gpr_device.h): first the terms inside the range, the longest kinds first, then
 // those that reach outside it; a term's energy counts in the range that holds its smallest atom.
-// term[kind]: the terms' atoms (-1: none) in the sorted order.  The records go to the ends of bi and src; returns the
-// first unit of each range, counted from there, and the end.
+// term[kind]: the terms' atoms (-1: none) in the sorted order.  The records go to the ends of bi and
+// src; returns the first unit of each range, counted from there, and the end.
 static std::vector<int> write_units(const std::vector<int4> *term, int n, const int *bnd, int nr, std::vector<uint2> &bi, std::vector<int> &src)
 {
     std::vector<unsigned char> range(n);
@@ -383,8 +384,8 @@ static hipError_t write_unit_params(gpr_system *S)
 }
 
 // The units of the plain path's blocks of 256 atoms and of every split that a launch may take (the
-// caller's 1 to 8 workgroups per replica, more where run_shape takes them), in one allocation, so that no
-// launch lays out any.
+// caller's 1 to 8 workgroups per replica, more where run_shape takes them), in one allocation, so
+// that no launch lays out any.
 static gpr_status lay_units(gpr_system *S, const std::vector<int4> *term)
 {
     const int n = S->n;
@@ -510,10 +511,10 @@ static gpr_status persist_capacity(gpr_system *S, int bt, size_t lds, int &cap)
 // shared by at most capacity / G sets (cap_blocks < 0: the whole device), so that the grid is
 // no larger than what the device holds at once, and every workgroup gets a CU as soon as the
 // device is free of other work.  (Other kernels hold the CUs it needs only until they end, and
-// launches that wait for workgroups of their own take room first, see admit; should a group still wait
-// longer than the bounded spin, the call reports GPR_EDEVICE, never hangs.)  No cooperative
-// launch: it adds tens of microseconds to each launch and is refused while another process
-// holds the device's cooperative resources.
+// launches that wait for workgroups of their own take room first, see admit, and places as they
+// start, see start_place; should a group still wait longer than the bounded spin, the call reports
+// GPR_EDEVICE, never hangs.)  No cooperative launch: it adds tens of microseconds to each launch
+// and is refused while another process holds the device's cooperative resources.
 static gpr_status persist_item(gpr_system *S, const Split &sp, int nrep, int bt, size_t lds, int cap_blocks,
                                PersistItem &it, int &nblocks)
 {
@@ -586,10 +587,10 @@ static bool hold(gpr_system *S, int units, bool wait)
     return true;
 }
 
-// The shape and item of a launch that there is room for beside the launches of other streams that wait for
-// their own workgroups too.  While others have room or wait for it, a launch takes no more workgroups per
-// replica than one of all replicas does; where that has no room, fewer, down to one, which needs
-// none; and it waits for room only where one does not fit or the caller chose the shape.
+// The shape and item of a launch that there is room for beside the launches of other streams that
+// wait for their own workgroups too.  While others have room or wait for it, a launch takes no more
+// workgroups per replica than one of all replicas does; where that has no room, fewer, down to one,
+// which needs none; and it waits for room only where one does not fit or the caller chose the shape.
 static gpr_status admit(gpr_system *S, int nrep, RunShape &sh, PersistItem &it, int &nblocks)
 {
     const bool fixed = chosen(S, S->groups_from, nrep);

@@ -1840,11 +1840,11 @@ __device__ __forceinline__ bool cycle_start(const PersistItem &it, long long &s0
 
 // A workgroup's place in a launch whose workgroups wait for one another: in the order in which they
 // start, not by blockIdx.  Of the first `mapped` workgroups, those with equal blockIdx mod 8 keep that
-// residue (they are of one XCD) and the order counts among them; the order of the others counts among
-// all of those.  So when a launch gets only part of the device, beside another process's, the workgroups that do run
-// make whole replicas but for one in each of these rows; the whole ones end and make room, where
-// workgroups placed by blockIdx could all be waiting for others that have none.  (The last to ask
-// clears the counter for the next launch.)
+// residue (they are of one XCD) and the order counts among them; the order of the others counts
+// among all of those.  So when a launch gets only part of the device, beside another process's, the
+// workgroups that do run make whole replicas but for one in each of these rows; the whole ones end
+// and make room, where workgroups placed by blockIdx could all be waiting for others that have none.
+// (The last to ask clears the counter for the next launch.)
 __device__ __forceinline__ int start_place(int *ticket, int mapped)
 {
     __shared__ int place;
@@ -1868,7 +1868,8 @@ __global__ void __launch_bounds__(1024) k_persist(PersistItem it)
     long long s0 = it.s0;
     int t0 = it.t0;
     if (it.cyc && !cycle_start(it, s0, t0)) return;
-    // (with one workgroup per replica too, though it waits for none: a choice here cost the step loop registers, 6 to 11 % of a step)
+    // (with one workgroup per replica too, though it waits for none: a choice between the two here
+    // cost the step loop 8 registers and 32 bytes of scratch, 5 to 11 % of a step)
     const int local = start_place(it.dev->ticket, it.xcd ? (int)gridDim.x : 0);
     if (!persist_place(it, local, set, g) || set + it.roff >= it.nrep) return;
     persist_replica(*it.dev, it.sp.G, it.sp.lmax, it.sp.bnd[g], it.sp.bnd[g + 1], it.sp.bu[g], it.sp.bu[g + 1], it.sp.bi,

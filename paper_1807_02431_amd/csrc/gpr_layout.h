@@ -20,9 +20,9 @@ struct AtomRanges {
 // loop covers 16 atoms of one group), with boundaries placed where the running sum of the per-atom
 // work estimate crosses g/G of the total.  No range is empty: the position exchange has a group
 // overwrite its words of two steps before once every other group's words of the last step are
-// there, and a group without atoms writes none, so nobody would wait for it to read.  Each group gets
-// a block of 16 atoms at least, and a replica of fewer blocks than G runs on fewer groups, the next power of
-// two down.
+// there, and a group without atoms writes none, so nobody would wait for it to read.  Each group
+// gets a block of 16 atoms at least, and a replica of fewer blocks than G runs on fewer groups, the
+// next power of two down.
 inline AtomRanges atom_ranges(const std::vector<double> &work, int n, int np, int G)
 {
     const int nblk = (n + 15) / 16;
@@ -50,9 +50,10 @@ inline AtomRanges atom_ranges(const std::vector<double> &work, int n, int np, in
 }
 
 // Pair-list margins by mass: an atom of less than four times the lightest's mass (light: 1/m above
-// im_light) may move half the skin between builds, any other one `heavy` times that, in proportion to
-// how much slower the lightest of them is, times 1.35 (measured on masses of 1 and 12 to 16: with 1.7, 2.2 and
-// 3.0, 20-step launches take 2 % less, 1,000-step launches 1 to 3 % more and plain steps 4 to 6 % more).
+// im_light) may move half the skin between builds, any other one `heavy` times that, in proportion
+// to how much slower the lightest of them is, times 1.35 (measured on masses of 1 and 12 to 16: with
+// 1.7, 2.2 and 3.0, 20-step launches take 2 % less, 1,000-step launches 1 to 3 % more and plain
+// steps 4 to 6 % more).
 struct MarginRule {
     float im_light;       // 0: every atom is light
     double heavy;

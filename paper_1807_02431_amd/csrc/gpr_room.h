@@ -3,9 +3,9 @@
 //
 // A launch with several workgroups per replica ends only if all groups of a replica run at the same
 // time.  One launch fits the device by itself; two on different streams, each asking for more
-// than half of it, could be placed in part each and then wait for ever (until the bounded spin ends).  So
-// every such launch of the process takes room here first, one unit for each compute unit, and gives
-// it back when the host has waited for it.  Launches on one stream follow each other and share their
+// than half of it, could be placed in part each and then wait until the bounded spin ends.  So every
+// such launch of the process takes room here first, one unit for each compute unit, and gives it
+// back when the host has waited for it.  Launches on one stream follow each other and share their
 // room.  Who takes room holds none while waiting for it and gives it back without taking more, so
 // every wait ends; waiting is first come, first served.
 #pragma once
