@@ -2,7 +2,6 @@
 replicas has more workgroups than the shapes it tries."""
 import time
 
-import numpy as np
 import pytest
 
 from test_gpu_small import _same, _spec
@@ -21,11 +20,11 @@ def test_tuned_is_not_slower_than_untuned(kind, n, R):
     took = []
     for s in (a, b):
         t = []
-        for _ in range(5):
+        for _ in range(9):
             t0 = time.perf_counter()
             s.advance(400)
             t.append(time.perf_counter() - t0)
-        took.append(float(np.median(t)))
+        took.append(min(t))
     print("tuned", took[0], "untuned", took[1], flush=True)
     assert took[0] < 1.2 * took[1]         # (12.7 against 9.2 us a step before, and the runs of one side differ by 1 %)
     _same(a, b)
